@@ -75,6 +75,42 @@ __device__ __forceinline__ double tanh_f64(double x)
     return m * r;
 }
 
+// The same from a table in LDS, for the FP64 embedding passes, which evaluate 45 of these per
+// 16-pair chunk and share the FP64 unit with their matrix products. With x0 = k / 32 the node nearest
+// to |x| and d = |x| - x0 (exact, |d| <= 1/64), t = tanh x0 from the table, u = tanh d = d - d^3/3 +
+// 2 d^5/15 - 17 d^7/315 (next term below 1e-16 relative):
+//   tanh |x| = (t + u) / (1 + t u) = t + u (1 - t^2) / (1 + t u),
+// and, with e = t u (|e| < 1/64), 1 / (1 + e) = (1 - e)(1 + e^2)(1 + e^4) up to e^8 < 4e-15, which
+// the factor u scales below 1e-16. 19 FP64 operations and an LDS read instead of the routine above's
+// 41 and a reciprocal. |x| is clamped to TH_MAX, past which tanh is +-1 in double; NaN propagates (the
+// index is bounded). Against the 80-bit C library over [-25, 25] and down to 1e-15: within 2 ulp
+// relative and 1.1e-16 absolute (the routine above: 3 ulp, 1.5 ulp(1)).
+constexpr int TH_STEP = 32;
+constexpr double TH_MAX = 19.5;
+constexpr int TH_N = (int)(TH_MAX * TH_STEP) + 1;
+__device__ __forceinline__ double tanh_tab(double x, const double* th)
+{
+    const double ax = __builtin_fabs(x), xa = ax > TH_MAX ? TH_MAX : ax;
+    // adding 1.5 x 2^52 rounds to the nearest integer and leaves it in the low word
+    const double kb = __builtin_fma(xa, (double)TH_STEP, 6755399441055744.0);
+    const unsigned k = min((unsigned)__double_as_longlong(kb), (unsigned)(TH_N - 1));
+    const double d = __builtin_fma(kb - 6755399441055744.0, -1.0 / TH_STEP, xa);
+    const double t = th[k];
+    const double q = d * d;
+    double p = __builtin_fma(q, -17.0 / 315.0, 2.0 / 15.0);
+    p = __builtin_fma(q, p, -1.0 / 3.0);
+    const double u = __builtin_fma(d * q, p, d);
+    const double e = t * u, e2 = e * e, e4 = e2 * e2;
+    double v = u * __builtin_fma(-t, t, 1.0);
+    v = __builtin_fma(-e, v, v);
+    v = __builtin_fma(e2, v, v);
+    return __builtin_copysign(t + __builtin_fma(e4, v, v), x);
+}
+__device__ __forceinline__ void tanh_tab_fill(double* th)
+{
+    for (int i = threadIdx.x; i < TH_N; i += blockDim.x) th[i] = tanh((double)i / TH_STEP);
+}
+
 // FP64: v_mfma_f64_16x16x4f64, four instructions per 16-wide K-chunk. Output register r of lane
 // group g holds row g + 4r. Weight matrices are stored with each 16-wide K-chunk permuted so that
 // the four K values a lane needs (g, g+4, g+8, g+12) are contiguous.
@@ -100,14 +136,18 @@ struct PF64 {
         return f;
     }
     __device__ static void mma(accv& d, const frag& a, const frag& b) {
-        d = __builtin_amdgcn_mfma_f64_16x16x4f64(a.v[0], b.v[0], d, 0, 0, 0);
-        d = __builtin_amdgcn_mfma_f64_16x16x4f64(a.v[1], b.v[1], d, 0, 0, 0);
-        d = __builtin_amdgcn_mfma_f64_16x16x4f64(a.v[2], b.v[2], d, 0, 0, 0);
-        d = __builtin_amdgcn_mfma_f64_16x16x4f64(a.v[3], b.v[3], d, 0, 0, 0);
+        mma(d, a, b, 4);
+    }
+    // the first n of the fragment's four K values per lane (the others have zero weights)
+    __device__ static void mma(accv& d, const frag& a, const frag& b, int n) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (v < n) d = __builtin_amdgcn_mfma_f64_16x16x4f64(a.v[v], b.v[v], d, 0, 0, 0);
     }
     __device__ static acc act(acc x) { return tanh_f64(x); }
+    __device__ static acc act(acc x, const double* th) { return tanh_tab(x, th); }
     // tanh(x + b) from the bias as staged (unscaled)
-    __device__ static acc act_b(acc x, acc b) { return tanh_f64(x + b); }
+    __device__ static acc act_b(acc x, acc b, const double* th) { return tanh_tab(x + b, th); }
     static constexpr double BIAS_SCALE = 1.0;
 };
 
@@ -170,9 +210,11 @@ struct PMIX {
         d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.h, b.l, d, 0, 0, 0);
         d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.h, b.h, d, 0, 0, 0);
     }
+    __device__ static void mma(accv& d, const frag& a, const frag& b, int) { mma(d, a, b); }
     __device__ static acc act(acc x) { return tanh_fast(x); }
+    __device__ static acc act(acc x, const double*) { return tanh_fast(x); }
     // tanh(x + b) from the bias as staged (K b)
-    __device__ static acc act_b(acc x, acc kb) { return tanh_scaled(__builtin_fmaf(x, TANH_K, kb)); }
+    __device__ static acc act_b(acc x, acc kb, const double*) { return tanh_scaled(__builtin_fmaf(x, TANH_K, kb)); }
     static constexpr float BIAS_SCALE = TANH_K;
 };
 
@@ -211,9 +253,11 @@ struct PBF16 {
     __device__ static void mma(accv& d, const frag& a, const frag& b) {
         d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.h, b.h, d, 0, 0, 0);
     }
+    __device__ static void mma(accv& d, const frag& a, const frag& b, int) { mma(d, a, b); }
     __device__ static acc act(acc x) { return tanh_fast(x); }
+    __device__ static acc act(acc x, const double*) { return tanh_fast(x); }
     // tanh(x + b) from the bias as staged (K b)
-    __device__ static acc act_b(acc x, acc kb) { return tanh_scaled(__builtin_fmaf(x, TANH_K, kb)); }
+    __device__ static acc act_b(acc x, acc kb, const double*) { return tanh_scaled(__builtin_fmaf(x, TANH_K, kb)); }
     static constexpr float BIAS_SCALE = TANH_K;
 };
 
@@ -239,14 +283,17 @@ struct PF32 {
     __device__ static frag lds(const char* p) { frag f; f.v = *reinterpret_cast<const f4*>(p); return f; }
     __device__ static frag load(const wt* p, int64_t) { frag f; f.v = *reinterpret_cast<const f4*>(p); return f; }
     __device__ static void mma(accv& d, const frag& a, const frag& b) {
-        d = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[0], b.v[0], d, 0, 0, 0);
-        d = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[1], b.v[1], d, 0, 0, 0);
-        d = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[2], b.v[2], d, 0, 0, 0);
-        d = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[3], b.v[3], d, 0, 0, 0);
+        mma(d, a, b, 4);
+    }
+    __device__ static void mma(accv& d, const frag& a, const frag& b, int n) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (v < n) d = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[v], b.v[v], d, 0, 0, 0);
     }
     __device__ static acc act(acc x) { return tanh_fast(x); }
+    __device__ static acc act(acc x, const double*) { return tanh_fast(x); }
     // tanh(x + b) from the bias as staged (K b)
-    __device__ static acc act_b(acc x, acc kb) { return tanh_scaled(__builtin_fmaf(x, TANH_K, kb)); }
+    __device__ static acc act_b(acc x, acc kb, const double*) { return tanh_scaled(__builtin_fmaf(x, TANH_K, kb)); }
     static constexpr float BIAS_SCALE = TANH_K;
 };
 
@@ -340,6 +387,11 @@ template <class P, bool FWD = false, bool TAB = false> struct EmbCfg {
     static constexpr int ROW3 = (N2P / P::VPL) * P::GB + 16;
     static constexpr int NC1 = K2P / P::KC;     // K-chunks of layer 2 (input 25, padded)
     static constexpr int NC2 = N2P / P::KC;     // K-chunks of layer 3 (input 50, padded)
+    // The skip-aligned order fills registers [0, NU1) of layer 1 and [0, NU2) of layer 2 (emb_feat;
+    // group 0 has the most features); the others hold zeros, so their activations and, in the 4-deep
+    // instructions, their K steps are left out. K values of chunk c in use: ku(NU, c).
+    static constexpr int NU1 = emb_ns(0), NU2 = 2 * emb_ns(0);
+    __device__ static constexpr int ku(int nu, int c) { return nu - c * P::VPL < P::VPL ? nu - c * P::VPL : P::VPL; }
 };
 
 // Fragment of row `row`, K-group `grp` (= 4 * chunk + lane group) from a staged block with `rowb`
@@ -581,6 +633,7 @@ __global__ void __launch_bounds__((EmbCfg<P, true, TAB>::NW * 64)) k_embed_fwd(E
     __shared__ acc s_z2[TAB ? 1 : NW][16][Z2S];
     __shared__ acc s_R[NW][16][4];
     __shared__ double s_x[NW][16];
+    __shared__ double s_th[Cfg::F64 && !TAB ? TH_N : 1];   // tanh nodes (FP64 network)
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform (scalar registers)
     const int lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
@@ -588,6 +641,7 @@ __global__ void __launch_bounds__((EmbCfg<P, true, TAB>::NW * 64)) k_embed_fwd(E
     const int a0 = blockIdx.x * APB;
     const int a1 = min(a0 + APB, A.natoms);
     if (a0 >= a1) return;
+    if constexpr (Cfg::F64 && !TAB) tanh_tab_fill(s_th);   // (ordered by the barriers around stage_net)
     const int t_lo = A.itype[a0], t_hi = A.itype[a1 - 1];
     const int nets = A.type_one_side ? A.ntypes : A.ntypes * A.ntypes;
     const int npass = E3 ? A.ntypes * A.ntypes : A.ntypes;
@@ -694,17 +748,19 @@ __global__ void __launch_bounds__((EmbCfg<P, true, TAB>::NW * 64)) k_embed_fwd(E
                     for (int c = 0; c < Cfg::NC1; ++c) {
 #pragma unroll
                         for (int v = 0; v < P::VPL; ++v) {
-                            const int k = P::kidx(c, g, v);
-                            z1[c * P::VPL + v] = s_vec[EV_WH1 + k] * P::act((acc)s * s_vec[EV_W1 + k] + s_vec[EV_B1 + k]);
+                            const int k = P::kidx(c, g, v), u = c * P::VPL + v;
+                            z1[u] = u < Cfg::NU1 ? s_vec[EV_WH1 + k] * P::act((acc)s * s_vec[EV_W1 + k] + s_vec[EV_B1 + k], s_th) : (acc)0;
                         }
                         B1[c] = P::make(&z1[c * P::VPL]);
                     }
                     // layer 2 (25 -> 50), transposed: pre2^T = W2^T z1^T
                     accv acc2[4];
+#pragma unroll
                     for (int t = 0; t < 4; ++t) {
                         zero4(acc2[t]);
+#pragma unroll
                         for (int c = 0; c < Cfg::NC1; ++c)
-                            P::mma(acc2[t], lds_frag<P>(s_w2, Cfg::ROW2, 16 * t + c16, 4 * c + g), B1[c]);
+                            P::mma(acc2[t], lds_frag<P>(s_w2, Cfg::ROW2, 16 * t + c16, 4 * c + g), B1[c], Cfg::ku(Cfg::NU1, c));
                     }
                     wave_sync();
                     // skip: register u = 4t + r of layer 2 adds register u / 2 of layer 1 (same lane)
@@ -714,7 +770,9 @@ __global__ void __launch_bounds__((EmbCfg<P, true, TAB>::NW * 64)) k_embed_fwd(E
 #pragma unroll
                         for (int r = 0; r < 4; ++r) {
                             const int n = 16 * t + P::orow(g, r);
-                            zt[t][r] = s_vec[EV_WH2 + n] * P::act_b(acc2[t][r], s_vec[EV_B2 + n]) + z1[(4 * t + r) >> 1];
+                            zt[t][r] = 4 * t + r < Cfg::NU2
+                                           ? s_vec[EV_WH2 + n] * P::act_b(acc2[t][r], s_vec[EV_B2 + n], s_th) + z1[(4 * t + r) >> 1]
+                                           : (acc)0;
                             s_z2[wave][p][n] = zt[t][r];
                         }
                     // output tiles -> K-chunks of layer 3: chunk c, value v is tile c*KC/16 + v/4, row r = v%4
@@ -725,33 +783,48 @@ __global__ void __launch_bounds__((EmbCfg<P, true, TAB>::NW * 64)) k_embed_fwd(E
                         A3[c] = P::make(x);
                     }
                     // layer 3 (50 -> 100), untransposed: pre3 = z2 W3
-                    accv acc3[7];
-                    for (int tm = 0; tm < 7; ++tm) {
-                        zero4(acc3[tm]);
+                    auto mm3 = [&](int tm, accv& o) {
+                        zero4(o);
+#pragma unroll
                         for (int c = 0; c < Cfg::NC2; ++c) {
                             const frag Bw = W3LDS ? lds_frag<P>(s_w3, Cfg::ROW3, 16 * tm + c16, 4 * c + g)
                                                   : P::load(gw3 + (16 * tm + c16) * N2P + P::KC * c + P::VPL * g, gpl);
-                            P::mma(acc3[tm], A3[c], Bw);
+                            P::mma(o, A3[c], Bw, Cfg::ku(Cfg::NU2, c));
                         }
-                    }
-                    wave_sync();
-                    if constexpr (!Cfg::F64)
-                        for (int r = 0; r < 4; ++r) Rq[r] = s_R[wave][P::orow(g, r)][c16 & 3];
+                    };
                     // G = w_hat tanh(pre3 + b) + z2 at the skip source of row m = 16 tm + c16 (its
                     // register u in lane group ogrp(c16) takes layer-2 register u / 2 of that group);
                     // contraction T += G^T R (padding rows have zero weights, G = 0, and are not stored)
                     const int gc = P::ogrp(c16), rc = P::oreg(c16);
-                    for (int tm = 0; tm < 7; ++tm) {
+                    auto epi3 = [&](int tm, const accv& o) {
                         const int m = 16 * tm + c16;
-                        if (Cfg::F64 && emb_feat(3, gc, 4 * tm + rc) < 0) continue;
                         const int u2 = (4 * tm + rc) >> 1;
                         const int n2 = 16 * (u2 >> 2) + P::orow(gc, u2 & 3);
                         const acc wh = s_vec[EV_WH3 + m], bb = s_vec[EV_B3 + m];
                         for (int r = 0; r < 4; ++r) {
                             const int q = P::orow(g, r);
-                            const acc G = wh * P::act_b(acc3[tm][r], bb) + s_z2[wave][q][n2];
+                            const acc G = wh * P::act_b(o[r], bb, s_th) + s_z2[wave][q][n2];
                             add_G(tm, r, q, G);
                         }
+                    };
+                    if constexpr (Cfg::F64) {
+                        // one tile at a time, the next tile's products issued before the current
+                        // tile's epilogue: two tiles of accumulators live (all seven spill)
+                        wave_sync();
+                        accv a3[2];
+                        mm3(0, a3[0]);
+#pragma unroll
+                        for (int tm = 0; tm < 7; ++tm) {
+                            if (tm + 1 < 7) mm3(tm + 1, a3[(tm + 1) & 1]);
+                            epi3(tm, a3[tm & 1]);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                    } else {
+                        accv acc3[7];
+                        for (int tm = 0; tm < 7; ++tm) mm3(tm, acc3[tm]);
+                        wave_sync();
+                        for (int r = 0; r < 4; ++r) Rq[r] = s_R[wave][P::orow(g, r)][c16 & 3];
+                        for (int tm = 0; tm < 7; ++tm) epi3(tm, acc3[tm]);
                     }
                 }
                 if (last) {
@@ -819,11 +892,13 @@ __global__ void __launch_bounds__((EmbCfg<P, false, TAB>::NW * 64)) k_embed_bwd(
     // the LDS atom table of the walk (its reads do not wait on the in-order vector memory counter,
     // which also holds the force atomics)
     __shared__ int s_wl[NW][2 * WL_MAX];
+    __shared__ double s_th[Cfg::F64 && !TAB ? TH_N : 1];   // tanh nodes (FP64 network)
     // three-body: dE/dR_j of every slot of the wave's atom
     __shared__ __attribute__((aligned(16))) acc s_dRs[E3 ? NW : 1][E3 ? E3_MAXN : 1][4];
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform (scalar registers)
     const int lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
+    if constexpr (Cfg::F64 && !TAB) tanh_tab_fill(s_th);   // (ordered by the barriers around stage_net)
     for (int e = lane; e < N3P * 4; e += 64) s_dT[wave][e >> 2][e & 3] = 0;
     for (int e = lane; e < 16 * 12; e += 64) s_pair[wave][e / 12][e % 12] = 0.0;
     if constexpr (E3)
@@ -945,23 +1020,27 @@ __global__ void __launch_bounds__((EmbCfg<P, false, TAB>::NW * 64)) k_embed_bwd(
                     for (int c = 0; c < Cfg::NC1; ++c) {
 #pragma unroll
                         for (int v = 0; v < P::VPL; ++v) {
-                            const int k = P::kidx(c, g, v);
+                            const int k = P::kidx(c, g, v), u = c * P::VPL + v;
+                            z1[u] = z1d[u] = 0;
+                            if (u >= Cfg::NU1) continue;
                             const acc w1 = s_vec[EV_W1 + k], wh = s_vec[EV_WH1 + k];
-                            const acc t1 = P::act((acc)s * w1 + s_vec[EV_B1 + k]);
-                            z1[c * P::VPL + v] = wh * t1;
-                            z1d[c * P::VPL + v] = wh * (1 - t1 * t1) * w1;
+                            const acc t1 = P::act((acc)s * w1 + s_vec[EV_B1 + k], s_th);
+                            z1[u] = wh * t1;
+                            z1d[u] = wh * (1 - t1 * t1) * w1;
                         }
                         B1[c] = P::make(&z1[c * P::VPL]);
                         B1d[c] = P::make(&z1d[c * P::VPL]);
                     }
                     accv acc2[4], acc2d[4];
+#pragma unroll
                     for (int t = 0; t < 4; ++t) {
                         zero4(acc2[t]);
                         zero4(acc2d[t]);
+#pragma unroll
                         for (int c = 0; c < Cfg::NC1; ++c) {
                             const frag W = lds_frag<P>(s_w2, Cfg::ROW2, 16 * t + c16, 4 * c + g);
-                            P::mma(acc2[t], W, B1[c]);
-                            P::mma(acc2d[t], W, B1d[c]);
+                            P::mma(acc2[t], W, B1[c], Cfg::ku(Cfg::NU1, c));
+                            P::mma(acc2d[t], W, B1d[c], Cfg::ku(Cfg::NU1, c));
                         }
                     }
                     // skip: register u = 4t + rr of layer 2 adds register u / 2 of layer 1 (same lane)
@@ -971,7 +1050,9 @@ __global__ void __launch_bounds__((EmbCfg<P, false, TAB>::NW * 64)) k_embed_bwd(
 #pragma unroll
                         for (int rr = 0; rr < 4; ++rr) {
                             const int n = 16 * t + P::orow(g, rr), u1 = (4 * t + rr) >> 1;
-                            const acc t2 = P::act_b(acc2[t][rr], s_vec[EV_B2 + n]);
+                            zt[t][rr] = ztd[t][rr] = 0;
+                            if (4 * t + rr >= Cfg::NU2) continue;
+                            const acc t2 = P::act_b(acc2[t][rr], s_vec[EV_B2 + n], s_th);
                             const acc wh = s_vec[EV_WH2 + n];
                             zt[t][rr] = wh * t2 + z1[u1];
                             ztd[t][rr] = wh * (1 - t2 * t2) * acc2d[t][rr] + z1d[u1];
@@ -997,8 +1078,8 @@ __global__ void __launch_bounds__((EmbCfg<P, false, TAB>::NW * 64)) k_embed_bwd(
                         for (int c = 0; c < Cfg::NC2; ++c) {
                             const frag W = W3LDS ? lds_frag<P>(s_w3, Cfg::ROW3, 16 * tm + c16, 4 * c + g)
                                                  : P::load(gw3 + (16 * tm + c16) * N2P + P::KC * c + P::VPL * g, gpl);
-                            P::mma(o, W, B3[c]);
-                            P::mma(od, W, B3d[c]);
+                            P::mma(o, W, B3[c], Cfg::ku(Cfg::NU2, c));
+                            P::mma(od, W, B3d[c], Cfg::ku(Cfg::NU2, c));
                         }
                     };
                     f4 dRq, Hq;   // FP32 paths: the contraction's accumulators (see outer4)
@@ -1008,7 +1089,7 @@ __global__ void __launch_bounds__((EmbCfg<P, false, TAB>::NW * 64)) k_embed_bwd(
 #pragma unroll
                         for (int rr = 0; rr < 4; ++rr) {
                             const int m = 16 * tm + P::orow(g, rr), u2 = (4 * tm + rr) >> 1;
-                            const acc t3 = P::act_b(o[rr], s_vec[EV_B3 + m]);
+                            const acc t3 = P::act_b(o[rr], s_vec[EV_B3 + m], s_th);
                             const acc wh = s_vec[EV_WH3 + m];
                             const acc G = wh * t3 + zt[u2 >> 2][u2 & 3];
                             const acc Gd = wh * (1 - t3 * t3) * od[rr] + ztd[u2 >> 2][u2 & 3];
