@@ -241,6 +241,23 @@ struct Planes {
     }
 };
 
+// One matrix of the fragment-major 16x16x4 weights (k_fitd): `rows` x `kdim`, zero-padded to whole
+// tiles and chunks, at `base` of P (FP64 or FP32).
+template <class Fn>
+void pack_frags4(Planes& P, size_t base, int ntiles, int nch, int rows, int kdim, Fn&& w)
+{
+    const bool f64 = P.precision == DPK_FP64;
+    for (int c = 0; c < nch; ++c)
+        for (int t = 0; t < ntiles; ++t, base += 256)
+            for (int lane = 0; lane < 64; ++lane)
+                for (int v = 0; v < 4; ++v) {
+                    const int g = lane >> 4, row = 16 * t + (lane & 15), k = 16 * c + (f64 ? g + 4 * v : 4 * g + v);
+                    const double x = row < rows && k < kdim ? w(row, k) : 0.0;
+                    if (f64) P.d[base + (v >> 1) * 128 + lane * 2 + (v & 1)] = x;
+                    else P.f[base + lane * 4 + v] = (float)x;
+                }
+}
+
 }  // namespace
 
 struct dpk_ctx {
@@ -552,12 +569,13 @@ int upload_model(dpk_ctx* c)
     const dpk_model* m = c->model;
     const int prec = c->precision, nets = m->nets, nt = m->desc.ntypes;
     const bool f64 = prec == DPK_FP64;
-    // FP64 and FP32 fit on the 16x16x4 MFMA with dense row-major weights (k_fit_dense); the BF16
-    // paths use fragment-major weights (k_fitx), except for a descriptor of M values, which every
-    // precision other than FP64 fits on the dense FP32 kernel
+    // FP64 fits on the 16x16x4 MFMA with fragment-major weights (k_fitd), FP32 with row-major weights
+    // (k_fit_dense), the BF16 paths with the 32-deep fragments of k_fitx; a descriptor of M values
+    // fits in FP32 on k_fitd in every precision other than FP64
     const bool radial = m->desc.descriptor != DPK_SE_E2_A;
     const bool dense = dense_fitting(c);
     const int fprec = f64 ? DPK_FP64 : DPK_FP32;   // precision of the dense fitting weights
+    const bool frag4 = dense && (f64 || radial);   // fragment-major 16x16x4 weights (k_fitd)
     std::vector<double> ev((size_t)nets * EVEC, 0.0), fv((size_t)nt * FVEC, 0.0);
     Planes em, fm;
     em.init(prec, (size_t)nets * EM_SIZE);
@@ -622,6 +640,16 @@ int upload_model(dpk_ctx* c)
         const size_t base = (size_t)t * FM_SIZE;
         // layer 1: W1^T [240][K] and W1 [K][240], K = 1600 (M x M_<) or 112 (M, zero-padded)
         const int nin = radial ? E2 : DD, kw = radial ? N3P : DD;
+        if (frag4) {
+            pack_frags4(fm, base + FM_W1T, 15, kw / 16, FW, nin, [&](int o, int f) { return L[0].W[(size_t)f * FW + o]; });
+            pack_frags4(fm, base + FM_W1, kw / 16, 15, nin, FW, [&](int f, int o) { return L[0].W[(size_t)f * FW + o]; });
+            for (int li = 1; li <= 2; ++li) {
+                const double* w = L[li].W;
+                pack_frags4(fm, base + (li == 1 ? FM_W2T : FM_W3T), 15, 15, FW, FW, [&](int o, int i) { return w[(size_t)i * FW + o]; });
+                pack_frags4(fm, base + (li == 1 ? FM_W2 : FM_W3), 15, 15, FW, FW, [&](int i, int o) { return w[(size_t)i * FW + o]; });
+            }
+            continue;
+        }
         for (int f = 0; f < nin; ++f)
             for (int o = 0; o < FW; ++o) {
                 const double w = L[0].W[(int64_t)f * FW + o];

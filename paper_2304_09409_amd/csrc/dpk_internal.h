@@ -25,7 +25,10 @@ constexpr int EV_W1 = 0, EV_B1 = K2P, EV_WH1 = 2 * K2P, EV_B2 = 3 * K2P, EV_WH2 
 // Offsets inside one packed fitting vector block.
 constexpr int FV_B1 = 0, FV_WH1 = FW, FV_B2 = 2 * FW, FV_WH2 = 3 * FW, FV_B3 = 4 * FW,
               FV_WH3 = 5 * FW, FV_W4 = 6 * FW, FV_B4 = 7 * FW, FV_WH4 = 7 * FW + 1;
-// Matrices of one fitting net, each [rows][cols] row-major, in this order.
+// Matrices of one fitting net on the 16x16x4 MFMA, [rows][cols], in this order: row-major with the K
+// order of kphys (FP32), or fragment-major (k_fitd): fragment (c, t) of 256 values at c * ntiles + t is
+// 16-row tile t, columns 16c .. 16c + 15; lane 16g + i holds row 16t + i and the four columns of its
+// lane group, in FP64 as two halves [2][64 lanes][2], in FP32 as [64 lanes][4].
 constexpr int64_t FM_W1T = 0;                          // [240][1600]
 constexpr int64_t FM_W1 = FM_W1T + (int64_t)FW * DD;   // [1600][240]
 constexpr int64_t FM_W2T = FM_W1 + (int64_t)DD * FW;   // [240][240]
@@ -33,6 +36,7 @@ constexpr int64_t FM_W2 = FM_W2T + FW * FW;
 constexpr int64_t FM_W3T = FM_W2 + FW * FW;
 constexpr int64_t FM_W3 = FM_W3T + FW * FW;
 constexpr int64_t FM_SIZE = FM_W3 + FW * FW;
+constexpr int RAD_K = N3P;   // padded width of a descriptor of M values (W1^T [240][112], W1 [112][240])
 // Fragment-major fitting weights of the BF16 paths (split and plain). A fragment is the A operand
 // of one v_mfma_f32_16x16x32_bf16 for one 16-row tile and one 32-wide K-chunk: the BF16 hi parts
 // of the 64 lanes (8 values, 16 B each), then the lo parts. Lane 16g + i holds row 16t + i and
@@ -204,9 +208,12 @@ struct EmbArgs {
 };
 
 // The arguments of the model that blockIdx.y selects.
+// (Pointer arithmetic, not through an integer: the compiler then still knows that the result points to
+// global memory. As an integer it became a generic pointer, whose loads also occupy the LDS counter,
+// and the ensemble kernels held their arguments in scratch.)
 template <class T> __host__ __device__ inline T* byte_offset(T* p, int64_t bytes)
 {
-    return p ? reinterpret_cast<T*>(reinterpret_cast<uintptr_t>(p) + bytes) : p;
+    return p ? (T*)((char*)p + bytes) : p;
 }
 __device__ inline EmbArgs model_args(const EmbArgs& A0)
 {

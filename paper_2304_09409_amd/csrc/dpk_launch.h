@@ -75,6 +75,8 @@ void launch_spatial_order(int n, const double4* cand, const int* cell_of, int* o
 int tab_blocks(int64_t natoms, int ncu);
 int tab_atoms_per_block_min();
 void launch_fit(int precision, const FitArgs& a, hipStream_t s);
+// fitting kernel of the FP64 path (every descriptor), or FP32 for a descriptor of M values
+void launch_fitd(bool f64, const FitArgs& a, hipStream_t s);
 // BF16 fitting kernel (split = three products); 16-atom tiles per block for a frame of natoms
 void launch_fitx(bool split, const FitArgs& a, hipStream_t s);
 int fitx_tiles_per_block(int natoms, int ncu);

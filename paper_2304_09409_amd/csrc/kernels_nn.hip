@@ -34,82 +34,11 @@
 
 namespace dpk {
 
-typedef __bf16 bf4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------------------------------------
 // Precision policies
 // ---------------------------------------------------------------------------------------------
-
-// FP64 hyperbolic tangent, tanh x = m / (m + 2) with m = e^{2x} - 1, written for the FP64 paths
-// (the device library's general routine costs about three times the instructions; the
-// embedding's FP64 passes are bound by these evaluations). Range reduction: 2x = n ln 2 + g with
-// n = rint(2x log2 e), |g| <= ln 2 / 2; e^g - 1 = g (1 + g/2! + ... + g^12/13!) (Taylor remainder
-// below 1e-17 relative on that interval); m = 2^n (e^g - 1) + (2^n - 1), free of cancellation for
-// small |x|. The quotient uses the hardware reciprocal refined by two Newton steps. |x| is clamped
-// to 20, past which tanh is +-1 in double; NaN propagates. Measured against the C library over
-// [-25, 25] and down to |x| = 1e-15: relative error within 3 ulp, absolute within 1.5 ulp(1).
-__device__ __forceinline__ double tanh_f64(double x)
-{
-    const double xc = x > 20.0 ? 20.0 : (x < -20.0 ? -20.0 : x);
-    const double n = __builtin_rint(xc * 2.8853900817779268);       // 2 log2 e
-    const double g = __builtin_fma(-n, 0.69314718055994531, 2.0 * xc);
-    double p = 1.0 / 6227020800.0;                                   // 1/13!
-    p = __builtin_fma(p, g, 1.0 / 479001600.0);
-    p = __builtin_fma(p, g, 1.0 / 39916800.0);
-    p = __builtin_fma(p, g, 1.0 / 3628800.0);
-    p = __builtin_fma(p, g, 1.0 / 362880.0);
-    p = __builtin_fma(p, g, 1.0 / 40320.0);
-    p = __builtin_fma(p, g, 1.0 / 5040.0);
-    p = __builtin_fma(p, g, 1.0 / 720.0);
-    p = __builtin_fma(p, g, 1.0 / 120.0);
-    p = __builtin_fma(p, g, 1.0 / 24.0);
-    p = __builtin_fma(p, g, 1.0 / 6.0);
-    p = __builtin_fma(p, g, 0.5);
-    p = __builtin_fma(p, g, 1.0);
-    const double s = __builtin_amdgcn_ldexp(1.0, (int)n);
-    const double m = __builtin_fma(s, g * p, s - 1.0), d = m + 2.0;
-    double r = __builtin_amdgcn_rcp(d);
-    r = __builtin_fma(r, __builtin_fma(-d, r, 1.0), r);
-    r = __builtin_fma(r, __builtin_fma(-d, r, 1.0), r);
-    return m * r;
-}
-
-// The same from a table in LDS, for the FP64 embedding passes, which evaluate 45 of these per
-// 16-pair chunk and share the FP64 unit with their matrix products. With x0 = k / 32 the node nearest
-// to |x| and d = |x| - x0 (exact, |d| <= 1/64), t = tanh x0 from the table, u = tanh d = d - d^3/3 +
-// 2 d^5/15 - 17 d^7/315 (next term below 1e-16 relative):
-//   tanh |x| = (t + u) / (1 + t u) = t + u (1 - t^2) / (1 + t u),
-// and, with e = t u (|e| < 1/64), 1 / (1 + e) = (1 - e)(1 + e^2)(1 + e^4) up to e^8 < 4e-15, which
-// the factor u scales below 1e-16. 19 FP64 operations and an LDS read instead of the routine above's
-// 41 and a reciprocal. |x| is clamped to TH_MAX, past which tanh is +-1 in double; NaN propagates (the
-// index is bounded). Against the 80-bit C library over [-25, 25] and down to 1e-15: within 2 ulp
-// relative and 1.1e-16 absolute (the routine above: 3 ulp, 1.5 ulp(1)).
-constexpr int TH_STEP = 32;
-constexpr double TH_MAX = 19.5;
-constexpr int TH_N = (int)(TH_MAX * TH_STEP) + 1;
-__device__ __forceinline__ double tanh_tab(double x, const double* th)
-{
-    const double ax = __builtin_fabs(x), xa = ax > TH_MAX ? TH_MAX : ax;
-    // adding 1.5 x 2^52 rounds to the nearest integer and leaves it in the low word
-    const double kb = __builtin_fma(xa, (double)TH_STEP, 6755399441055744.0);
-    const unsigned k = min((unsigned)__double_as_longlong(kb), (unsigned)(TH_N - 1));
-    const double d = __builtin_fma(kb - 6755399441055744.0, -1.0 / TH_STEP, xa);
-    const double t = th[k];
-    const double q = d * d;
-    double p = __builtin_fma(q, -17.0 / 315.0, 2.0 / 15.0);
-    p = __builtin_fma(q, p, -1.0 / 3.0);
-    const double u = __builtin_fma(d * q, p, d);
-    const double e = t * u, e2 = e * e, e4 = e2 * e2;
-    double v = u * __builtin_fma(-t, t, 1.0);
-    v = __builtin_fma(-e, v, v);
-    v = __builtin_fma(e2, v, v);
-    return __builtin_copysign(t + __builtin_fma(e4, v, v), x);
-}
-__device__ __forceinline__ void tanh_tab_fill(double* th)
-{
-    for (int i = threadIdx.x; i < TH_N; i += blockDim.x) th[i] = tanh((double)i / TH_STEP);
-}
 
 // FP64: v_mfma_f64_16x16x4f64, four instructions per 16-wide K-chunk. Output register r of lane
 // group g holds row g + 4r. Weight matrices are stored with each 16-wide K-chunk permuted so that
@@ -144,23 +73,11 @@ struct PF64 {
         for (int v = 0; v < 4; ++v)
             if (v < n) d = __builtin_amdgcn_mfma_f64_16x16x4f64(a.v[v], b.v[v], d, 0, 0, 0);
     }
-    __device__ static acc act(acc x) { return tanh_f64(x); }
     __device__ static acc act(acc x, const double* th) { return tanh_tab(x, th); }
     // tanh(x + b) from the bias as staged (unscaled)
     __device__ static acc act_b(acc x, acc b, const double* th) { return tanh_tab(x + b, th); }
     static constexpr double BIAS_SCALE = 1.0;
 };
-
-// FP32 hyperbolic tangent: 1 - 2 / (exp(2x) + 1), with exp(2x) = 2^(K x), K = 2 log2 e, on the
-// hardware exp2 and the hardware reciprocal. Saturates to +-1 without overflow trouble (2^inf =
-// inf, 1/inf = 0). Absolute error about 1e-7. tanh_scaled takes y = K x, so that a bias staged as
-// K b folds into one FMA: tanh(x + b) = tanh_scaled(K x + K b).
-constexpr float TANH_K = 2.885390081777927f;
-__device__ __forceinline__ float tanh_scaled(float y)
-{
-    return 1.0f - 2.0f * __builtin_amdgcn_rcpf(__builtin_amdgcn_exp2f(y) + 1.0f);
-}
-__device__ __forceinline__ float tanh_fast(float x) { return tanh_scaled(x * TANH_K); }
 
 // Split BF16 on v_mfma_f32_16x16x32_bf16: each FP32 operand is hi + lo with both parts BF16; the
 // product is formed as lo*hi + hi*lo + hi*hi with FP32 accumulation, about 16 significant bits per
@@ -310,51 +227,6 @@ template <class V> __device__ __forceinline__ void zero4(V& v) { v[0] = 0; v[1] 
 __device__ __forceinline__ void outer4(f4& d, float a, float b)
 {
     d = __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, d, 0, 0, 0);
-}
-
-
-// Cross-lane sums over the four 16-lane groups of a wave on v_permlane32_swap (exchanges the
-// upper half of one register with the lower half of another: pairs groups g, g + 2) and
-// v_permlane16_swap (odd rows of one with even rows of the other: pairs g, g + 1).
-__device__ __forceinline__ void swap_halves(float& a, float& b, bool rows16)
-{
-    const auto r = rows16 ? __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false)
-                          : __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    a = __uint_as_float(r[0]);
-    b = __uint_as_float(r[1]);
-}
-__device__ __forceinline__ void swap_halves(double& a, double& b, bool rows16)
-{
-    const unsigned long long ua = __double_as_longlong(a), ub = __double_as_longlong(b);
-    unsigned alo = (unsigned)ua, ahi = (unsigned)(ua >> 32), blo = (unsigned)ub, bhi = (unsigned)(ub >> 32);
-    const auto rl = rows16 ? __builtin_amdgcn_permlane16_swap(alo, blo, false, false)
-                           : __builtin_amdgcn_permlane32_swap(alo, blo, false, false);
-    const auto rh = rows16 ? __builtin_amdgcn_permlane16_swap(ahi, bhi, false, false)
-                           : __builtin_amdgcn_permlane32_swap(ahi, bhi, false, false);
-    a = __longlong_as_double((long long)(((unsigned long long)rh[0] << 32) | rl[0]));
-    b = __longlong_as_double((long long)(((unsigned long long)rh[1] << 32) | rl[1]));
-}
-// Every lane receives the sum of v over the four lanes of its column (lane & 15).
-template <class T> __device__ __forceinline__ T sum_groups(T v)
-{
-    T a = v, b = v;
-    swap_halves(a, b, false);
-    v = a + b;
-    a = v;
-    b = v;
-    swap_halves(a, b, true);
-    return a + b;
-}
-// Lane group G receives the column sum of p[ksel(G)], ksel = {0, 2, 1, 3}.
-__device__ __forceinline__ int ksel(int g) { return ((g & 1) << 1) | (g >> 1); }
-template <class T> __device__ __forceinline__ T sum_groups4(const T* p)
-{
-    T a = p[0], b = p[1], c = p[2], d = p[3];
-    swap_halves(a, b, false);
-    swap_halves(c, d, false);
-    T q0 = a + b, q1 = c + d;
-    swap_halves(q0, q1, true);
-    return q0 + q1;
 }
 
 
@@ -661,8 +533,8 @@ __global__ void __launch_bounds__((EmbCfg<P, true, TAB>::NW * 64)) k_embed_fwd(E
             w.i = 0;
             w.c0 = 0;
             w.ac = 0;
-            w.have = w.find_atom(A, nullptr, a0, a1, wave, NW, APW, ti, tj, false);
-            w.fetch(A, tj, c16);
+            w.have = w.find_atom(A_, nullptr, a0, a1, wave, NW, APW, ti, tj, false);
+            w.fetch(A_, tj, c16);
             accv Tacc[7];
             while (w.have) {
                 double x = 0.0, y = 0.0, z = 0.0;
@@ -679,10 +551,10 @@ __global__ void __launch_bounds__((EmbCfg<P, true, TAB>::NW * 64)) k_embed_fwd(E
                 if (w.c0 >= w.np) {
                     ++w.i;
                     w.c0 = 0;
-                    w.have = w.find_atom(A, nullptr, a0, a1, wave, NW, APW, ti, tj, false);
+                    w.have = w.find_atom(A_, nullptr, a0, a1, wave, NW, APW, ti, tj, false);
                     last = true;
                 }
-                w.fetch(A, tj, c16);
+                w.fetch(A_, tj, c16);
                 if (cc0 == 0)
                     for (int t = 0; t < 7; ++t) zero4(Tacc[t]);
 
@@ -925,9 +797,9 @@ __global__ void __launch_bounds__((EmbCfg<P, false, TAB>::NW * 64)) k_embed_bwd(
             w.i = 0;
             w.c0 = 0;
             w.ac = 0;
-            if constexpr (!E3) w.template load_atoms<true>(s_wl[wave], A, a0, a1, wave, NW, APW, tj, lane);
-            w.have = w.template find_atom<true>(A, s_wl[wave], a0, a1, wave, NW, APW, ti, tj, true);
-            w.template fetch<true>(A, tj, c16);
+            if constexpr (!E3) w.template load_atoms<true>(s_wl[wave], A_, a0, a1, wave, NW, APW, tj, lane);
+            w.have = w.template find_atom<true>(A_, s_wl[wave], a0, a1, wave, NW, APW, ti, tj, true);
+            w.template fetch<true>(A_, tj, c16);
             acc pdT[DTL];
             for (int q = 0; q < DTL; ++q) {
                 const int e = lane + 64 * q;
@@ -955,10 +827,10 @@ __global__ void __launch_bounds__((EmbCfg<P, false, TAB>::NW * 64)) k_embed_bwd(
                 if (w.c0 >= w.np) {
                     ++w.i;
                     w.c0 = 0;
-                    w.have = w.template find_atom<true>(A, s_wl[wave], a0, a1, wave, NW, APW, ti, tj, true);
+                    w.have = w.template find_atom<true>(A_, s_wl[wave], a0, a1, wave, NW, APW, ti, tj, true);
                     last = true;
                 }
-                w.template fetch<true>(A, tj, c16);
+                w.template fetch<true>(A_, tj, c16);
                 if (cc0 == 0) {
                     // the prefetched dT of this atom goes to LDS, feature f to its layer-3 row; the
                     // next atom's is requested
@@ -1195,8 +1067,8 @@ __global__ void __launch_bounds__((EmbCfg<P, false, TAB>::NW * 64)) k_embed_bwd(
             double f[3] = {0.0, 0.0, 0.0}, vir[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
             for (int sl = lane; sl < A.nc; sl += 64) {
                 int t = 0;
-                while (t + 1 < nt && sl >= A.off[t + 1]) ++t;
-                if (sl - A.off[t] >= A.nnei[(size_t)a * nt + t]) continue;
+                while (t + 1 < nt && sl >= A_.off[t + 1]) ++t;
+                if (sl - A_.off[t] >= A.nnei[(size_t)a * nt + t]) continue;
                 const size_t slot = (size_t)a * A.nc + sl;
                 const double x = A.nl_r[3 * slot], y = A.nl_r[3 * slot + 1], z = A.nl_r[3 * slot + 2];
                 const int j = A.nl_j[slot];
@@ -1256,47 +1128,46 @@ __global__ void __launch_bounds__((EmbCfg<P, false, TAB>::NW * 64)) k_embed_bwd(
 }
 
 // ---------------------------------------------------------------------------------------------
-// Fitting net F_0 of the FP64 path (Sec. II.A.2, eq. fitting_energy): forward E_i and the input
-// gradient dE_i/dT through D = T T_<^T. Each wave owns 16 atoms and computes all 240 features of
-// every layer; the four waves of a block share the weight K-chunks, staged through LDS with
-// register double buffering. (The BF16 paths use k_fitx in kernels_fit.hip.)
+// Fitting net F_0 of the FP32 path's M x M_< descriptor (Sec. II.A.2, eq. fitting_energy): forward E_i
+// and the input gradient dE_i/dT through D = T T_<^T. Each wave owns 16 atoms and computes all 240
+// features of every layer; the four waves of a block share the weight K-chunks, staged through LDS
+// with register double buffering. (The BF16 paths use k_fitx in kernels_fit.hip, FP64 and the
+// descriptors of M values k_fitd in kernels_fitd.hip.)
 // ---------------------------------------------------------------------------------------------
 
-// Weight staging for the FP64 fitting kernel. A stage is ROWS rows x KC columns (K) of a row-major
-// matrix in global memory, stored per plane (BF16 hi, BF16 lo) or once (FP64). In LDS each row
-// holds KC/4 groups of four K values; a group is [hi0..3 lo0..3] (16 B) or [four doubles] (32 B),
-// exactly one lane's A fragment, and rows are padded by 16 B so the 16 rows a wave reads at once
-// fall in distinct banks. Global reads are 16-B pieces, issued into registers by load() one stage
-// ahead and written to LDS by store() after the MFMAs of the current stage.
+// Weight staging for the FP32 fitting kernel. A stage is ROWS rows x KC columns (K) of a row-major
+// matrix in global memory. In LDS each row holds KC/4 groups of four K values (16 B), exactly one
+// lane's A fragment, and rows are padded by 16 B so the 16 rows a wave reads at once fall in distinct
+// banks. Global reads are 16-B pieces, issued into registers by load() one stage ahead and written to
+// LDS by store() after the MFMAs of the current stage.
 template <class P, int ROWS, int KC, int NT = 256>
 struct FitStage {
     typedef typename P::wt wt;
-    static constexpr int GB = 4 * sizeof(wt) * P::NPL;       // bytes per group in LDS
+    static_assert(sizeof(wt) == 4 && P::NPL == 1, "one plane of floats");
+    static constexpr int GB = 16;                             // bytes per group in LDS
     static constexpr int ROWB = (KC / 4) * GB + 16;           // bytes per LDS row
     static constexpr int BYTES = ROWS * ROWB;
     static constexpr int EPP = 16 / sizeof(wt);               // elements per 16-B piece
     static constexpr int PPR = KC / EPP;                      // pieces per row and plane
-    static constexpr int TOTAL = ROWS * PPR * P::NPL;
+    static constexpr int TOTAL = ROWS * PPR;
     static constexpr int NP = (TOTAL + NT - 1) / NT;          // pieces per thread (NT threads)
     u32x4 r[NP];
 
     // Only the first nrows <= ROWS source rows are read; staged rows past them repeat the last one.
-    __device__ __forceinline__ void load(const wt* src, int64_t ld, int64_t plane, int k0, int nrows = ROWS) {
+    __device__ __forceinline__ void load(const wt* src, int64_t ld, int k0, int nrows) {
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
             const int q = threadIdx.x + NT * p;
             if (TOTAL % NT == 0 || q < TOTAL) {
-                const int pl = q / (ROWS * PPR), rem = q - pl * ROWS * PPR;
-                const int row = rem / PPR, pc = rem - row * PPR;
+                const int row = q / PPR, pc = q - row * PPR;
                 const int rs = row < nrows ? row : nrows - 1;
-                r[p] = *reinterpret_cast<const u32x4*>(src + pl * plane + (int64_t)rs * ld + k0 + pc * EPP);
+                r[p] = *reinterpret_cast<const u32x4*>(src + (int64_t)rs * ld + k0 + pc * EPP);
             }
         }
     }
     // Two row ranges in one stage: rows [0, ROWS/2) from the first n0 rows of src0 and rows
     // [ROWS/2, ROWS) from the first n1 rows of src1 (n0, n1 >= 1; past them the last row repeats).
     __device__ __forceinline__ void load2(const wt* src0, int n0, const wt* src1, int n1, int64_t ld, int k0) {
-        static_assert(P::NPL == 1, "one plane");
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
             const int q = threadIdx.x + NT * p;
@@ -1314,20 +1185,8 @@ struct FitStage {
         for (int p = 0; p < NP; ++p) {
             const int q = threadIdx.x + NT * p;
             if (TOTAL % NT == 0 || q < TOTAL) {
-                const int pl = q / (ROWS * PPR), rem = q - pl * ROWS * PPR;
-                const int row = rem / PPR, pc = rem - row * PPR;
-                char* rowp = dst + row * ROWB;
-                if (sizeof(wt) == 8) {
-                    // two doubles: half of group pc/2
-                    *reinterpret_cast<u32x4*>(rowp + (pc >> 1) * GB + (pc & 1) * 16) = r[p];
-                } else if (sizeof(wt) == 4) {
-                    // four floats: group pc
-                    *reinterpret_cast<u32x4*>(rowp + pc * GB) = r[p];
-                } else {
-                    // eight BF16 of one plane: the plane's half of groups 2pc and 2pc+1
-                    *reinterpret_cast<uint2*>(rowp + (2 * pc) * GB + pl * 8) = make_uint2(r[p].x, r[p].y);
-                    *reinterpret_cast<uint2*>(rowp + (2 * pc + 1) * GB + pl * 8) = make_uint2(r[p].z, r[p].w);
-                }
+                const int row = q / PPR, pc = q - row * PPR;
+                *reinterpret_cast<u32x4*>(dst + row * ROWB + pc * GB) = r[p];
             }
         }
     }
@@ -1337,40 +1196,26 @@ struct FitStage {
 template <class P, int ROWB>
 __device__ __forceinline__ typename P::frag fit_afrag(const char* base, int row, int grp)
 {
-    typename P::frag f;
-    const char* p = base + row * ROWB + grp * (4 * sizeof(typename P::wt) * P::NPL);
-    if constexpr (P::NPL == 2) {
-        f.h = *reinterpret_cast<const bf4*>(p);
-        f.l = *reinterpret_cast<const bf4*>(p + 8);
-    } else {
-        f = *reinterpret_cast<const typename P::frag*>(p);
-    }
-    return f;
+    return *reinterpret_cast<const typename P::frag*>(base + row * ROWB + grp * 16);
 }
 
 // ---------------------------------------------------------------------------------------------
-// Fitting net on the 16x16x4 MFMA of one element type: FP64 (PF64) or FP32 (PF32). FP64
-// accumulators take twice the registers, so every product runs in passes of eight 16-row output
-// tiles and the layer outputs go to a per-atom scratch row instead of registers. Values are stored
-// in the K order the MFMA lanes read (position 16c + 4g + v holds logical index kidx(c, g, v):
-// 16c + g + 4v in FP64, 16c + 4g + v in FP32): the four outputs a lane produces and the four
-// B-operand values it later reads are the same 32 (FP64) or 16 (FP32) bytes, written and read by
-// the same lane, so the scratch row needs no synchronisation.
+// Fitting net on v_mfma_f32_16x16x4f32. Every product runs in passes of eight 16-row output tiles and
+// the layer outputs go to a per-atom scratch row. Values are stored in the K order the MFMA lanes read
+// (position 16c + 4g + v holds logical index kidx(c, g, v)): the four outputs a lane produces and the
+// four B-operand values it later reads are the same 16 bytes, written and read by the same lane, so
+// the scratch row needs no synchronisation.
 // Scratch row per atom: a1, a2, a3 (tanh outputs), ga (two ping-pong buffers), gh; during the
 // forward pass the slots of the second ga buffer and of gh hold the inputs of layers 2 and 3.
-// RAD: a descriptor of M values D_m = T[m][0] (se_e2_r, se_e3): layer 1 has K = 100 (padded to
-// 112, zero weights past 100; W1^T is [240][112] and W1 [112][240] in the same slots), and the
-// input gradient is dT[m] = (dE/dD_m, 0, 0, 0).
 // ---------------------------------------------------------------------------------------------
-constexpr int F64_TP = 8;
+constexpr int FIT_TP = 8;
 constexpr int FS_A1 = 0, FS_A2 = FW, FS_A3 = 2 * FW, FS_GA = 3 * FW, FS_GB = 4 * FW, FS_GH = 5 * FW, FS_ROW = 6 * FW;
-constexpr int RAD_K = N3P;   // padded width of a descriptor of M values
 
 // HALVES = 2: eight waves per block, two per atom tile; each layer's output tiles are split
 // between the two (the first ceil(n/2) tiles and the rest), and one LDS stage holds both halves'
 // weight rows. Every layer's input is read by both halves, so the scratch row is then shared between
 // two waves of the block (ordered by the barriers at the start of every product).
-template <class P, bool ENS, bool RAD, int HALVES>
+template <class P, bool ENS, int HALVES>
 __global__ void __launch_bounds__(256 * HALVES) k_fit_dense(FitArgs A_)
 {
     const FitArgs A = ENS ? model_args(A_) : A_;
@@ -1381,7 +1226,7 @@ __global__ void __launch_bounds__(256 * HALVES) k_fit_dense(FitArgs A_)
     typedef accv d4;   // four values of the element type (the lane's 4-row output or K group)
     // output tiles per pass: eight, or four in the two-half shape (two waves per SIMD: half the
     // registers per wave)
-    constexpr int TP = HALVES == 2 ? 4 : F64_TP;
+    constexpr int TP = HALVES == 2 ? 4 : FIT_TP;
     typedef FitStage<P, 16 * TP * HALVES, 16, 256 * HALVES> SW;
     __shared__ __attribute__((aligned(32))) char s_w[2][SW::BYTES];
     __shared__ acc s_p1[4][16][16][4];
@@ -1412,7 +1257,7 @@ __global__ void __launch_bounds__(256 * HALVES) k_fit_dense(FitArgs A_)
 #pragma unroll
         for (int v = 0; v < 4; ++v)
 #pragma unroll
-            for (int k = 0; k < 4; ++k) Tn[v][k] = RAD ? (acc)0 : Ta[P::kidx(0, g, v) * 4 + k];
+            for (int k = 0; k < 4; ++k) Tn[v][k] = Ta[P::kidx(0, g, v) * 4 + k];
 
         // y = W x for ntiles 16-row output tiles of the row-major matrix at fm + mo (K columns,
         // stored in the MFMA K order); x for K-chunk c is make(fetch(c)), where fetch(c) is the one
@@ -1447,7 +1292,7 @@ __global__ void __launch_bounds__(256 * HALVES) k_fit_dense(FitArgs A_)
                 const wt* src1 = fm + mo + (int64_t)16 * (hs + t0) * K;
                 auto ld = [&](SW& st, int k0) {
                     if constexpr (HALVES == 2) st.load2(src, 16 * n0, src1, 16 * n1, K, k0);
-                    else st.load(src, K, 0, k0, 16 * n0);
+                    else st.load(src, K, k0, 16 * n0);
                 };
                 const int clast = nchunk - 1;
                 __syncthreads();
@@ -1506,30 +1351,15 @@ __global__ void __launch_bounds__(256 * HALVES) k_fit_dense(FitArgs A_)
         };
 
         // ---------------------------------------------------------- forward
-        // layer 1: a1 = tanh(W1 D + b1), D formed on the fly from T (Eq. 7); RAD: D_m = T[m][0]
-        if constexpr (RAD) {
-            gemm(FM_W1T, RAD_K, 15,
-                 [&](int c) {
-                     d4 x;
+        // layer 1: a1 = tanh(W1 D + b1), D formed on the fly from T (Eq. 7)
+        gemm(FM_W1T, DD, 15, [&](int c) { return *reinterpret_cast<const d4*>(Ta + c * 4); },
+             [&](const d4& T) {
+                 acc d[4];
 #pragma unroll
-                     for (int v = 0; v < 4; ++v) {
-                         const int m = P::kidx(c, g, v);
-                         x[v] = Ta[(m < E2 ? m : 0) * 4];
-                         if (m >= E2) x[v] = 0;
-                     }
-                     return x;
-                 },
-                 asis, [&](int t, const acc* o) { wr4(FS_A1 + 16 * t + 4 * g, o); });
-        } else {
-            gemm(FM_W1T, DD, 15, [&](int c) { return *reinterpret_cast<const d4*>(Ta + c * 4); },
-                 [&](const d4& T) {
-                     acc d[4];
-#pragma unroll
-                     for (int v = 0; v < 4; ++v) d[v] = T[0] * Tn[v][0] + T[1] * Tn[v][1] + T[2] * Tn[v][2] + T[3] * Tn[v][3];
-                     return P::make(d[0], d[1], d[2], d[3]);
-                 },
-                 [&](int t, const acc* o) { wr4(FS_A1 + 16 * t + 4 * g, o); });
-        }
+                 for (int v = 0; v < 4; ++v) d[v] = T[0] * Tn[v][0] + T[1] * Tn[v][1] + T[2] * Tn[v][2] + T[3] * Tn[v][3];
+                 return P::make(d[0], d[1], d[2], d[3]);
+             },
+             [&](int t, const acc* o) { wr4(FS_A1 + 16 * t + 4 * g, o); });
         // layer 2 input h1 = wh1 a1 and layer 3 input h2 = wh2 a2 + h1, formed as the activations
         // are, in the slots GB and GH (the backward pass's, free until then)
         activate(FS_A1, FV_B1, [&](int t, const acc* a) {
@@ -1593,18 +1423,6 @@ __global__ void __launch_bounds__(256 * HALVES) k_fit_dense(FitArgs A_)
                  wr4(FS_GA + 16 * t + 4 * g, ga);
              });
         // ---------------------------------------------------------- dD = W1^T ga1 and dT (Eq. 7)
-        if constexpr (RAD) {
-            // rows 16t + orow(g, r) of the 7 tiles are dE/dD_m (m < 100 stored)
-            gemm(FM_W1, FW, RAD_K / 16, rdrow(FS_GA), asis,
-                 [&](int t, const acc* dd) {
-#pragma unroll
-                     for (int r = 0; r < 4; ++r) {
-                         const int m = 16 * t + P::orow(g, r);
-                         if (mine && m < E2) *reinterpret_cast<d4*>(dTout + ((size_t)atom * E2 + m) * 4) = d4{dd[r], 0, 0, 0};
-                     }
-                 });
-            continue;
-        }
         // Tile m of dD holds dD[m][n], n < 16: dT[m] += sum_n dD[m][n] T[n] (reduced over the lane
         // groups, tiles m < 16 parked in LDS) and dT[n] += sum_m dD[m][n] T[m] (kept per lane).
         acc q2[4][4];
@@ -1791,38 +1609,33 @@ void launch_e3_env(int precision, const EmbArgs& a, hipStream_t s)
     else hipLaunchKernelGGL((k_e3_env<float>), grid, block, 0, s, a);
 }
 
-// The fitting net: FP64 and FP32 on the dense kernel, the BF16 paths on k_fitx; a descriptor of M
-// values (a.radial) always on the dense kernel (FP64, else FP32), whose first layer is then small.
-// Shape of the dense kernel: FP64 always in two halves (four 4-wave blocks run one wave per SIMD);
-// FP32 in two halves when the 64-atom blocks do not outnumber the CUs, else in the 4-wave shape,
-// whose blocks then share the CUs two at a time (measured: the 12,288-atom water box 0.424 -> 0.387
-// ms with halves, the 32,000-atom fcc box 0.730 -> 0.857 ms).
-template <class P, bool RAD, int HALVES>
+// The fitting net: FP64, and every precision of a descriptor of M values (a.radial: FP64, else FP32),
+// on k_fitd; FP32 on the kernel here; the BF16 paths on k_fitx.
+// Shape of the kernel here: two halves when the 64-atom blocks do not outnumber the CUs, else the
+// 4-wave shape, whose blocks then share the CUs two at a time (measured: the 12,288-atom water box
+// 0.424 -> 0.387 ms with halves, the 32,000-atom fcc box 0.730 -> 0.857 ms).
+template <int HALVES>
 static void launch_dense_shape(const FitArgs& a, hipStream_t s)
 {
     const bool ens = a.nmodels > 1;
     const dim3 grid((a.natoms + FIT_AF - 1) / FIT_AF, ens ? a.nmodels : 1), block(256 * HALVES);
-    if (ens) hipLaunchKernelGGL((k_fit_dense<P, true, RAD, HALVES>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((k_fit_dense<P, false, RAD, HALVES>), grid, block, 0, s, a);
+    if (ens) hipLaunchKernelGGL((k_fit_dense<PF32, true, HALVES>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_fit_dense<PF32, false, HALVES>), grid, block, 0, s, a);
 }
 
-template <class P, bool RAD>
 static void launch_dense(const FitArgs& a, hipStream_t s)
 {
     const int64_t blocks = (int64_t)((a.natoms + FIT_AF - 1) / FIT_AF) * (a.nmodels > 1 ? a.nmodels : 1);
-    if (sizeof(typename P::acc) == 8 || blocks <= (a.ncu > 0 ? a.ncu : 256)) launch_dense_shape<P, RAD, 2>(a, s);
-    else launch_dense_shape<P, RAD, 1>(a, s);
+    if (blocks <= (a.ncu > 0 ? a.ncu : 256)) launch_dense_shape<2>(a, s);
+    else launch_dense_shape<1>(a, s);
 }
 
 void launch_fit(int precision, const FitArgs& a, hipStream_t s)
 {
-    if (a.radial) {
-        if (precision == 0) launch_dense<PF64, true>(a, s);
-        else launch_dense<PF32, true>(a, s);
-    } else if (precision == 0) {
-        launch_dense<PF64, false>(a, s);
+    if (precision == 0 || a.radial) {
+        launch_fitd(precision == 0, a, s);
     } else if (precision == 3) {
-        launch_dense<PF32, false>(a, s);
+        launch_dense(a, s);
     } else {
         launch_fitx(precision == 1, a, s);
     }

@@ -277,7 +277,7 @@ __global__ void __launch_bounds__(TNW * 64) k_tab_fwd(EmbArgs A_)
         if (tos) tmax = tmin;   // the nets depend on the neighbour type only: one pass covers all
         for (int ti = tmin; ti <= tmax; ++ti)
             for (int tj = 0; tj < nt; ++tj) {
-                const TabPass ps = tab_pass(A, nullptr, a0, na, ti, tj, tos, lane, inv_w);
+                const TabPass ps = tab_pass(A_, nullptr, a0, na, ti, tj, tos, lane, inv_w);
                 if (!ps.any) continue;
                 const int net = tos ? tj : ti * nt + tj;
                 const T* tk = tabk + (size_t)net * kp * N3P;
@@ -291,7 +291,7 @@ __global__ void __launch_bounds__(TNW * 64) k_tab_fwd(EmbArgs A_)
 #pragma unroll
                     for (int a = 0; a < TGA; ++a) {
                         const int n = ps.cnt[a];
-                        const size_t row0 = (size_t)(a0 + a) * A.nc + A.off[tj];
+                        const size_t row0 = (size_t)(a0 + a) * A.nc + A_.off[tj];
                         while (cur[a] < n) {
                             const int q = cur[a] + lane;
                             const bool valid = q < n;
@@ -448,7 +448,7 @@ __global__ void __launch_bounds__(TNW * 64) k_tab_bwd(EmbArgs A_)
                 for (int ms = 0; ms < E2 / 4; ++ms) adt[ms] = ok ? src[16 * ms] : (T)0;
             }
             for (int tj = 0; tj < nt; ++tj) {
-                const TabPass ps = tab_pass(A, ord, a0, na, ti, tj, tos, lane, inv_w);
+                const TabPass ps = tab_pass(A_, ord, a0, na, ti, tj, tos, lane, inv_w);
                 if (!ps.any) continue;
                 const int net = tos ? tj : ti * nt + tj;
                 const T* tmat = tabm + (size_t)net * N3P * kp;
@@ -501,7 +501,7 @@ __global__ void __launch_bounds__(TNW * 64) k_tab_bwd(EmbArgs A_)
                     for (int a = 0; a < TGA; ++a) {
                         const int n = ps.cnt[a];
                         if (n == 0) continue;
-                        const size_t row0 = (size_t)group_atom(ord, a0, a) * A.nc + A.off[tj];
+                        const size_t row0 = (size_t)group_atom(ord, a0, a) * A.nc + A_.off[tj];
                         // r_ij and j of the chunk at the cursor; each chunk reads the next one's
                         // before its force atomics (reads and atomics retire in order, so a read
                         // issued after them would wait for them)
