@@ -308,7 +308,6 @@ struct dpk_ctx {
     void *T, *dT, *act;
     void* env;                           // three-body descriptor: environment rows [N][nc][4]
     DevStats* stats;
-    int64_t vir_blocks = 0;
     // frame being set up (for the candidate-buffer estimate) and the overflow retry switch
     int64_t cur_natoms = 0;
     bool force_big_cap = false;
@@ -348,7 +347,6 @@ size_t layout_ws(dpk_ctx* c, int64_t n, int64_t ncell, char* base)
 {
     const dpk_model* m = c->model;
     const int nt = m->desc.ntypes, nc = m->nc;
-    const int64_t nvb = embed_bwd_max_blocks(c->precision, n);
     const bool e3 = c->model->desc.descriptor == DPK_SE_E3;
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -383,11 +381,11 @@ size_t layout_ws(dpk_ctx* c, int64_t n, int64_t ncell, char* base)
     const bool dense_fit = dense_fitting(c);
     const int64_t nfit = fit_slots(n, dense_fit);
     p = take(dense_fit ? c->acc_size * nfit * 6 * FW : sizeof(float) * (nfit / 16) * XF_ACT);
-    if (base) c->act = p;
+    // (after the fitting net the same memory takes the backward blocks' partials)
+    if (base) { c->act = p; c->vir_part = (double*)p; }
     p = take(e3 ? c->acc_size * n * nc * 4 : 0); if (base) c->env = e3 ? p : nullptr;
     p = take(sizeof(double) * n); if (base) c->Ei = (double*)p;
     p = take(sizeof(double) * 3 * n); if (base) c->F = (double*)p;
-    p = take(sizeof(double) * 10 * nvb); if (base) { c->vir_part = (double*)p; c->vir_blocks = nvb; }
     p = take(sizeof(double) * 8); if (base) c->bbox = (double*)p;
     p = take(sizeof(double) * 3 * n); if (base) c->h_coord = (double*)p;
     p = take(sizeof(int) * n); if (base) c->h_atype = (int*)p;
@@ -737,7 +735,6 @@ void run_network(dpk_ctx* c, int n, const GeomParams& gp, double* F, double* vir
     ea.nc = m->nc;
     ea.type_one_side = m->desc.type_one_side;
     ea.ncu = c->ncu;
-    ea.apw = 1;
     for (int t = 0; t < nt; ++t) ea.off[t] = gp.off[t];
     ea.itype = c->itype;
     ea.nnei = c->nnei;
@@ -835,7 +832,7 @@ void enqueue_frame(dpk_ctx* c, int n, const double* d_coord, const int* d_atype,
     enqueue_geometry(c, n, d_coord, d_atype, gp, d_force, s, shared, ev);
     run_network(c, n, gp, d_force, nullptr, true, d_atom_energy, ev, s);
     prof_mark(ev, DPK_STAGE_FINAL, s);
-    launch_finalize(embed_bwd_blocks(c->precision, c->tab, n, c->ncu, is_e3(c)), c->vir_part, d_energy, d_virial,
+    launch_finalize(embed_bwd_blocks(c->precision, c->tab, n, c->ncu, is_e3(c), 1), c->vir_part, d_energy, d_virial,
                     c->stats, s);
     prof_mark(ev, DPK_NSTAGES, s);
 }
@@ -1282,7 +1279,7 @@ int dpk_compute_ghost(dpk_ctx* c, int64_t nlocal, int64_t nghost, const double* 
         // descriptor, fitting and adjoint over the owned atoms: E_i of owned atoms only; forces land
         // on owned and ghost atoms alike (the ghosts' are the caller's to send back to their owners)
         run_network(c, nl, gp, d_force, nullptr, true, atom_energy ? o + 10 + 3 * n : nullptr, nullptr, s, nl == n);
-        launch_finalize(embed_bwd_blocks(c->precision, c->tab, nl, c->ncu, is_e3(c)), c->vir_part, o, o + 1, c->stats, s);
+        launch_finalize(embed_bwd_blocks(c->precision, c->tab, nl, c->ncu, is_e3(c), 1), c->vir_part, o, o + 1, c->stats, s);
         HIPCHK(hipGetLastError());
         c->last_stream = s;
         c->last_n = n;
@@ -1488,7 +1485,7 @@ struct dpk_devi {
     // views (model 0; model k at k times the stride)
     void *T = nullptr, *dT = nullptr, *act = nullptr;
     double *Ei = nullptr, *F = nullptr, *vir = nullptr, *ev = nullptr, *eps = nullptr;
-    size_t st_T = 0, st_act = 0, st_vir = 0;
+    size_t st_T = 0, st_act = 0;
 };
 
 namespace {
@@ -1515,8 +1512,7 @@ int devi_buffers(dpk_devi* d, int64_t n)
     const int64_t nfit = fit_slots(n, dense_fit);
     d->st_T = align256(c->acc_size * n * E2 * 4);
     d->st_act = align256(dense_fit ? c->acc_size * nfit * 6 * FW : sizeof(float) * (nfit / 16) * XF_ACT);
-    d->st_vir = align256(sizeof(double) * 10 * embed_bwd_max_blocks(c->precision, n));
-    const size_t per = 2 * d->st_T + d->st_act + align256(sizeof(double) * n) + align256(sizeof(double) * 3 * n) + d->st_vir;
+    const size_t per = 2 * d->st_T + d->st_act + align256(sizeof(double) * n) + align256(sizeof(double) * 3 * n);
     const size_t bytes = per * d->nm + align256(sizeof(double) * 10 * d->nm) + align256(sizeof(double) * n);
     if (d->buf) {
         HIPCHK(hipStreamSynchronize(c->stream));
@@ -1535,7 +1531,7 @@ int devi_buffers(dpk_devi* d, int64_t n)
     d->act = p; p += nm * d->st_act;
     d->Ei = (double*)p; p += nm * align256(sizeof(double) * n);
     d->F = (double*)p; p += nm * align256(sizeof(double) * 3 * n);
-    d->vir = (double*)p; p += nm * d->st_vir;
+    d->vir = (double*)d->act;   // the backward blocks' partials, once the fitting scratch is free
     d->ev = (double*)p; p += align256(sizeof(double) * 10 * nm);
     d->eps = (double*)p;
     d->buf_bytes = bytes;
@@ -1570,7 +1566,6 @@ void devi_enqueue(dpk_devi* d, int n, const GeomParams& gp, double nu, hipStream
     const bool e3 = is_e3(c);
     ea.type_one_side = e3 ? 0 : c->model->desc.type_one_side;
     ea.ncu = c->ncu;
-    ea.apw = 1;
     for (int t = 0; t < nt; ++t) ea.off[t] = gp.off[t];
     ea.itype = c->itype;
     ea.nnei = c->nnei;
@@ -1599,7 +1594,7 @@ void devi_enqueue(dpk_devi* d, int n, const GeomParams& gp, double nu, hipStream
     ea.ms_T = d->st_T;
     ea.ms_F = stF;
     ea.ms_Ei = stE;
-    ea.ms_vir = d->st_vir;
+    ea.ms_vir = d->st_act;
     if (e3) launch_e3_env(c->precision, ea, s);
     launch_embed_fwd(c->precision, c->tab, ea, s, e3);
     FitArgs fa;
@@ -1624,9 +1619,9 @@ void devi_enqueue(dpk_devi* d, int n, const GeomParams& gp, double nu, hipStream
     fa.radial = c->model->desc.descriptor != DPK_SE_E2_A;
     launch_fit(c->precision, fa, s);
     launch_embed_bwd(c->precision, c->tab, ea, s, e3);
-    const int nb = embed_bwd_blocks(c->precision, c->tab, n, c->ncu, e3);
+    const int nb = embed_bwd_blocks(c->precision, c->tab, n, c->ncu, e3, nm);
     for (int k = 0; k < nm; ++k)
-        launch_finalize(nb, (const double*)((const char*)d->vir + k * d->st_vir), d->ev + 10 * k, d->ev + 10 * k + 1,
+        launch_finalize(nb, (const double*)((const char*)d->vir + k * d->st_act), d->ev + 10 * k, d->ev + 10 * k + 1,
                         c->stats, s);
     launch_force_devi(n, nm, d->F, (int64_t)(stF / sizeof(double)), nu, d->eps, s);
 }

@@ -170,7 +170,8 @@ constexpr int E3_MAXN = 128;
 struct EmbArgs {
     int natoms, ntypes, nc, type_one_side;
     int ncu;                 // compute units of the device (sizes the launch)
-    int apw;                 // atoms per wave (set by the launcher)
+    int apb;                 // atoms per block of the network kernels (set by the launcher)
+    int apw;                 // tabulated kernels: atom groups per wave (set by the launcher)
     int off[MAXT];
     const int* itype;        // [N] type of internal atom
     const int* nnei;         // [N][ntypes] kept neighbours per type block
@@ -187,7 +188,7 @@ struct EmbArgs {
     const int* perm;         // [N] caller index of each internal atom
     double* F;               // [N][3] caller order (backward output, atomics; zero on entry)
     void* env;               // three-body descriptor: [N][nc][4] environment rows R_j (acc type)
-    double* vir_part;        // [gridDim][10]: E of the block's atoms (single frame), virial
+    double* vir_part;        // [blocks][10]: E of the block's atoms (single frame), virial
     double* vir_atom;        // [N][9] virial per centre atom (batched frames), or nullptr
     DevStats* stats;
     // single frame (nullptr for a batch): E_i of the fitting net, summed per block into vir_part

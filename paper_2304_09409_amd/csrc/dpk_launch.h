@@ -54,11 +54,10 @@ void launch_nlist_ext(int nlocal, int ntot, const double* pos, const int* perm, 
 void launch_force_devi(int n, int nm, const double* F, int64_t stride, double nu, double* eps, hipStream_t s);
 
 // precision: 0 = FP64, 1 = split-BF16 (three products), 2 = BF16 (one product), 3 = FP32
-// blocks of the embedding backward for a frame on the network or the table path (one [E, virial]
-// partial each; the two paths have their own launch shapes), and their maximum over launch shapes
-// (workspace sizing)
-int embed_bwd_blocks(int precision, bool table, int64_t natoms, int ncu, bool e3 = false);
-int64_t embed_bwd_max_blocks(int precision, int64_t natoms);
+// blocks of the embedding backward for a frame (per model of an ensemble of nmodels) on the network or
+// the table path: one [E, virial] partial each. The partials lie in the fitting scratch, which is free
+// by then and holds more than 80 bytes per atom
+int embed_bwd_blocks(int precision, bool table, int64_t natoms, int ncu, bool e3, int nmodels);
 // E and the virial of a single frame from the backward pass's nb partials [E, virial[9]], and the
 // frame's dropped-neighbour count into st
 void launch_finalize(int nb, const double* part, double* energy, double* virial, DevStats* st, hipStream_t s);
@@ -73,7 +72,6 @@ void launch_tab(bool fwd, int precision, const EmbArgs& a, hipStream_t s);
 // *cnt (zero on entry) += the number of internal atoms i < n - 1 in the bin of atom i + 1
 void launch_spatial_order(int n, const double4* cand, const int* cell_of, int* order, int* cnt, hipStream_t s);
 int tab_blocks(int64_t natoms, int ncu);
-int tab_atoms_per_block_min();
 void launch_fit(int precision, const FitArgs& a, hipStream_t s);
 // fitting kernel of the FP64 path (every descriptor), or FP32 for a descriptor of M values
 void launch_fitd(bool f64, const FitArgs& a, hipStream_t s);

@@ -236,22 +236,23 @@ __device__ __forceinline__ void outer4(f4& d, float a, float b)
 // 128-bit store (odd strides split them into 32-bit pairs: the bank-conflict counter rose 60 %).
 constexpr int Z2S = 68;
 
-// Launch shape of the embedding kernels: NW waves per block share one staged net; each wave takes
-// A.apw atoms, chosen per launch (embed_apw) between 1 and APW_MAX so that a large frame gets about
-// one block per CU (fewer net stagings per atom) and a small one still spreads over the CUs. Every
-// path stages W3^T in LDS. FP64 runs 8 waves (network; two per SIMD, in at most 256 registers) or
-// 4 (table; three blocks per CU). The FP32-accumulating policies run:
+// Launch shape of the embedding kernels: the waves of a block share one staged net; a block takes A.apb
+// consecutive atoms, wave w of nw the atoms w, w + nw, ... of them. embed_shape chooses apb and nw per
+// launch. Every path stages W3^T in LDS. At most NW waves per block: FP64 8 (network; two per SIMD, in
+// at most 256 registers) or 4 (table; three blocks per CU). The FP32-accumulating policies run:
 //   * forward (network): 16 waves, four per SIMD, in at most 128 VGPRs (the contraction's
 //     accumulators live in the matrix cores' operands, see outer4): the extra waves per SIMD hide
 //     more of the exp/rcp, MFMA and LDS latency;
 //   * forward (table): 8 waves (the polynomial path needs more registers);
 //   * backward: 12 waves, three per SIMD, in at most 168 VGPRs (skips in registers, the
 //     contraction on the matrix cores, the pair sums of force and virial in LDS).
+constexpr int EMB_MIN = 4;   // smallest block in atoms
 template <class P, bool FWD = false, bool TAB = false> struct EmbCfg {
     typedef typename P::wt wt;
     static constexpr bool F64 = sizeof(typename P::acc) == 8;
     static constexpr int NW = F64 ? (TAB ? 4 : 8) : (FWD ? (TAB ? 8 : 16) : 12);
     static constexpr int APW_MAX = F64 ? 3 : (FWD ? (TAB ? 3 : 4) : 6);
+    static constexpr int E3_APW = TAB ? 1 : 2;   // three-body backward: atoms per wave (slot gradients in LDS)
     static constexpr bool W3LDS = true;
     // LDS rows of staged weights: one lane's fragment per group (VPL K values; [hi lo] for split
     // BF16), rows padded by 16 B so 16 consecutive rows fall in distinct banks.
@@ -274,21 +275,34 @@ __device__ __forceinline__ typename P::frag lds_frag(const char* base, int rowb,
     return P::lds(base + row * rowb + grp * P::GB);
 }
 
-// Stage rows x K of a per-plane row-major matrix into LDS rows of fragment groups.
+// Stage rows x K of a per-plane row-major matrix into LDS rows of fragment groups. Every thread issues
+// the loads of up to STG groups before it stores the first (a load-store loop paid one memory latency
+// per group; the last groups repeat, so that no load is under a branch).
 template <class P>
 __device__ void stage_rows(char* dst, int rowb, const typename P::wt* src, int64_t plane, int rows, int K)
 {
     typedef typename P::wt wt;
-    const int G = K / P::VPL;
-    for (int i = threadIdx.x; i < rows * G; i += blockDim.x) {
-        const int row = i / G, grp = i - row * G;
-        const wt* sp = src + (int64_t)row * K + P::VPL * grp;
-        char* d = dst + row * rowb + grp * P::GB;
-        if constexpr (sizeof(wt) == 8) {
-            *reinterpret_cast<d4*>(d) = *reinterpret_cast<const d4*>(sp);
-        } else {
-            *reinterpret_cast<u32x4*>(d) = *reinterpret_cast<const u32x4*>(sp);
-            if constexpr (P::NPL == 2) *reinterpret_cast<u32x4*>(d + 16) = *reinterpret_cast<const u32x4*>(sp + plane);
+    constexpr int STG = 4;
+    typedef std::conditional_t<sizeof(wt) == 8, d4, u32x4> piece;
+    const int G = K / P::VPL, n = rows * G;
+    const int step = blockDim.x;
+    for (int b0 = 0; b0 < n; b0 += STG * step) {
+        piece h[STG], l[STG];
+#pragma unroll
+        for (int q = 0; q < STG; ++q) {
+            if (b0 + q * step >= n) break;   // (uniform)
+            const int i = min(b0 + q * step + (int)threadIdx.x, n - 1), row = i / G, grp = i - row * G;
+            const wt* sp = src + (int64_t)row * K + P::VPL * grp;
+            h[q] = *reinterpret_cast<const piece*>(sp);
+            if constexpr (P::NPL == 2) l[q] = *reinterpret_cast<const piece*>(sp + plane);
+        }
+#pragma unroll
+        for (int q = 0; q < STG; ++q) {
+            if (b0 + q * step >= n) break;
+            const int i = min(b0 + q * step + (int)threadIdx.x, n - 1), row = i / G, grp = i - row * G;
+            char* d = dst + row * rowb + grp * P::GB;
+            *reinterpret_cast<piece*>(d) = h[q];
+            if constexpr (P::NPL == 2) *reinterpret_cast<piece*>(d + 16) = l[q];
         }
     }
 }
@@ -495,7 +509,7 @@ __global__ void __launch_bounds__((EmbCfg<P, true, TAB>::NW * 64)) k_embed_fwd(E
     typedef typename P::frag frag;
     typedef EmbCfg<P, true, TAB> Cfg;
     constexpr int NW = Cfg::NW;
-    const int APW = A.apw, APB = NW * APW;
+    const int nw = blockDim.x >> 6, APB = A.apb, APW = (APB + nw - 1) / nw;
     constexpr bool W3LDS = Cfg::W3LDS;
     __shared__ acc s_vec[EVEC];
     __shared__ __attribute__((aligned(16))) char s_w2[TAB ? 16 : N2P * Cfg::ROW2];
@@ -533,7 +547,7 @@ __global__ void __launch_bounds__((EmbCfg<P, true, TAB>::NW * 64)) k_embed_fwd(E
             w.i = 0;
             w.c0 = 0;
             w.ac = 0;
-            w.have = w.find_atom(A_, nullptr, a0, a1, wave, NW, APW, ti, tj, false);
+            w.have = w.find_atom(A_, nullptr, a0, a1, wave, nw, APW, ti, tj, false);
             w.fetch(A_, tj, c16);
             accv Tacc[7];
             while (w.have) {
@@ -551,7 +565,7 @@ __global__ void __launch_bounds__((EmbCfg<P, true, TAB>::NW * 64)) k_embed_fwd(E
                 if (w.c0 >= w.np) {
                     ++w.i;
                     w.c0 = 0;
-                    w.have = w.find_atom(A_, nullptr, a0, a1, wave, NW, APW, ti, tj, false);
+                    w.have = w.find_atom(A_, nullptr, a0, a1, wave, nw, APW, ti, tj, false);
                     last = true;
                 }
                 w.fetch(A_, tj, c16);
@@ -585,7 +599,8 @@ __global__ void __launch_bounds__((EmbCfg<P, true, TAB>::NW * 64)) k_embed_fwd(E
                 float Rq[4];
                 auto add_G = [&](int tm, int r, int q, acc G) {
                     if constexpr (Cfg::F64) {
-                        for (int k = 0; k < 4; ++k) Tacc[tm][k] += G * s_R[wave][q][k];
+                        // (three-body rows are (theta, 0, 0, 0))
+                        for (int k = 0; k < (E3 && !TAB ? 1 : 4); ++k) Tacc[tm][k] += G * s_R[wave][q][k];
                     } else {
                         outer4(Tacc[tm], Rq[r], G);
                     }
@@ -748,33 +763,38 @@ __global__ void __launch_bounds__((EmbCfg<P, false, TAB>::NW * 64)) k_embed_bwd(
     typedef typename P::frag frag;
     typedef EmbCfg<P, false, TAB> Cfg;
     constexpr int NW = Cfg::NW;
-    const int APW = A.apw, APB = NW * APW;
+    const int nw = blockDim.x >> 6, APB = A.apb, APW = (APB + nw - 1) / nw;
     constexpr bool W3LDS = Cfg::W3LDS;
-    constexpr int DTL = (E2 * 4 + 63) / 64;     // dT values per lane
+    // components of dT in use: the three-body descriptor's dT[m] is (dE/dD_m, 0, 0, 0) (the FP32 paths
+    // contract all four on the matrix cores at once)
+    constexpr int DC = E3 && Cfg::F64 ? 1 : 4;
+    constexpr int DTL = (E2 * DC + 63) / 64;    // dT values per lane
     __shared__ acc s_vec[EVEC];
     __shared__ __attribute__((aligned(16))) char s_w2[TAB ? 16 : N2P * Cfg::ROW2];
     __shared__ __attribute__((aligned(16))) char s_w3[(TAB || !W3LDS) ? 16 : N3P * Cfg::ROW3];
     // dT of the wave's current atom by layer-3 row (the feature's row position; padding rows zero)
-    __shared__ __attribute__((aligned(16))) acc s_dT[NW][N3P][4];
+    __shared__ __attribute__((aligned(16))) acc s_dT[NW][N3P][DC];
     // per neighbour column of a wave: [0, 3) the centre atom's force over its pairs, [3, 12) the
     // virial sum -g r^T over the wave's pairs (kept here rather than in every lane's registers);
     // 13 doubles per column (the 16 columns' read-modify-writes conflict less in the banks than
     // with 12: the backward's bank-conflict counter reads 8 % lower)
-    __shared__ __attribute__((aligned(16))) double s_pair[NW][16][13];
+    constexpr int PC = E3 ? 1 : 16;   // (three-body: the wave's virial only)
+    __shared__ __attribute__((aligned(16))) double s_pair[NW][PC][13];
     // the LDS atom table of the walk (its reads do not wait on the in-order vector memory counter,
     // which also holds the force atomics)
     __shared__ int s_wl[NW][2 * WL_MAX];
     __shared__ double s_th[Cfg::F64 && !TAB ? TH_N : 1];   // tanh nodes (FP64 network)
-    // three-body: dE/dR_j of every slot of the wave's atom
-    __shared__ __attribute__((aligned(16))) acc s_dRs[E3 ? NW : 1][E3 ? E3_MAXN : 1][4];
+    // three-body: dE/dR_j of every slot of the wave's atoms (atom i of wave w at EA w + i)
+    constexpr int EA = Cfg::E3_APW;
+    __shared__ __attribute__((aligned(16))) acc s_dRs[E3 ? NW * EA : 1][E3 ? E3_MAXN : 1][4];
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform (scalar registers)
     const int lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
     if constexpr (Cfg::F64 && !TAB) tanh_tab_fill(s_th);   // (ordered by the barriers around stage_net)
-    for (int e = lane; e < N3P * 4; e += 64) s_dT[wave][e >> 2][e & 3] = 0;
-    for (int e = lane; e < 16 * 12; e += 64) s_pair[wave][e / 12][e % 12] = 0.0;
+    for (int e = lane; e < N3P * DC; e += 64) s_dT[wave][e / DC][e % DC] = 0;
+    for (int e = lane; e < PC * 12; e += 64) s_pair[wave][e / 12][e % 12] = 0.0;
     if constexpr (E3)
-        for (int e = lane; e < E3_MAXN * 4; e += 64) s_dRs[wave][e >> 2][e & 3] = 0;
+        for (int e = lane; e < EA * E3_MAXN * 4; e += 64) s_dRs[EA * wave + e / (E3_MAXN * 4)][(e >> 2) % E3_MAXN][e & 3] = 0;
     const double inv_w = 1.0 / (A.rc - A.rs);
     const int a0 = blockIdx.x * APB;
     const int a1 = min(a0 + APB, A.natoms);
@@ -797,13 +817,13 @@ __global__ void __launch_bounds__((EmbCfg<P, false, TAB>::NW * 64)) k_embed_bwd(
             w.i = 0;
             w.c0 = 0;
             w.ac = 0;
-            if constexpr (!E3) w.template load_atoms<true>(s_wl[wave], A_, a0, a1, wave, NW, APW, tj, lane);
-            w.have = w.template find_atom<true>(A_, s_wl[wave], a0, a1, wave, NW, APW, ti, tj, true);
+            if constexpr (!E3) w.template load_atoms<true>(s_wl[wave], A_, a0, a1, wave, nw, APW, tj, lane);
+            w.have = w.template find_atom<true>(A_, s_wl[wave], a0, a1, wave, nw, APW, ti, tj, true);
             w.template fetch<true>(A_, tj, c16);
             acc pdT[DTL];
             for (int q = 0; q < DTL; ++q) {
                 const int e = lane + 64 * q;
-                pdT[q] = (w.have && e < E2 * 4) ? dTin[(size_t)w.a * E2 * 4 + e] : (acc)0;
+                pdT[q] = (w.have && e < E2 * DC) ? dTin[(size_t)w.a * E2 * 4 + e * (4 / DC)] : (acc)0;
             }
             // the first chunk's r and j are in place before the loop, as every later chunk's are
             // at the end of the previous one, so the loop itself never waits for them
@@ -821,13 +841,13 @@ __global__ void __launch_bounds__((EmbCfg<P, false, TAB>::NW * 64)) k_embed_bwd(
                     x = w.px; y = w.py; z = w.pz;
                     jn = w.pj;
                 }
-                const int ca = w.a, cac = w.ac, cc0 = w.c0, cnp = w.np;
+                const int ca = w.a, cac = w.ac, cc0 = w.c0, cnp = w.np, ci = w.i;
                 bool last = false;
                 w.c0 += 16;
                 if (w.c0 >= w.np) {
                     ++w.i;
                     w.c0 = 0;
-                    w.have = w.template find_atom<true>(A_, s_wl[wave], a0, a1, wave, NW, APW, ti, tj, true);
+                    w.have = w.template find_atom<true>(A_, s_wl[wave], a0, a1, wave, nw, APW, ti, tj, true);
                     last = true;
                 }
                 w.template fetch<true>(A_, tj, c16);
@@ -836,12 +856,12 @@ __global__ void __launch_bounds__((EmbCfg<P, false, TAB>::NW * 64)) k_embed_bwd(
                     // next atom's is requested
                     wave_sync();
                     for (int q = 0; q < DTL; ++q) {
-                        const int e = lane + 64 * q, f = e >> 2;
-                        if (e < E2 * 4) {
+                        const int e = lane + 64 * q, f = e / DC;
+                        if (e < E2 * DC) {
                             int gf = 0, uf = 0;
                             emb_reg3(f, gf, uf);
                             const int row = TAB ? f : 16 * (uf >> 2) + P::orow(gf, uf & 3);
-                            s_dT[wave][row][e & 3] = pdT[q];
+                            s_dT[wave][row][e % DC] = pdT[q];
                         }
                     }
                     wave_sync();
@@ -849,7 +869,7 @@ __global__ void __launch_bounds__((EmbCfg<P, false, TAB>::NW * 64)) k_embed_bwd(
                 if (last) {
                     for (int q = 0; q < DTL; ++q) {
                         const int e = lane + 64 * q;
-                        pdT[q] = (w.have && e < E2 * 4) ? dTin[(size_t)w.a * E2 * 4 + e] : (acc)0;
+                        pdT[q] = (w.have && e < E2 * DC) ? dTin[(size_t)w.a * E2 * 4 + e * (4 / DC)] : (acc)0;
                     }
                 }
 
@@ -877,7 +897,7 @@ __global__ void __launch_bounds__((EmbCfg<P, false, TAB>::NW * 64)) k_embed_bwd(
                             const acc* cf = tab + ((size_t)li * E2 + m) * 6;
                             const acc G = ((((cf[0] * t + cf[1]) * t + cf[2]) * t + cf[3]) * t + cf[4]) * t + cf[5];
                             const acc Gd = (((5 * cf[0] * t + 4 * cf[1]) * t + 3 * cf[2]) * t + 2 * cf[3]) * t + cf[4];
-                            for (int k = 0; k < 4; ++k) {
+                            for (int k = 0; k < DC; ++k) {
                                 const acc dt = s_dT[wave][m][k];
                                 dR[k] += G * dt;
                                 H[k] += Gd * dt;
@@ -967,8 +987,8 @@ __global__ void __launch_bounds__((EmbCfg<P, false, TAB>::NW * 64)) k_embed_bwd(
                             const acc Gd = wh * (1 - t3 * t3) * od[rr] + ztd[u2 >> 2][u2 & 3];
                             if constexpr (Cfg::F64) {
                                 const acc* dt = s_dT[wave][m];
-                                dR[0] += G * dt[0]; dR[1] += G * dt[1]; dR[2] += G * dt[2]; dR[3] += G * dt[3];
-                                H[0] += Gd * dt[0]; H[1] += Gd * dt[1]; H[2] += Gd * dt[2]; H[3] += Gd * dt[3];
+#pragma unroll
+                                for (int k = 0; k < DC; ++k) { dR[k] += G * dt[k]; H[k] += Gd * dt[k]; }
                             } else {
                                 // rank-1 updates on the matrix cores: every lane of a quad has the
                                 // same row m, so register k gains dT[m][k] G (and dT[m][k] Gd)
@@ -1005,8 +1025,8 @@ __global__ void __launch_bounds__((EmbCfg<P, false, TAB>::NW * 64)) k_embed_bwd(
                     if (valid) {
                         const acc rag = g == 0 ? ra[0] : g == 1 ? ra[1] : g == 2 ? ra[2] : ra[3];
                         const acc rbg = g == 0 ? rb[0] : g == 1 ? rb[1] : g == 2 ? rb[2] : rb[3];
-                        atomicAdd(&s_dRs[wave][sa][g], de * rbg);
-                        atomicAdd(&s_dRs[wave][sb][g], de * rag);
+                        atomicAdd(&s_dRs[EA * wave + ci][sa][g], de * rbg);
+                        atomicAdd(&s_dRs[EA * wave + ci][sb][g], de * rag);
                     }
                     continue;
                 }
@@ -1059,10 +1079,9 @@ __global__ void __launch_bounds__((EmbCfg<P, false, TAB>::NW * 64)) k_embed_bwd(
         }
     }
     if constexpr (E3) {
-        // slot gradients -> forces and virial (Sec. II.A.2) for the wave's atom (apw = 1)
+        // slot gradients -> forces and virial (Sec. II.A.2) for the wave's atoms
         wave_sync();
-        const int a = a0 + wave;
-        if (a < a1) {
+        for (int i = 0, a = a0 + wave; i < APW && a < a1; ++i, a += nw) {
             const int nt = A.ntypes;
             double f[3] = {0.0, 0.0, 0.0}, vir[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
             for (int sl = lane; sl < A.nc; sl += 64) {
@@ -1076,8 +1095,8 @@ __global__ void __launch_bounds__((EmbCfg<P, false, TAB>::NW * 64)) k_embed_bwd(
                 double s, ds;
                 switch_fn(r, ir, A.rs, A.rc, inv_w, s, ds);
                 const double ux = x * ir, uy = y * ir, uz = z * ir, sr = s * ir;
-                const double d0 = s_dRs[wave][sl][0], d1 = s_dRs[wave][sl][1], d2 = s_dRs[wave][sl][2],
-                             d3 = s_dRs[wave][sl][3];
+                const double d0 = s_dRs[EA * wave + i][sl][0], d1 = s_dRs[EA * wave + i][sl][1], d2 = s_dRs[EA * wave + i][sl][2],
+                             d3 = s_dRs[EA * wave + i][sl][3];
                 const double q = d1 * ux + d2 * uy + d3 * uz;
                 const double rad = d0 * ds + q * (ds - sr);
                 const double gx = rad * ux + sr * d1, gy = rad * uy + sr * d2, gz = rad * uz + sr * d3;
@@ -1111,8 +1130,8 @@ __global__ void __launch_bounds__((EmbCfg<P, false, TAB>::NW * 64)) k_embed_bwd(
     double* part = A.vir_part + 10 * (size_t)blockIdx.x;
     if (threadIdx.x < 9) {
         double v = 0.0;
-        for (int q = 0; q < NW; ++q)
-            for (int c = 0; c < 16; ++c) v += s_pair[q][c][3 + threadIdx.x];
+        for (int q = 0; q < nw; ++q)
+            for (int c = 0; c < PC; ++c) v += s_pair[q][c][3 + threadIdx.x];
         part[1 + threadIdx.x] = v;
     }
     if (A.Ei) {
@@ -1123,7 +1142,7 @@ __global__ void __launch_bounds__((EmbCfg<P, false, TAB>::NW * 64)) k_embed_bwd(
             if (lane == 0) part[0] = e;
         }
         if (A.atom_energy)
-            for (int a = a0 + (int)threadIdx.x; a < a1; a += NW * 64) A.atom_energy[A.perm[a]] = A.Ei[a];
+            for (int a = a0 + (int)threadIdx.x; a < a1; a += nw * 64) A.atom_energy[A.perm[a]] = A.Ei[a];
     }
 }
 
@@ -1486,50 +1505,56 @@ __global__ void __launch_bounds__(256 * HALVES) k_fit_dense(FitArgs A_)
 // ---------------------------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------------------------
-// Atoms per wave of one launch (see EmbCfg).
-static int embed_apw(int nw, int apw_max, int64_t natoms, int ncu)
+// Launch shape of the embedding kernels for n atoms of each of nm models on ncu CUs (one network block
+// per CU: its staged net fills most of the LDS). The atoms are spread evenly: a round of blocks holds at
+// most NW times APW_MAX atoms per CU, and with the fewest such rounds every block takes the same share
+// (the mean is over all rounds), so that no CU gets a block more than another. Whole multiples of NW
+// atoms per block left a part-filled second round: 3,072 atoms se_e3 FP64 as 384 blocks of 8 against 256
+// of 12 here. A block starts only as many waves as it has atoms, in fours (one per SIMD): a frame of
+// fewer atoms than the device has waves then gets a SIMD per atom on four times as many CUs.
+struct EmbShape {
+    int apb, nw;
+    int64_t blocks;   // per model
+};
+static EmbShape embed_shape(int nw_max, int apw_max, int64_t n, int64_t nm, int64_t ncu)
 {
-    const int64_t a = natoms / ((int64_t)nw * (ncu > 0 ? ncu : 1));
-    return (int)std::max<int64_t>(1, std::min<int64_t>(apw_max, a));
+    const int64_t cus = std::max<int64_t>(1, (ncu > 0 ? ncu : 256) / std::max<int64_t>(1, nm));
+    const int64_t cap = (int64_t)nw_max * apw_max, rounds = std::max<int64_t>(1, (n + cus * cap - 1) / (cus * cap));
+    const int64_t apb = std::max<int64_t>(EMB_MIN, (n + cus * rounds - 1) / (cus * rounds));
+    EmbShape sh;
+    sh.apb = (int)apb;
+    sh.nw = (int)std::min<int64_t>(nw_max, (apb + 3) / 4 * 4);
+    sh.blocks = (n + apb - 1) / apb;
+    return sh;
 }
 
-// Atoms per wave of the backward launch: one for the three-body descriptor (a wave keeps its
-// atom's slot gradients in LDS over all passes).
-template <class P, bool TAB>
-static int embed_bwd_apw(int64_t natoms, int ncu, bool e3)
+template <class P, bool FWD, bool TAB>
+static EmbShape embed_shape_p(int64_t n, int64_t nm, int64_t ncu, bool e3)
 {
-    typedef EmbCfg<P, false, TAB> Cfg;
-    return e3 ? 1 : embed_apw(Cfg::NW, Cfg::APW_MAX, natoms, ncu);
+    typedef EmbCfg<P, FWD, TAB> Cfg;
+    if constexpr (TAB) {
+        // several blocks share a CU: whole blocks, one to APW_MAX atoms per wave
+        const int64_t a = n / ((int64_t)Cfg::NW * (ncu > 0 ? ncu : 1));
+        const int apw = !FWD && e3 ? 1 : (int)std::max<int64_t>(1, std::min<int64_t>(Cfg::APW_MAX, a)), apb = Cfg::NW * apw;
+        return EmbShape{apb, Cfg::NW, (n + apb - 1) / apb};
+    } else {
+        return embed_shape(Cfg::NW, !FWD && e3 ? Cfg::E3_APW : Cfg::APW_MAX, n, nm, ncu);
+    }
 }
 
-template <class P, bool TAB>
-static int embed_bwd_blocks_p(int64_t natoms, int ncu, bool e3)
+template <class P>
+static int embed_bwd_blocks_p(bool table, int64_t n, int64_t nm, int ncu, bool e3)
 {
-    typedef EmbCfg<P, false, TAB> Cfg;
-    const int64_t apb = (int64_t)Cfg::NW * embed_bwd_apw<P, TAB>(natoms, ncu, e3);
-    return (int)((natoms + apb - 1) / apb);
+    return (int)(table ? embed_shape_p<P, false, true>(n, nm, ncu, e3) : embed_shape_p<P, false, false>(n, nm, ncu, e3)).blocks;
 }
 
-int embed_bwd_blocks(int precision, bool table, int64_t natoms, int ncu, bool e3)
+int embed_bwd_blocks(int precision, bool table, int64_t natoms, int ncu, bool e3, int nmodels)
 {
     if (table && !e3) return tab_blocks(natoms, ncu);
-    if (precision == 0) return table ? embed_bwd_blocks_p<PF64, true>(natoms, ncu, e3) : embed_bwd_blocks_p<PF64, false>(natoms, ncu, e3);
-    if (precision == 1) return table ? embed_bwd_blocks_p<PMIX, true>(natoms, ncu, e3) : embed_bwd_blocks_p<PMIX, false>(natoms, ncu, e3);
-    if (precision == 3) return table ? embed_bwd_blocks_p<PF32, true>(natoms, ncu, e3) : embed_bwd_blocks_p<PF32, false>(natoms, ncu, e3);
-    return table ? embed_bwd_blocks_p<PBF16, true>(natoms, ncu, e3) : embed_bwd_blocks_p<PBF16, false>(natoms, ncu, e3);
-}
-
-// at least one atom per wave: the smallest block (in atoms) over both paths bounds the count
-int64_t embed_bwd_max_blocks(int precision, int64_t natoms)
-{
-    const int nw = std::min(tab_atoms_per_block_min(),
-                            precision == 0 ? std::min(EmbCfg<PF64, false, false>::NW, EmbCfg<PF64, false, true>::NW)
-                                           : std::min(EmbCfg<PMIX, false, false>::NW, EmbCfg<PMIX, false, true>::NW));
-    static_assert(EmbCfg<PBF16, false, false>::NW == EmbCfg<PMIX, false, false>::NW &&
-                  EmbCfg<PBF16, false, true>::NW == EmbCfg<PMIX, false, true>::NW &&
-                  EmbCfg<PF32, false, false>::NW == EmbCfg<PMIX, false, false>::NW &&
-                  EmbCfg<PF32, false, true>::NW == EmbCfg<PMIX, false, true>::NW, "backward shapes");
-    return (natoms + nw - 1) / nw;
+    if (precision == 0) return embed_bwd_blocks_p<PF64>(table, natoms, nmodels, ncu, e3);
+    if (precision == 1) return embed_bwd_blocks_p<PMIX>(table, natoms, nmodels, ncu, e3);
+    if (precision == 3) return embed_bwd_blocks_p<PF32>(table, natoms, nmodels, ncu, e3);
+    return embed_bwd_blocks_p<PBF16>(table, natoms, nmodels, ncu, e3);
 }
 int fit_atoms_per_block(int) { return FIT_AF; }
 
@@ -1545,12 +1570,11 @@ template __global__ void k_embed_bwd<PF64, true, true, true>(EmbArgs);
 template <class P, bool FWD, bool TAB>
 static void launch_embed_shape(const EmbArgs& a0, bool e3, hipStream_t s)
 {
-    typedef EmbCfg<P, FWD, TAB> Cfg;
     EmbArgs a = a0;
-    a.apw = FWD ? embed_apw(Cfg::NW, Cfg::APW_MAX, a.natoms, a.ncu) : embed_bwd_apw<P, TAB>(a.natoms, a.ncu, e3);
-    const int apb = Cfg::NW * a.apw;
     const bool ens = a.nmodels > 1;
-    const dim3 grid((a.natoms + apb - 1) / apb, ens ? a.nmodels : 1), block(Cfg::NW * 64);
+    const EmbShape sh = embed_shape_p<P, FWD, TAB>(a.natoms, ens ? a.nmodels : 1, a.ncu, e3);
+    a.apb = sh.apb;
+    const dim3 grid((unsigned)sh.blocks, ens ? a.nmodels : 1), block(sh.nw * 64);
     if constexpr (FWD) {
         if (e3 && ens) hipLaunchKernelGGL((k_embed_fwd<P, TAB, true, true>), grid, block, 0, s, a);
         else if (e3) hipLaunchKernelGGL((k_embed_fwd<P, TAB, false, true>), grid, block, 0, s, a);

@@ -648,8 +648,6 @@ int tab_blocks(int64_t natoms, int ncu)
     return (int)((natoms + apb - 1) / apb);
 }
 
-int tab_atoms_per_block_min() { return TNW * TGA; }
-
 // The centres in bin order, from the candidate records (bin order, one per atom; the tag's low 30
 // bits are the internal index): groups of consecutive positions in this order are atoms in one or
 // two bins, whose neighbour lists overlap in the force hash. The caller's own order (kept within
