@@ -15,6 +15,11 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// No vector memory access moves across this point in the instruction schedule (everything else may):
+// the scheduler otherwise sinks a load that fills a register ring ahead of its use down to that use,
+// to save registers, and the wave waits for its whole latency.
+__device__ __forceinline__ void keep_loads() { __builtin_amdgcn_sched_barrier(0x78f); }
+
 // Switching function of Sec. II.A.1 (eq. switch) and its derivative, FP64, from r, ir = 1/r and
 // inv_w = 1/(rc - rs) (no division here: the caller's 1/r is the only one per neighbour).
 __device__ __forceinline__ void switch_fn(double r, double ir, double rs, double rc, double inv_w, double& s,

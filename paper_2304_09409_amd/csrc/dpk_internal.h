@@ -26,7 +26,7 @@ constexpr int EV_W1 = 0, EV_B1 = K2P, EV_WH1 = 2 * K2P, EV_B2 = 3 * K2P, EV_WH2 
 constexpr int FV_B1 = 0, FV_WH1 = FW, FV_B2 = 2 * FW, FV_WH2 = 3 * FW, FV_B3 = 4 * FW,
               FV_WH3 = 5 * FW, FV_W4 = 6 * FW, FV_B4 = 7 * FW, FV_WH4 = 7 * FW + 1;
 // Matrices of one fitting net on the 16x16x4 MFMA, [rows][cols], in this order: row-major with the K
-// order of kphys (FP32), or fragment-major (k_fitd): fragment (c, t) of 256 values at c * ntiles + t is
+// order of kphys (FP32), or fragment-major (k_fitd): fragment (c, t) of 256 values at c * ntiles + t (W1: 15 t + c) is
 // 16-row tile t, columns 16c .. 16c + 15; lane 16g + i holds row 16t + i and the four columns of its
 // lane group, in FP64 as two halves [2][64 lanes][2], in FP32 as [64 lanes][4].
 constexpr int64_t FM_W1T = 0;                          // [240][1600]
@@ -51,7 +51,8 @@ constexpr int XF_W2F = XF_W1F + XF_NCH1 * 15;  // layer 2 forward: rows = output
 constexpr int XF_W3F = XF_W2F + XF_NCH2 * 15;
 constexpr int XF_W3B = XF_W3F + XF_NCH2 * 15;  // layer 3 backward: rows = inputs, K = outputs
 constexpr int XF_W2B = XF_W3B + XF_NCH2 * 15;
-constexpr int XF_W1B = XF_W2B + XF_NCH2 * 15;  // layer 1 backward: rows = 1600 D entries, K = outputs
+constexpr int XF_W1B = XF_W2B + XF_NCH2 * 15;  // layer 1 backward: rows = 1600 D entries, K = outputs;
+                                               // fragment (c, t) at base + 8 t + c
 constexpr int XF_NFRAG = XF_W1B + XF_NCH2 * 100;
 constexpr int XF_ACT = 3 * 16 * 256;           // fitting scratch floats per 16-atom tile
 

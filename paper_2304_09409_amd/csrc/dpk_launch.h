@@ -75,8 +75,7 @@ int tab_blocks(int64_t natoms, int ncu);
 void launch_fit(int precision, const FitArgs& a, hipStream_t s);
 // fitting kernel of the FP64 path (every descriptor), or FP32 for a descriptor of M values
 void launch_fitd(bool f64, const FitArgs& a, hipStream_t s);
-// BF16 fitting kernel (split = three products); 16-atom tiles per block for a frame of natoms
+// BF16 fitting kernel (split = three products)
 void launch_fitx(bool split, const FitArgs& a, hipStream_t s);
-int fitx_tiles_per_block(int natoms, int ncu);
 
 }  // namespace dpk

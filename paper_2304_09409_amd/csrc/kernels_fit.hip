@@ -4,24 +4,29 @@
 // gradient dE_i/dT through D = T T_<^T (Sec. II.A.1). The products run on
 // v_mfma_f32_16x16x32_bf16, which issues twice the K of the 16x16x16 form in the same cycles.
 //
-// Work split: a block holds NAT tiles of 16 atoms and four waves; wave w owns the 16-row feature
-// tiles w, w+4, w+8, w+12 (< 15) of every layer for all atoms of the block, and in the backward
-// dD product the D-row tiles w, w+4, ... Weights are read by exactly one wave each, straight from
-// global memory (fragment-major, one coalesced 1 KB load per plane), one K-chunk ahead. The B
-// operands (D for layer 1, then h_l or ga_l) are shared through LDS as split BF16 fragments; a
-// layer's output tiles 2c and 2c+1 fill the two halves of K-chunk c of the next layer (the
-// weights' K order matches, see XF_* in dpk_internal.h). D is formed from T by the wave that owns
-// the atom tile, a group of K-chunks ahead, so layer 1 has one barrier per group.
+// Work split: a block holds NAT tiles of 16 atoms and eight waves; wave w owns the 16-row feature
+// tiles w and w + 8 (< 15) of every layer for all atoms of the block; the backward dD product is split
+// by role (below). Weights are read by exactly one wave each, straight from global memory
+// (fragment-major, one coalesced 1 KB load per plane), several K-chunks ahead. The B operands (D for
+// layer 1, then h_l or ga_l) are shared through LDS as split BF16 fragments; a layer's output tiles 2c
+// and 2c+1 fill the two halves of K-chunk c of the next layer (the weights' K order matches, see XF_*
+// in dpk_internal.h). D is formed from T by the waves of its atom tile, a group of K-chunks ahead, so
+// layer 1 has one barrier per group.
 // Blocks are placed so that each XCD (block b runs on XCD b % 8) works on a contiguous range of
 // atoms: with atoms sorted by species, an XCD's L2 mostly holds one species' weights.
+// Bound: the streaming of the weights (4.16 MB per block; small frames) and, in the 64-atom shape, the
+// matrix unit with the LDS reads of the B operands. Measured (mixed; before the split by role and the
+// longer lookahead in brackets): 192 atoms 76 us (91), 12,288 atoms 119 us (128), 110,592 atoms 798 us
+// (900).
 #include <hip/hip_runtime.h>
+#include <type_traits>
+#include "dpk_device.h"
 #include "dpk_internal.h"
 #include "dpk_launch.h"
 
 namespace dpk {
 namespace {
 
-typedef float f4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 
@@ -30,16 +35,7 @@ struct F8 {
 };
 
 constexpr int FX_G = 4;    // layer-1 K-chunks per D group
-#ifndef FITX_PD
-#define FITX_PD 4          // weight lookahead (K-chunks) of the 32-atom block shape
-#endif
-
-// FP32 hyperbolic tangent on the hardware exp2 and reciprocal: 1 - 2 / (2^(2x log2 e) + 1).
-__device__ __forceinline__ float fx_tanh(float x)
-{
-    const float e = __builtin_amdgcn_exp2f(x * 2.885390081777927f);
-    return 1.0f - 2.0f * __builtin_amdgcn_rcpf(e + 1.0f);
-}
+constexpr int FX_PD = 4;   // weight lookahead (K-chunks) of the 240-wide layers
 
 // acc += a b with a, b split as hi + lo: lo*hi + hi*lo + hi*hi (SPLIT), or hi*hi only.
 template <bool SPLIT>
@@ -98,31 +94,16 @@ __device__ __forceinline__ void st_half(__bf16* f, int lane, int half, const flo
     if constexpr (SPLIT) *reinterpret_cast<bf4*>(f + 512 + lane * 8 + half * 4) = lo;
 }
 
-// Sum of p[0..3] over the four 16-lane groups of the wave: v_permlane32_swap pairs groups g and
-// g+2, v_permlane16_swap pairs g and g+1. Lane group G receives the total of p[ksel(G)],
-// ksel = {0, 2, 1, 3}.
-__device__ __forceinline__ float sum_groups4(const float* p)
-{
-    const auto s01 = __builtin_amdgcn_permlane32_swap(__float_as_uint(p[0]), __float_as_uint(p[1]), false, false);
-    const auto s23 = __builtin_amdgcn_permlane32_swap(__float_as_uint(p[2]), __float_as_uint(p[3]), false, false);
-    const float q0 = __uint_as_float(s01[0]) + __uint_as_float(s01[1]);
-    const float q1 = __uint_as_float(s23[0]) + __uint_as_float(s23[1]);
-    const auto t = __builtin_amdgcn_permlane16_swap(__float_as_uint(q0), __float_as_uint(q1), false, false);
-    return __uint_as_float(t[0]) + __uint_as_float(t[1]);
-}
-__device__ __forceinline__ int ksel(int g) { return ((g & 1) << 1) | (g >> 1); }
-
-template <int NAT, bool SPLIT, int NW, bool ENS, int PD>
+template <int NAT, bool SPLIT, int NW, bool ENS>
 __global__ void __launch_bounds__(64 * NW) k_fitx(FitArgs A_)
 {
     const FitArgs A = ENS ? model_args(A_) : A_;
     constexpr int NA = 16 * NAT;                       // atoms per block
-    constexpr int FR = XF_ELEMS;
+    constexpr int FR = XF_ELEMS, PD = FX_PD;
     constexpr int TPW = (15 + NW - 1) / NW;            // feature tiles per wave (at most)
     constexpr int NWA = NW / NAT;                      // waves sharing one atom tile's D fragments
-    // the dD phase splits the waves into NW / 4 atom groups of NAT / (NW / 4) atom tiles each
-    static_assert(NW % NAT == 0 && NW % 4 == 0 && NAT % (NW / 4) == 0, "wave layout");
-    static_assert(FX_G % PD == 0 && XF_NCH2 % PD == 0, "prefetch ring slots are compile-time");
+    static_assert(NW % NAT == 0 && NW >= 4, "wave layout");
+    static_assert(XF_NCH2 % PD == 0, "prefetch ring slots are compile-time");
     // B operands [K-chunk][atom tile] (layer 1: two groups of FX_G chunks); at the end the
     // per-wave dT partials (floats) of the D rows n < 16.
     __shared__ __attribute__((aligned(16))) __bf16 s_b[XF_NCH2 * NAT * FR];
@@ -130,6 +111,7 @@ __global__ void __launch_bounds__(64 * NW) k_fitx(FitArgs A_)
     // rows padded to 17 entries so that the 16 atoms a wave touches at once fall in distinct banks
     __shared__ __attribute__((aligned(16))) float s_p1[NA][17][4];
     __shared__ __attribute__((aligned(16))) float s_tq[NA][17][4];     // T rows n < 16 of the block's atoms
+    __shared__ __attribute__((aligned(16))) float s_dd[2][4][NAT][64][4];   // D rows between the waves (dD phase)
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform (scalar registers)
     const int lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
@@ -215,6 +197,7 @@ __global__ void __launch_bounds__(64 * NW) k_fitx(FitArgs A_)
 #pragma unroll
                     for (int i = 0; i < TPW; ++i) Rg[c % PD][i] = ld_wfrag<SPLIT>(wrs, lane16, wb + (c + PD) * 15 + wtile(i));
                 }
+                keep_loads();
                 F8 B[NAT];
 #pragma unroll
                 for (int a = 0; a < NAT; ++a) B[a] = ld_frag<SPLIT>(sb(c, a), lane);
@@ -247,10 +230,18 @@ __global__ void __launch_bounds__(64 * NW) k_fitx(FitArgs A_)
 #pragma unroll
             for (int k = 0; k < 4; ++k) Tn[r][k] = v[k];
         }
-        // T rows 2c and 2c + 1 of this lane's atom, and the D fragment of K-chunk c formed from them
-        auto trows = [&](int c, f4& ta, f4& tb) {
-            ta = *reinterpret_cast<const f4*>(Tw + (2 * c) * 4);
-            tb = *reinterpret_cast<const f4*>(Tw + (2 * c + 1) * 4);
+        // T rows 2c and 2c + 1 of this lane's atom for the chunks c = ph, ph + NWA, ... of a group, and
+        // the D fragment of a chunk formed from them
+        constexpr int NF = FX_G / NWA;
+        static_assert(FX_G % NWA == 0, "every wave forms as many fragments of a group");
+        f4 ta[NF], tb[NF];
+        auto trows = [&](int grp) {
+#pragma unroll
+            for (int q = 0; q < NF; ++q) {
+                const float* r = Tw + min(grp * FX_G + ph + NWA * q, XF_NCH1 - 1) * 8;
+                ta[q] = *reinterpret_cast<const f4*>(r);
+                tb[q] = *reinterpret_cast<const f4*>(r + 4);
+            }
         };
         auto dform = [&](const f4& ta, const f4& tb, __bf16* f) {
             float d0[4], d1[4];
@@ -262,44 +253,40 @@ __global__ void __launch_bounds__(64 * NW) k_fitx(FitArgs A_)
             st_half<SPLIT>(f, lane, 0, d0);
             st_half<SPLIT>(f, lane, 1, d1);
         };
+        trows(0);
 #pragma unroll
-        for (int cc = 0; cc < FX_G; ++cc)
-            if (cc % NWA == ph) {
-                f4 ta, tb;
-                trows(cc, ta, tb);
-                dform(ta, tb, sb(cc, wa));
-            }
+        for (int q = 0; q < NF; ++q) dform(ta[q], tb[q], sb(ph + NWA * q, wa));
         __syncthreads();
         {
             zero_acc();
             const int wb = XF_W1F;
-            F8 R1[PD][TPW];
+            constexpr int P1 = 2 * FX_G;   // weight lookahead: the ring slots of two groups
+            F8 R1[P1][TPW];
 #pragma unroll
-            for (int d = 0; d < PD; ++d)
+            for (int d = 0; d < P1; ++d)
 #pragma unroll
                 for (int i = 0; i < TPW; ++i) R1[d][i] = ld_wfrag<SPLIT>(wrs, lane16, wb + d * 15 + wtile(i));
             constexpr int NGRP = (XF_NCH1 + FX_G - 1) / FX_G;
-            // One group of FX_G K-chunks. Reads retire in issue order, so the T rows of the D
-            // fragment formed after a chunk's products are read before that chunk's weight
-            // prefetch, and every read is unconditional (clamped to valid rows and fragments; a
-            // wave with fewer tiles reads one it does not use): a read skipped by a branch would
-            // make the compiler drain all reads in flight. The last, partial group is peeled so
-            // that its chunk bounds are constants.
-            auto group = [&](int grp) {
-                const int p = grp & 1;
+            // One group of FX_G K-chunks. Reads retire in issue order, so the T rows of the D fragments
+            // this wave forms for the next group are read at the group's start, before its weight
+            // prefetches, and every read is unconditional (clamped to valid rows and fragments; a wave
+            // with fewer tiles reads one it does not use): a read skipped by a branch would make the
+            // compiler drain all reads in flight. The last, partial group is peeled so that its chunk
+            // bounds are constants.
+            auto group = [&](int grp, auto par) {
+                constexpr int p = par.value;   // grp % 2
+                trows(grp + 1);
 #pragma unroll
                 for (int cc = 0; cc < FX_G; ++cc) {
                     const int c = grp * FX_G + cc;
                     if (c < XF_NCH1) {
                         F8 Ac[TPW];
 #pragma unroll
-                        for (int i = 0; i < TPW; ++i) Ac[i] = R1[cc % PD][i];
-                        const int cn = c + FX_G;
-                        f4 ta, tb;
-                        trows(min(cn, XF_NCH1 - 1), ta, tb);
-                        const int c1 = min(c + PD, XF_NCH1 - 1);
+                        for (int i = 0; i < TPW; ++i) Ac[i] = R1[p * FX_G + cc][i];
+                        const int c1 = min(c + P1, XF_NCH1 - 1);
 #pragma unroll
-                        for (int i = 0; i < TPW; ++i) R1[cc % PD][i] = ld_wfrag<SPLIT>(wrs, lane16, wb + c1 * 15 + wtile(i));
+                        for (int i = 0; i < TPW; ++i) R1[p * FX_G + cc][i] = ld_wfrag<SPLIT>(wrs, lane16, wb + c1 * 15 + wtile(i));
+                        keep_loads();
                         F8 B[NAT];
 #pragma unroll
                         for (int a = 0; a < NAT; ++a) B[a] = ld_frag<SPLIT>(sb(p * FX_G + cc, a), lane);
@@ -309,14 +296,22 @@ __global__ void __launch_bounds__(64 * NW) k_fitx(FitArgs A_)
 #pragma unroll
                                 for (int a = 0; a < NAT; ++a) mma32<SPLIT>(acc[i][a], Ac[i], B[a]);
                             }
-                        if (cn < XF_NCH1 && cc % NWA == ph) dform(ta, tb, sb((p ^ 1) * FX_G + cc, wa));
                     }
                 }
+                if (grp < NGRP - 1)
+#pragma unroll
+                    for (int q = 0; q < NF; ++q) dform(ta[q], tb[q], sb((p ^ 1) * FX_G + ph + NWA * q, wa));
                 __syncthreads();
             };
+            const std::integral_constant<int, 0> even;
+            const std::integral_constant<int, 1> odd;
 #pragma unroll 1
-            for (int grp = 0; grp < NGRP - 1; ++grp) group(grp);
-            group(NGRP - 1);
+            for (int grp = 0; grp < NGRP - 1; grp += 2) {
+                group(grp, even);
+                group(grp + 1, odd);
+            }
+            static_assert(NGRP % 2 == 1, "the last group has an even number");
+            group(NGRP - 1, even);
         }
         prefetch8(XF_W2F);
         // a1 = tanh(W1 D + b1), h1 = wh1 a1
@@ -330,7 +325,7 @@ __global__ void __launch_bounds__(64 * NW) k_fitx(FitArgs A_)
                     f4 av;
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        av[r] = fx_tanh(acc[i][a][r] + b[r]);
+                        av[r] = tanh_fast(acc[i][a][r] + b[r]);
                         h[i][a][r] = wh[r] * av[r];
                     }
                     *sptr(0, t, a) = av;
@@ -360,7 +355,7 @@ __global__ void __launch_bounds__(64 * NW) k_fitx(FitArgs A_)
                         f4 av;
 #pragma unroll
                         for (int r = 0; r < 4; ++r) {
-                            av[r] = fx_tanh(acc[i][a][r] + b[r]);
+                            av[r] = tanh_fast(acc[i][a][r] + b[r]);
                             h[i][a][r] += wh[r] * av[r];
                         }
                         *sptr(layer - 1, t, a) = av;
@@ -449,123 +444,138 @@ __global__ void __launch_bounds__(64 * NW) k_fitx(FitArgs A_)
         // D-row tile m of dD holds dD[m][n = 4g + r] for 16 atoms. dT[m][k] collects
         // sum_n dD[m][n] T[n][k] (part 1, reduced over lane groups) and, for rows n < 16,
         // sum_m dD[m][n] T[m][k] (part 2, q2, per wave; reduced over waves at the end).
-        // Waves form AG atom groups x 4 row groups: wave w takes atom tiles ag*NATD.. of its
-        // group ag = w % AG and the D-row tiles mw + 4j, mw = w / AG (each W1 fragment is read
-        // by AG waves, each ga1 fragment by 4 waves per atom group).
+        // Waves 0 to 3 (one per SIMD) form the D rows mw + 4p of pass p for all atom tiles of the block,
+        // so that each W1 fragment is read once, and hand them through LDS (two buffers, one barrier
+        // per pass) to waves 4 to 7, which form dT and write it. The products, which bound the phase,
+        // then wait neither for the epilogue's dependent sums nor, on the in-order memory counter, for
+        // its stores. The weights are the latency: 4.16 MB per species do not stay in an XCD's L2, and a
+        // fragment takes about 2,500 cycles to arrive, so two passes of fragments are in flight. Cycles of
+        // a 64-atom (32-atom) block: rows and atom tiles split over all eight waves, each doing both,
+        // 124,000 (86,000); as here with 4 fragments per wave in flight 161,000 (125,000), 8: 101,000
+        // (82,000), 16: 93,000 (72,000).
+        float* qs = reinterpret_cast<float*>(s_b);
         {
-            constexpr int AG = NW / 4, NATD = NAT / AG, MGD = NW == 4 ? 4 : 2;
-            const int ag = wave % AG, mw = wave / AG;
-            const float* Td[NATD];
-            int atd[NATD];
-            bool mined[NATD];
+            constexpr int NPASS = E2 / 4, PDD = 16;       // PDD: K-chunks of weights in flight (two passes)
+            static_assert(NW == 8 && PDD == 2 * XF_NCH2, "four product and four epilogue waves; ring slots by pass parity");
+            const int mw = wave & 3;
+            auto dslot = [&](int p, int a) { return reinterpret_cast<f4*>(&s_dd[p & 1][mw][a][lane][0]); };
+            if (wave < 4) {
+                // the fragments of the next two passes (clamped at the end: unconditional reads)
+                auto wfrag = [&](int p, int c) {
+                    return ld_wfrag<SPLIT>(wrs, lane16, XF_W1B + (mw + 4 * min(p, NPASS - 1)) * XF_NCH2 + c);
+                };
+                F8 RD[PDD];
 #pragma unroll
-            for (int a2 = 0; a2 < NATD; ++a2) {
-                const int at = a0 + 16 * (ag * NATD + a2) + c16;
-                atd[a2] = at;
-                Td[a2] = Tg + (size_t)(at < A.natoms ? at : a0) * (E2 * 4);
-                mined[a2] = at < A.natoms && A.itype[at] == ti;
-            }
-            float q2[NATD][4][4];
+                for (int d = 0; d < PDD; ++d) RD[d] = wfrag(d / XF_NCH2, d % XF_NCH2);
+                auto pass = [&](int p, auto par) {
+                    f4 dd[NAT];
 #pragma unroll
-            for (int a2 = 0; a2 < NATD; ++a2)
+                    for (int a = 0; a < NAT; ++a) dd[a] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int r = 0; r < 4; ++r)
+                    for (int c = 0; c < XF_NCH2; ++c) {
+                        const int sl = par.value * XF_NCH2 + c;
+                        const F8 Ac = RD[sl];
+                        RD[sl] = wfrag(p + 2, c);
+                        keep_loads();
+                        F8 B[NAT];
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) q2[a2][r][k] = 0.f;
-            const int wb = XF_W1B;
-            constexpr int NMT = E2 / 4;                   // D-row tiles per row group: mw + 4 j
-            constexpr int NPASS = (NMT + MGD - 1) / MGD;
-            // one flat loop over (pass, K-chunk): the weight fragments of the next step, also
-            // across a pass boundary, are requested one step ahead
-            auto wfrag = [&](int pass, int c, int j) {
-                return ld_wfrag<SPLIT>(wrs, lane16, wb + c * E2 + mw + 4 * (pass * MGD + j));
-            };
-            // a ring of PD steps of weight fragments (a row tile past the last pass reads tile
-            // 0 of the pass again: unconditional reads)
-            constexpr int NSTEP = NPASS * XF_NCH2;
-            static_assert(NSTEP % PD == 0, "whole ring turns");
-            auto wstep = [&](int st, int j) {
-                const int pn = st / XF_NCH2, cn = st - pn * XF_NCH2;
-                return wfrag(pn, cn, j < min(MGD, NMT - pn * MGD) ? j : 0);
-            };
-            F8 RD[PD][MGD];
+                        for (int a = 0; a < NAT; ++a) B[a] = ld_frag<SPLIT>(sb(c, a), lane);
 #pragma unroll
-            for (int d = 0; d < PD; ++d)
+                        for (int a = 0; a < NAT; ++a) mma32<SPLIT>(dd[a], Ac, B[a]);
+                    }
 #pragma unroll
-                for (int j = 0; j < MGD; ++j) RD[d][j] = wstep(d, j);
-            f4 dd[MGD][NATD];
-            f4 tmv[MGD][NATD];
+                    for (int a = 0; a < NAT; ++a) *dslot(p, a) = dd[a];
+                    __syncthreads();
+                };
+                const std::integral_constant<int, 0> even;
+                const std::integral_constant<int, 1> odd;
 #pragma unroll 1
-            for (int s0 = 0; s0 < NSTEP; s0 += PD)
-#pragma unroll
-            for (int dstep = 0; dstep < PD; ++dstep) {
-                const int step = s0 + dstep;
-                const int pass = step / XF_NCH2, c = step - pass * XF_NCH2;
-                const int nm = min(MGD, NMT - pass * MGD);
-                if (c == 0) {
-#pragma unroll
-                    for (int j = 0; j < MGD; ++j)
-#pragma unroll
-                        for (int a2 = 0; a2 < NATD; ++a2) {
-                            dd[j][a2] = f4{0.f, 0.f, 0.f, 0.f};
-                            // rows T[m] of this pass, used by the epilogue
-                            const int m = mw + 4 * (pass * MGD + (j < nm ? j : 0));
-                            tmv[j][a2] = *reinterpret_cast<const f4*>(Td[a2] + m * 4);
-                        }
+                for (int p = 0; p < NPASS - 1; p += 2) {
+                    pass(p, even);
+                    pass(p + 1, odd);
                 }
-                F8 Ac[MGD];
+                static_assert(NPASS % 2 == 1, "the last pass has an even number");
+                pass(NPASS - 1, even);
+                __syncthreads();   // (the epilogue waves' q2, below)
+            } else {
+                f4 tn[NAT][4];     // T rows 4g..4g+3 of this lane's atoms
+                float q2[NAT][4][4];
+                const float* Td[NAT];
+                // where this lane's component of dT goes: rows of its atom, or (no such atom) one word of
+                // the block's scratch, so that the stores stand under no branch: the compiler then knows
+                // how many are in flight, and the T rows, read two passes ahead, wait for none of them
+                float* dst[NAT];
+                int dstep[NAT];
 #pragma unroll
-                for (int j = 0; j < MGD; ++j) Ac[j] = RD[dstep][j];
-                if (step + PD < NSTEP) {
+                for (int a = 0; a < NAT; ++a) {
+                    const int at = a0 + 16 * a + c16;
+                    const bool mined = at < A.natoms && A.itype[at] == ti;
+                    Td[a] = Tg + (size_t)(at < A.natoms ? at : a0) * (E2 * 4);
+                    dst[a] = mined ? dTg + (size_t)at * (E2 * 4) + ksel(g) : scr + threadIdx.x;
+                    dstep[a] = mined ? 4 : 0;
 #pragma unroll
-                    for (int j = 0; j < MGD; ++j) RD[dstep][j] = wstep(step + PD, j);
-                }
-                F8 B[NATD];
+                    for (int r = 0; r < 4; ++r) {
+                        tn[a][r] = *reinterpret_cast<const f4*>(&s_tq[16 * a + c16][4 * g + r][0]);
 #pragma unroll
-                for (int a2 = 0; a2 < NATD; ++a2) B[a2] = ld_frag<SPLIT>(sb(c, ag * NATD + a2), lane);
-#pragma unroll
-                for (int j = 0; j < MGD; ++j)
-                    if (j < nm) {
-#pragma unroll
-                        for (int a2 = 0; a2 < NATD; ++a2) mma32<SPLIT>(dd[j][a2], Ac[j], B[a2]);
+                        for (int k = 0; k < 4; ++k) q2[a][r][k] = 0.f;
                     }
-                if (c == XF_NCH2 - 1) {
+                }
+                f4 tm[2][NAT];     // rows T[m] of passes p and p + 1
+                auto trow = [&](int p, f4* t) {
 #pragma unroll
-                    for (int a2 = 0; a2 < NATD; ++a2) {
-                        const int al = 16 * (ag * NATD + a2) + c16;   // atom within the block
-                        f4 tn[4];                                     // T rows 4g..4g+3 of the atom
+                    for (int a = 0; a < NAT; ++a)
+                        t[a] = *reinterpret_cast<const f4*>(Td[a] + (mw + 4 * min(p, NPASS - 1)) * 4);
+                };
+                trow(0, tm[0]);
+                trow(1, tm[1]);
+                auto pass = [&](int p, auto slot, auto low) {   // low: rows m < 16, kept in LDS
+                    const int m = mw + 4 * p;
+                    __syncthreads();
+                    f4 t[NAT];
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) tn[r] = *reinterpret_cast<const f4*>(&s_tq[al][4 * g + r][0]);
+                    for (int a = 0; a < NAT; ++a) t[a] = tm[slot.value][a];
+                    trow(p + 2, tm[slot.value]);
 #pragma unroll
-                        for (int j = 0; j < MGD; ++j)
-                            if (j < nm) {
-                                const int m = mw + 4 * (pass * MGD + j);
-                                const f4 tm = tmv[j][a2];
-                                float part[4] = {0.f, 0.f, 0.f, 0.f};
+                    for (int a = 0; a < NAT; ++a) {
+                        const f4 dd = *dslot(p, a);
+                        float part[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                                for (int r = 0; r < 4; ++r)
+                        for (int r = 0; r < 4; ++r)
 #pragma unroll
-                                    for (int k = 0; k < 4; ++k) {
-                                        part[k] += dd[j][a2][r] * tn[r][k];
-                                        q2[a2][r][k] += dd[j][a2][r] * tm[k];
-                                    }
-                                const float pk = sum_groups4(part);   // lane group g: component ksel(g)
-                                if (m < 16) s_p1[al][m][ksel(g)] = pk;
-                                else if (mined[a2]) dTg[((size_t)atd[a2] * E2 + m) * 4 + ksel(g)] = pk;
+                            for (int k = 0; k < 4; ++k) {
+                                part[k] += dd[r] * tn[a][r][k];
+                                q2[a][r][k] += dd[r] * t[a][k];
                             }
+                        const float pk = sum_groups4(part);   // lane group g: component ksel(g)
+                        if constexpr (low.value) s_p1[16 * a + c16][m][ksel(g)] = pk;
+                        else dst[a][m * dstep[a]] = pk;
                     }
+                };
+                const std::integral_constant<int, 0> s0;
+                const std::integral_constant<int, 1> s1;
+                const std::true_type low;
+                const std::false_type high;
+                pass(0, s0, low);
+                pass(1, s1, low);
+                pass(2, s0, low);
+                pass(3, s1, low);
+#pragma unroll 1
+                for (int p = 4; p < NPASS - 1; p += 2) {
+                    pass(p, s0, high);
+                    pass(p + 1, s1, high);
                 }
+                static_assert(NPASS % 2 == 1, "the last pass has an even number");
+                pass(NPASS - 1, s0, high);
+                // part 2 partials: slot (row group, atom tile) [lane][16], each written by one wave (the
+                // product waves are done with ga1 in s_b since the last pass's barrier)
+#pragma unroll
+                for (int a = 0; a < NAT; ++a)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        *reinterpret_cast<f4*>(qs + ((mw * NAT + a) * 64 + lane) * 16 + 4 * r) =
+                            f4{q2[a][r][0], q2[a][r][1], q2[a][r][2], q2[a][r][3]};
+                __syncthreads();
             }
-            __syncthreads();   // every wave is done with ga1 in s_b
-            // part 2 partials: slot (row group, atom tile) [lane][16], each written by one wave
-            float* qs = reinterpret_cast<float*>(s_b);
-#pragma unroll
-            for (int a2 = 0; a2 < NATD; ++a2)
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    *reinterpret_cast<f4*>(qs + ((mw * NAT + ag * NATD + a2) * 64 + lane) * 16 + 4 * r) =
-                        f4{q2[a2][r][0], q2[a2][r][1], q2[a2][r][2], q2[a2][r][3]};
-            __syncthreads();
             // rows n < 16 of dT: part 1 + the four row groups' part 2
             for (int idx = threadIdx.x; idx < NA * 16; idx += 64 * NW) {
                 const int al = idx >> 4, n = idx & 15;
@@ -584,18 +594,9 @@ __global__ void __launch_bounds__(64 * NW) k_fitx(FitArgs A_)
 
 }  // namespace
 
-int fitx_tiles_per_block(int, int)
-{
-    // Four 16-atom tiles per block: the weights a block streams are amortised over 64 atoms. (On
-    // the 12,288-atom box, 192 blocks of 64 atoms ran the kernel in 0.17 ms, 256 blocks of 48 atoms
-    // in 0.27 ms.)
-    return 4;
-}
-
-// Block shape: 64 atoms with a one-chunk weight lookahead when the frame fills the CUs; otherwise
-// 32 atoms per block (twice the blocks, so twice the CUs stream a frame's weights) and a ring of
-// FITX_PD chunks per wave, which the smaller accumulator set leaves registers for.
-template <int NAT, int PD>
+// Block shape: 64 atoms when the frame fills the CUs, so that the weights a block streams serve more
+// atoms; 32 atoms while the 64-atom blocks would leave half of the CUs idle (8,100 atoms: 86 us).
+template <int NAT>
 static void launch_fitx_shape(bool split, const FitArgs& a, hipStream_t s)
 {
     constexpr int NW = 8;
@@ -603,11 +604,11 @@ static void launch_fitx_shape(bool split, const FitArgs& a, hipStream_t s)
     dim3 grid((a.natoms + 16 * NAT - 1) / (16 * NAT) + a.ntypes, ens ? a.nmodels : 1), block(64 * NW);
     // ens: one launch for a model ensemble, blockIdx.y = model (a separate instantiation)
     if (split) {
-        if (ens) hipLaunchKernelGGL((k_fitx<NAT, true, NW, true, PD>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((k_fitx<NAT, true, NW, false, PD>), grid, block, 0, s, a);
+        if (ens) hipLaunchKernelGGL((k_fitx<NAT, true, NW, true>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((k_fitx<NAT, true, NW, false>), grid, block, 0, s, a);
     } else {
-        if (ens) hipLaunchKernelGGL((k_fitx<NAT, false, NW, true, PD>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((k_fitx<NAT, false, NW, false, PD>), grid, block, 0, s, a);
+        if (ens) hipLaunchKernelGGL((k_fitx<NAT, false, NW, true>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((k_fitx<NAT, false, NW, false>), grid, block, 0, s, a);
     }
 }
 
@@ -615,8 +616,8 @@ void launch_fitx(bool split, const FitArgs& a, hipStream_t s)
 {
     if (a.natoms <= 0) return;
     const int64_t blocks64 = ((int64_t)a.natoms + 63) / 64 * (a.nmodels > 1 ? a.nmodels : 1);
-    if (blocks64 * 2 <= (a.ncu > 0 ? a.ncu : 256)) launch_fitx_shape<2, FITX_PD>(split, a, s);
-    else launch_fitx_shape<4, 1>(split, a, s);
+    if (blocks64 * 2 <= (a.ncu > 0 ? a.ncu : 256)) launch_fitx_shape<2>(split, a, s);
+    else launch_fitx_shape<4>(split, a, s);
 }
 
 }  // namespace dpk

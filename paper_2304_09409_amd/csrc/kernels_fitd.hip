@@ -144,13 +144,13 @@ __global__ void __launch_bounds__(64 * FD_NW, DEEP ? 2 : 4) k_fitd(FitArgs A_)
 
     accv acc_[TPW];
     accv ring[P1 > PD ? P1 : PD][TPW];
-    auto wld = [&](int64_t mo, int ntiles, int c, int t) { return P::ld(W + mo + ((int64_t)c * ntiles + t) * FR, lane); };
+    auto wld = [&](int64_t mo, int c, int t) { return P::ld(W + mo + ((int64_t)c * 15 + t) * FR, lane); };
     // the first np chunks of a 15-tile product, requested before the preceding epilogue and barrier
     auto prefetch = [&](int64_t mo, auto np) {
 #pragma unroll
         for (int d = 0; d < np.value; ++d)
 #pragma unroll
-            for (int i = 0; i < TPW; ++i) ring[d][i] = wld(mo, 15, d, wtile(i));
+            for (int i = 0; i < TPW; ++i) ring[d][i] = wld(mo, d, wtile(i));
     };
     auto zero_acc = [&]() {
 #pragma unroll
@@ -163,7 +163,8 @@ __global__ void __launch_bounds__(64 * FD_NW, DEEP ? 2 : 4) k_fitd(FitArgs A_)
 #pragma unroll
         for (int i = 0; i < TPW; ++i) Ac[i] = ring[sl][i];
 #pragma unroll
-        for (int i = 0; i < TPW; ++i) ring[sl][i] = wld(mo, 15, cn, wtile(i));
+        for (int i = 0; i < TPW; ++i) ring[sl][i] = wld(mo, cn, wtile(i));
+        keep_loads();
         const accv B = P::ld(b, lane);
 #pragma unroll
         for (int i = 0; i < TPW; ++i)
@@ -329,9 +330,10 @@ __global__ void __launch_bounds__(64 * FD_NW, DEEP ? 2 : 4) k_fitd(FitArgs A_)
     // D rows m = wave + 8 j (RAD: 16-row tiles of dE/dD_m); the weight fragments of the next PD steps,
     // also across a row boundary, are in flight
     constexpr int NM = RAD ? RAD_K / 16 : E2;
+    auto wrow = [&](int m, int c) { return P::ld(W + FM_W1 + ((int64_t)m * 15 + c) * FR, lane); };   // (by tile)
     accv rd[PD];
 #pragma unroll
-    for (int d = 0; d < PD; ++d) rd[d] = wld(FM_W1, NM, d, min(wave, NM - 1));
+    for (int d = 0; d < PD; ++d) rd[d] = wrow(min(wave, NM - 1), d);
     accv q2[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) q2[r] = accv{0, 0, 0, 0};
@@ -345,7 +347,8 @@ __global__ void __launch_bounds__(64 * FD_NW, DEEP ? 2 : 4) k_fitd(FitArgs A_)
             for (int d = 0; d < PD; ++d) {
                 const int c = c0 + d;
                 const accv Ac = rd[d];
-                rd[d] = c + PD < 15 ? wld(FM_W1, NM, c + PD, m) : wld(FM_W1, NM, c + PD - 15, min(m + NW, NM - 1));
+                rd[d] = c + PD < 15 ? wrow(m, c + PD) : wrow(min(m + NW, NM - 1), c + PD - 15);
+                keep_loads();
                 P::mma(dd, Ac, P::ld(sb(c), lane));
             }
         if constexpr (RAD) {
