@@ -31,6 +31,7 @@ SOURCES = {
     "api.cpp": ["-ffp-contract=off"],
     "model_file.cpp": [],
     "kernels_train.hip": [],
+    "kernels_tre.hip": [],
     "trainer.cpp": [],
 }
 

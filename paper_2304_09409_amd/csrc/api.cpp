@@ -309,6 +309,8 @@ struct dpk_ctx {
     GeomParams* gps;                     // batched frames: [BATCH_MAX_FRAMES]
     void* pin_desc = nullptr;            // pinned staging of fd and gps
     hipEvent_t desc_copied = nullptr;    // recorded after the last copy out of pin_desc
+    DevStats* pin_stats = nullptr;       // training frames: the statistics block after the geometry,
+    hipEvent_t stats_copied = nullptr;   // recorded after its copy
     bool desc_pending = false;
     void *T, *dT, *act;
     void* env;                           // three-body descriptor: environment rows [N][nc][4]
@@ -721,15 +723,8 @@ int upload_model(dpk_ctx* c)
     return DPK_OK;
 }
 
-// Embedding, fitting and adjoint over n atoms (internal order), after the neighbour list.
-// vir_atom == nullptr: virial as per-block partials; else per centre atom (batched frames).
-// Embedding, fitting and the backward pass. F: force accumulator in caller order (zeroed by the
-// preparation). Single frame (single = true): per-block partials [E, virial] and E_i in caller
-// order (atom_energy, if not nullptr); batch: per-atom virials (vir_atom).
-// spatial: the candidate records hold exactly the n centres (no ghosts), so the tabulated
-// backward may take its atoms in their bin order
-void run_network(dpk_ctx* c, int n, const GeomParams& gp, double* F, double* vir_atom, bool single,
-                 double* atom_energy, std::vector<hipEvent_t>* ev, hipStream_t s, bool spatial = true)
+// The embedding kernels' arguments that depend on the context and its frame of n atoms alone.
+EmbArgs emb_args(const dpk_ctx* c, int n, const GeomParams& gp)
 {
     const dpk_model* m = c->model;
     const int nt = m->desc.ntypes;
@@ -760,10 +755,27 @@ void run_network(dpk_ctx* c, int n, const GeomParams& gp, double* F, double* vir
     ea.T = c->T;
     ea.dT = c->dT;
     ea.perm = c->perm;
+    ea.stats = c->stats;
+    return ea;
+}
+
+// Embedding, fitting and adjoint over n atoms (internal order), after the neighbour list.
+// vir_atom == nullptr: virial as per-block partials; else per centre atom (batched frames).
+// Embedding, fitting and the backward pass. F: force accumulator in caller order (zeroed by the
+// preparation). Single frame (single = true): per-block partials [E, virial] and E_i in caller
+// order (atom_energy, if not nullptr); batch: per-atom virials (vir_atom).
+// spatial: the candidate records hold exactly the n centres (no ghosts), so the tabulated
+// backward may take its atoms in their bin order
+void run_network(dpk_ctx* c, int n, const GeomParams& gp, double* F, double* vir_atom, bool single,
+                 double* atom_energy, std::vector<hipEvent_t>* ev, hipStream_t s, bool spatial = true)
+{
+    const dpk_model* m = c->model;
+    const int nt = m->desc.ntypes;
+    const bool e3 = is_e3(c);
+    EmbArgs ea = emb_args(c, n, gp);
     ea.F = F;
     ea.vir_part = c->vir_part;
     ea.vir_atom = vir_atom;
-    ea.stats = c->stats;
     if (single) {
         ea.Ei = c->Ei;
         ea.atom_energy = atom_energy;
@@ -1107,6 +1119,8 @@ void dpk_ctx_free(dpk_ctx* c)
     hipFree(c->ext_buf);
     hipHostFree(c->pin_desc);
     if (c->desc_copied) hipEventDestroy(c->desc_copied);
+    hipHostFree(c->pin_stats);
+    if (c->stats_copied) hipEventDestroy(c->stats_copied);
     for (auto& set : c->prof_events)
         for (auto e : set) hipEventDestroy(e);
     if (c->stream) hipStreamDestroy(c->stream);
@@ -2505,16 +2519,25 @@ void dpk_server_free(dpk_server* s)
 
 }  // extern "C"
 
-// Geometry of one host frame for the training path (Sec. II.B needs the same neighbour list as
-// inference): partition, bin and search, with the same candidate-buffer retry as dpk_compute.
-int dpk::frame_geometry(dpk_ctx* c, int64_t natoms, const double* coord, const int32_t* atype, const double* box,
-                        FrameGeom* g)
+// One host frame of the training path (Sec. II.B starts from the inference pass): geometry with the same
+// candidate-buffer retry as dpk_compute, and the network queued behind it; the geometry's error flags
+// are waited for here, while the network runs.
+int dpk::frame_network(dpk_ctx* c, int64_t natoms, const double* coord, const int32_t* atype, const double* box,
+                       double* ev, FrameNet* f)
 {
-    if (!c || !coord || !atype || !g) return fail(DPK_E_INVALID_ARG, "NULL argument");
+    if (!c || !coord || !atype || !f) return fail(DPK_E_INVALID_ARG, "NULL argument");
     if (natoms < 1 || natoms > (1LL << 30)) return fail(DPK_E_INVALID_ARG, "natoms = %lld", (long long)natoms);
     HIPCHK(hipSetDevice(c->device));
     const int n = (int)natoms;
     hipStream_t s = c->stream;
+    if (!c->pin_stats) {
+        if (hipHostMalloc((void**)&c->pin_stats, sizeof(DevStats)) != hipSuccess) {
+            hipGetLastError();
+            c->pin_stats = nullptr;
+            return fail(DPK_E_OOM, "pinned staging of the frame statistics failed");
+        }
+    }
+    if (!c->stats_copied) HIPCHK(hipEventCreateWithFlags(&c->stats_copied, hipEventDisableTiming));
     int rc = DPK_OK;
     for (int attempt = 0; attempt < 2; ++attempt) {
         GeomParams gp;
@@ -2535,29 +2558,45 @@ int dpk::frame_geometry(dpk_ctx* c, int64_t natoms, const double* coord, const i
         HIPCHK(hipMemcpyAsync(c->h_coord, coord, sizeof(double) * 3 * natoms, hipMemcpyHostToDevice, s));
         HIPCHK(hipMemcpyAsync(c->h_atype, atype, sizeof(int) * natoms, hipMemcpyHostToDevice, s));
         enqueue_geometry(c, n, c->h_coord, c->h_atype, gp, c->F, s, false, nullptr);
+        HIPCHK(hipMemcpyAsync(c->pin_stats, c->stats, sizeof(DevStats), hipMemcpyDeviceToHost, s));
+        HIPCHK(hipEventRecord(c->stats_copied, s));
+        run_network(c, n, gp, c->F, nullptr, true, nullptr, nullptr, s);
+        launch_finalize(embed_bwd_blocks(c->precision, c->tab, n, c->ncu, is_e3(c), 1), c->vir_part, ev, ev + 1, c->stats, s);
         HIPCHK(hipGetLastError());
         c->last_stream = s;
         c->last_n = n;
         c->last_centres = n;
-        rc = dpk_ctx_check(c);
+        HIPCHK(hipEventSynchronize(c->stats_copied));
+        rc = check_stats(c, *c->pin_stats);
         if (rc == DPK_E_NBR_OVERFLOW && !c->force_big_cap && !c->strict) {
             c->force_big_cap = true;   // a locally dense frame: once more with the largest buffer
             continue;
         }
         if (rc == DPK_OK) {
-            g->n = n;
-            g->nc = c->model->nc;
-            g->nt = c->model->desc.ntypes;
-            for (int t = 0; t < MAXT; ++t) g->off[t] = gp.off[t];
-            g->itype = c->itype;
-            g->nnei = c->nnei;
-            g->nl_j = c->nl_j;
-            g->nl_r = c->nl_r;
-            g->perm = c->perm;
-            g->stream = s;
+            f->n = n;
+            f->nt = c->model->desc.ntypes;
+            f->ncu = c->ncu;
+            f->emb = emb_args(c, n, gp);
+            f->toff = c->toff;
+            f->nnei = c->nnei;
+            f->perm = c->perm;
+            f->T = (const double*)c->T;
+            f->F = c->F;
+            f->stream = s;
         }
         break;
     }
     c->force_big_cap = false;
     return rc;
+}
+
+void dpk::packed_weights(dpk_ctx* c, PackedWeights* w)
+{
+    void* p[4] = {c->evec, c->emat, c->fvec, c->fmat};
+    const size_t b[4] = {c->evec_b, c->emat_b, c->fvec_b, c->fmat_b};
+    for (int k = 0; k < 4; ++k) {
+        w->p[k] = (double*)p[k];
+        w->n[k] = (int64_t)(b[k] / sizeof(double));
+    }
+    w->stream = c->stream;
 }

@@ -1,207 +1,361 @@
-// kernels_train.hip -- training-mode backward of the se_e2_a model (Sec. II.B), FP64.
+// kernels_train.hip -- training-mode backward (Sec. II.B), FP64: the fitting nets with their tangent and
+// their reverse pass, the loss, the packing of the parameters, Adam. The decomposition is in
+// dpk_train.h, the embedding nets in kernels_tre.hip.
 //
-// The gradient of the loss of eq. loss with respect to every parameter, force and virial terms
-// included. With g_ij = dE/dr_ij, the force and virial terms are linear in the g_ij, so
-//   dL/dtheta = d/dtheta [ cE E + sum_ij g_ij . rdot_ij ],
-//   cE = 2 p_E (E - E*) / N,  rdot_ij = vdir_j - vdir_i + CV r_ij,
-//   vdir_k = -2 p_F q_k (F_k - F*_k) / (3N),  CV = -2 p_Xi (Xi - Xi*) / (9N),
-// and sum_ij g_ij . rdot_ij is the derivative of E along the pair displacements rdot_ij: a
-// forward-mode tangent through the model (s, R, G = N(s), T, D, F_0), then reverse mode through
-// the model and its tangent. Every layer y = w_hat tanh(x W + b) + skip(x) carries (y, ydot); its
+// Every layer y = w_hat tanh(x W + b) + skip(x) of the fitting net carries its tangent (y, ydot); the
 // adjoint pair (ybar, ydotbar) gives
 //   zbar = w_hat (1 - a^2) ybar - 2 w_hat a (1 - a^2) zdot ydotbar,  zdotbar = w_hat (1 - a^2) ydotbar,
 //   Wbar += x zbar^T + xdot zdotbar^T,  bbar += zbar,  w_hatbar += a ybar + (1 - a^2) zdot ydotbar,
 //   xbar = W zbar + skip^T ybar,  xdotbar = W zdotbar + skip^T ydotbar.
-// The embedding net has a scalar input s, so its tangent along any direction is sdot times its
-// unit tangent d/ds: the forward pass (which the forces need anyway) stores the unit tangents and
-// the reverse pass scales them per pair.
-//
-// Layout: the activations of every layer are materialised per row (rows = neighbour pairs grouped
-// by embedding net, or atoms grouped by type), and every layer is a row GEMM (tr_gemm) with a fused
-// epilogue; the weight gradients are GEMMs over the rows (tr_wgrad, split over rows with FP64
-// atomics). 64 x 64 output tiles, 16-deep K chunks staged in LDS, four waves of 2 x 2 tiles of the
-// 16 x 16 x 4 FP64 matrix instruction.
+// The rows are the atoms, grouped by type; one launch covers every type (blockIdx.z). The layers are row
+// GEMMs on v_mfma_f64_16x16x4f64 with both products of a weight tile (value and tangent) in one pass and
+// the layer's arithmetic in the epilogue: forward the activation, in reverse the adjoint of the layer
+// below with its bias and w_hat sums, so that no elementwise pass stands between two GEMMs. The next
+// K-chunk of every operand is read into registers before the products of the current one.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 
+#include "dpk_device.h"
 #include "dpk_train.h"
 
 namespace dpk {
+namespace {
 
-constexpr int TB = 64, TK = 16;
-
-// ---------------------------------------------------------------------------------------------
-// Row GEMM with layer epilogues, on v_mfma_f64_16x16x4f64. A block computes a 64 x 64 tile of C
-// with four waves of 32 x 32 (2 x 2 MFMA tiles); K runs in chunks of 16 staged in LDS. For one
-// instruction, lane l (group g = l / 16, column c = l % 16) supplies A[c][g] and B[g][c] of the
-// 16 x 16 x 4 step and receives D[g + 4r][c] in register r.
-// ---------------------------------------------------------------------------------------------
-typedef double d4v __attribute__((ext_vector_type(4)));
-constexpr int TAP = TK + 1;   // LDS row pitch of the A tiles (doubles): rows c = 0..15 fall in distinct banks
-
-__device__ __forceinline__ void tr_epilogue(const TrGemm& g, int m, int n, double c, double c2, bool dual)
+// Offsets inside one fitting net's block of the parameter vector: layers (W, b, w_hat) 1600 -> 240 ->
+// 240 -> 240 -> 1.
+constexpr int64_t TF_W[4] = {0, (int64_t)DD * FW + 2 * FW, (int64_t)DD * FW + 4 * FW + FW * FW,
+                             (int64_t)DD * FW + 6 * FW + 2 * FW * FW};
+constexpr int64_t TF_NET = TF_W[3] + FW + 2;
+__host__ __device__ constexpr int tf_in(int l) { return l == 0 ? DD : FW; }   // inputs of layer l = 0, 1, 2
+__host__ __device__ constexpr int64_t tf_w(int l)
 {
-    const int64_t o = (int64_t)m * g.N + n;
-    if (g.mode == TR_FWD) {
-        // skip source: the input row at n (N == K) or n mod K (N == 2K)
-        const int ks = g.N == g.K ? n : (g.N == 2 * g.K ? (n < g.K ? n : n - g.K) : -1);
-        const double a = tanh(c + g.bias[n]);
-        g.C[o] = a;
-        g.Y[o] = g.wh[n] * a + (ks >= 0 ? g.A[(int64_t)m * g.K + ks] : 0.0);
-        if (dual) {
-            g.Zd[o] = c2;
-            g.Yd[o] = g.wh[n] * (1.0 - a * a) * c2 + (ks >= 0 ? g.A2[(int64_t)m * g.K + ks] : 0.0);
+    return l == 0 ? TF_W[0] : l == 1 ? TF_W[1] : l == 2 ? TF_W[2] : TF_W[3];
+}
+
+// ---------------------------------------------------------------------------------------------
+// D = T T_<^T and its tangent, one block per atom
+// ---------------------------------------------------------------------------------------------
+__global__ void __launch_bounds__(256) k_trf_desc(TrfArgs A)
+{
+    __shared__ __attribute__((aligned(16))) double sT[E2][4], sTd[E2][4];
+    const size_t a = blockIdx.x;
+    for (int e = threadIdx.x; e < E2 * 4; e += 256) {
+        sT[e >> 2][e & 3] = A.T[a * E2 * 4 + e];
+        sTd[e >> 2][e & 3] = A.Td[a * E2 * 4 + e];
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < DD; e += 256) {
+        const int m = e >> 4, n = e & 15;
+        double d = 0.0, dd = 0.0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            d += sT[m][k] * sT[n][k];
+            dd += sTd[m][k] * sT[n][k] + sT[m][k] * sTd[n][k];
         }
-    } else if (g.mode == TR_BWD) {
-        double sk = 0.0, sk2 = 0.0;
-        if (g.NS == g.N) {
-            sk = g.S[(int64_t)m * g.NS + n];
-            if (dual) sk2 = g.S2[(int64_t)m * g.NS + n];
-        } else if (g.NS == 2 * g.N) {
-            sk = g.S[(int64_t)m * g.NS + n] + g.S[(int64_t)m * g.NS + n + g.N];
-            if (dual) sk2 = g.S2[(int64_t)m * g.NS + n] + g.S2[(int64_t)m * g.NS + n + g.N];
-        }
-        g.C[o] = c + sk;
-        if (dual) g.C2[o] = c2 + sk2;
-    } else {
-        g.C[o] = c;
-        if (dual) g.C2[o] = c2;
+        A.D[a * DD + e] = d;
+        A.Dd[a * DD + e] = dd;
     }
 }
 
-template <bool DUAL>
-__global__ void __launch_bounds__(256) k_tr_gemm(TrGemm g)
+// Its adjoint: Tb[p] = sum_n Db[p][n] T[n] + Ddb[p][n] Td[n], Tdb[p] = sum_n Ddb[p][n] T[n], and for p < 16
+// also the sums over m of the transposed terms.
+__global__ void __launch_bounds__(256) k_trf_desc_adj(TrfArgs A)
 {
-    __shared__ double sA[TB][TAP];
-    __shared__ double sA2[DUAL ? TB : 1][TAP];
-    __shared__ double sB[TK][TB + 1];
+    __shared__ __attribute__((aligned(16))) double sT[E2][4], sTd[E2][4];
+    __shared__ double sDb[E2][AX + 1], sDdb[E2][AX + 1], s_r[4][64], s_rd[4][64];
+    const size_t a = blockIdx.x;
+    for (int e = threadIdx.x; e < E2 * 4; e += 256) {
+        sT[e >> 2][e & 3] = A.T[a * E2 * 4 + e];
+        sTd[e >> 2][e & 3] = A.Td[a * E2 * 4 + e];
+    }
+    for (int e = threadIdx.x; e < DD; e += 256) {
+        sDb[e >> 4][e & 15] = A.Db[a * DD + e];
+        sDdb[e >> 4][e & 15] = A.Ddb[a * DD + e];
+    }
+    __syncthreads();
+    {
+        // the transposed terms: entry (p, k) of the first 16 rows, a quarter of the m each
+        const int q = threadIdx.x >> 6, p = (threadIdx.x >> 2) & 15, k = threadIdx.x & 3;
+        double tb = 0.0, tdb = 0.0;
+        for (int m = 25 * q; m < 25 * q + 25; ++m) {
+            tb += sDb[m][p] * sT[m][k] + sDdb[m][p] * sTd[m][k];
+            tdb += sDdb[m][p] * sT[m][k];
+        }
+        s_r[q][threadIdx.x & 63] = tb;
+        s_rd[q][threadIdx.x & 63] = tdb;
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < E2 * 4; e += 256) {
+        const int p = e >> 2, k = e & 3;
+        double tb = 0.0, tdb = 0.0;
+#pragma unroll
+        for (int n = 0; n < AX; ++n) {
+            tb += sDb[p][n] * sT[n][k] + sDdb[p][n] * sTd[n][k];
+            tdb += sDdb[p][n] * sT[n][k];
+        }
+        if (p < AX)
+            for (int q = 0; q < 4; ++q) {
+                tb += s_r[q][e];
+                tdb += s_rd[q][e];
+            }
+        A.Tb[a * E2 * 4 + e] = tb;
+        A.Tdb[a * E2 * 4 + e] = tdb;
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Row GEMM, C = X B and C2 = X2 B, on TM x TM tiles (four waves of a quarter each). LDS rows are padded
+// by one double (the 16 rows a wave reads at once fall in distinct banks).
+//   TRF_FWD  layer l: X = the layer's input, B = W; epilogue a, y, zd, yd;
+//   TRF_BWD  layer l (1 or 2) to the pre-activation of layer l - 1: X = zbar_l, B = W^T;
+//   TRF_IN   layer 0 to D: X = zbar_0, B = W^T, stored.
+// TM = 64 with 32-deep K-chunks where that fills the device, else 32 with 64-deep ones.
+// ---------------------------------------------------------------------------------------------
+enum { TRF_FWD, TRF_BWD, TRF_IN };
+
+template <int MODE, int TM>
+__global__ void __launch_bounds__(256) k_trf_gemm(TrfArgs A, int l)
+{
+    constexpr int KC = TM == 64 ? 32 : 64, IT = TM / 32, NLD = TM * KC / 256;
+    __shared__ double sA[TM][KC + 1], sA2[TM][KC + 1], sB[KC][TM + 1];
+    const int ty = blockIdx.z, r0 = A.rows[ty], M = A.rows[ty + 1] - r0;
+    const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TM;
+    if (m0 >= M) return;
+    const int K = MODE == TRF_FWD ? tf_in(l) : FW, N = MODE == TRF_IN ? DD : FW;
+    const double* X = (MODE != TRF_FWD ? A.zb[l] : l == 0 ? A.D : A.y[l - 1]) + (size_t)r0 * K;
+    const double* X2 = (MODE != TRF_FWD ? A.zdb[l] : l == 0 ? A.Dd : A.yd[l - 1]) + (size_t)r0 * K;
+    const int64_t net = A.fit0 + ty * TF_NET;
+    const double* W = A.theta + net + tf_w(l);
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, lg = lane >> 4, lc = lane & 15;
     const int wr = wave >> 1, wc = wave & 1;
-    const int m0 = blockIdx.y * TB, n0 = blockIdx.x * TB;
-    d4v acc[2][2], acc2[2][2];
+    double ra[NLD], ra2[NLD], rb[NLD];
+    // (reads past the edges are clamped and cleared, so that none stands under a branch)
+    auto load = [&](int k0) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+        for (int q = 0; q < NLD; ++q) {
+            const int idx = tid + 256 * q, r = idx / KC, kk = idx % KC, m = m0 + r, k = k0 + kk;
+            const bool in = m < M && k < K;
+            const size_t o = (size_t)min(m, M - 1) * K + min(k, K - 1);
+            const double v = X[o], v2 = X2[o];
+            ra[q] = in ? v : 0.0;
+            ra2[q] = in ? v2 : 0.0;
+            // B[k][n] = W[k][n] forward, W[n][k] in reverse
+            const int kb = MODE == TRF_FWD ? idx / TM : idx % KC, c = MODE == TRF_FWD ? idx % TM : idx / KC;
+            const int n = min(n0 + c, N - 1), k2 = min(k0 + kb, K - 1);
+            const double b = MODE == TRF_FWD ? W[(size_t)k2 * N + n] : W[(size_t)n * K + k2];
+            rb[q] = k0 + kb < K && n0 + c < N ? b : 0.0;
+        }
+        keep_loads();
+    };
+    d4 acc[IT][IT], acc2[IT][IT];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = acc2[i][j] = d4v{0.0, 0.0, 0.0, 0.0};
-    for (int k0 = 0; k0 < g.K; k0 += TK) {
+    for (int i = 0; i < IT; ++i)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
+        for (int j = 0; j < IT; ++j) acc[i][j] = acc2[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+    load(0);
+#pragma unroll 1
+    for (int k0 = 0; k0 < K; k0 += KC) {
+#pragma unroll
+        for (int q = 0; q < NLD; ++q) {
             const int idx = tid + 256 * q;
-            // A tile: 64 rows x 16 k, read along k
-            const int r = idx >> 4, kk = idx & 15;
-            const int m = m0 + r, k = k0 + kk;
-            const bool in = m < g.M && k < g.K;
-            sA[r][kk] = in ? g.A[(int64_t)m * g.K + k] : 0.0;
-            if (DUAL) sA2[r][kk] = in ? g.A2[(int64_t)m * g.K + k] : 0.0;
-            // B tile: 16 k x 64 n
-            if (g.transB) {
-                const int c = idx >> 4, kb = idx & 15;
-                const int n = n0 + c, k2 = k0 + kb;
-                sB[kb][c] = (n < g.N && k2 < g.K) ? g.W[(int64_t)n * g.K + k2] : 0.0;
-            } else {
-                const int kb = idx >> 6, c = idx & 63;
-                const int n = n0 + c, k2 = k0 + kb;
-                sB[kb][c] = (n < g.N && k2 < g.K) ? g.W[(int64_t)k2 * g.N + n] : 0.0;
-            }
+            sA[idx / KC][idx % KC] = ra[q];
+            sA2[idx / KC][idx % KC] = ra2[q];
+            if (MODE == TRF_FWD) sB[idx / TM][idx % TM] = rb[q];
+            else sB[idx % KC][idx / KC] = rb[q];
         }
         __syncthreads();
+        load(min(k0 + KC, K - 1));
 #pragma unroll
-        for (int ks = 0; ks < TK; ks += 4) {
-            double a[2], a2[2], b[2];
+        for (int ks = 0; ks < KC; ks += 4) {
+            double a[IT], a2[IT], b[IT];
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                a[i] = sA[wr * 32 + i * 16 + lc][ks + lg];
-                if (DUAL) a2[i] = sA2[wr * 32 + i * 16 + lc][ks + lg];
-                b[i] = sB[ks + lg][wc * 32 + i * 16 + lc];
+            for (int i = 0; i < IT; ++i) {
+                a[i] = sA[wr * 16 * IT + i * 16 + lc][ks + lg];
+                a2[i] = sA2[wr * 16 * IT + i * 16 + lc][ks + lg];
+                b[i] = sB[ks + lg][wc * 16 * IT + i * 16 + lc];
             }
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+            for (int i = 0; i < IT; ++i)
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
+                for (int j = 0; j < IT; ++j) {
                     acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
-                    if (DUAL) acc2[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a2[i], b[j], acc2[i][j], 0, 0, 0);
+                    acc2[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a2[i], b[j], acc2[i][j], 0, 0, 0);
                 }
         }
         __syncthreads();
     }
+    const double cE = A.coef->cE;
+    const double *bias = W + (size_t)tf_in(l) * FW, *wh = bias + FW;   // (FWD: of layer l)
+    const int lb = l - 1;                                              // (BWD: the layer below)
+    const double* whb = MODE == TRF_BWD ? A.theta + net + tf_w(lb) + (size_t)tf_in(lb) * FW + FW : nullptr;
+    const double *w4 = A.theta + net + tf_w(3), wh4 = w4[FW + 1];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int j = 0; j < IT; ++j) {
+        const int n = n0 + wc * 16 * IT + j * 16 + lc;
+        double sb = 0.0, sh = 0.0;
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int i = 0; i < IT; ++i)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int m = m0 + wr * 32 + i * 16 + lg + 4 * r, n = n0 + wc * 32 + j * 16 + lc;
-                if (m < g.M && n < g.N) tr_epilogue(g, m, n, acc[i][j][r], DUAL ? acc2[i][j][r] : 0.0, DUAL);
+                const int m = m0 + wr * 16 * IT + i * 16 + lg + 4 * r;
+                if (m >= M || n >= N) continue;
+                const double c = acc[i][j][r], c2 = acc2[i][j][r];
+                const size_t o = (size_t)(r0 + m) * N + n;
+                if constexpr (MODE == TRF_FWD) {
+                    const double a = tanh(c + bias[n]);
+                    const double sx = l == 0 ? 0.0 : X[(size_t)m * K + n], sxd = l == 0 ? 0.0 : X2[(size_t)m * K + n];
+                    A.a[l][o] = a;
+                    A.y[l][o] = wh[n] * a + sx;
+                    A.zd[l][o] = c2;
+                    A.yd[l][o] = wh[n] * (1.0 - a * a) * c2 + sxd;
+                } else if constexpr (MODE == TRF_BWD) {
+                    // adjoint of layer lb's output: the product and the skip of layer l
+                    const double yb = c + (l == 2 ? cE * wh4 * w4[n] : A.yb[o]), ydb = c2 + (l == 2 ? wh4 * w4[n] : A.ydb[o]);
+                    const double a = A.a[lb][o], gd = 1.0 - a * a, gzy = gd * A.zd[lb][o] * ydb;
+                    const double zb = whb[n] * (gd * yb - 2.0 * a * gzy);
+                    if (l == 2) {
+                        A.yb[o] = yb;
+                        A.ydb[o] = ydb;
+                    }
+                    A.zb[lb][o] = zb;
+                    A.zdb[lb][o] = whb[n] * gd * ydb;
+                    sb += zb;
+                    sh += a * yb + gzy;
+                } else {
+                    A.Db[o] = c;
+                    A.Ddb[o] = c2;
+                }
             }
+        if constexpr (MODE == TRF_BWD) {
+            sb += __shfl_xor(sb, 16);
+            sb += __shfl_xor(sb, 32);
+            sh += __shfl_xor(sh, 16);
+            sh += __shfl_xor(sh, 32);
+            if (lg == 0 && n < N) {
+                double* gb = A.grad + net + tf_w(lb) + (size_t)tf_in(lb) * FW;
+                unsafeAtomicAdd(&gb[n], sb);
+                unsafeAtomicAdd(&gb[FW + n], sh);
+            }
+        }
+    }
 }
 
-void tr_gemm(const TrGemm& g, hipStream_t s)
+// Output layer o = y3 W4 + b4, E_i = w_hat4 o: the adjoints of its input are cE w_hat4 W4 and w_hat4 W4 for
+// every row; those of layer 3's pre-activation, and the sums of both layers' vectors. A thread per
+// column, OUT_ROWS rows per block.
+constexpr int OUT_ROWS = 16;
+__global__ void __launch_bounds__(256) k_trf_out(TrfArgs A)
 {
-    if (g.M <= 0 || g.N <= 0) return;
-    const dim3 grid((g.N + TB - 1) / TB, (g.M + TB - 1) / TB), block(256);
-    if (g.A2) hipLaunchKernelGGL((k_tr_gemm<true>), grid, block, 0, s, g);
-    else hipLaunchKernelGGL((k_tr_gemm<false>), grid, block, 0, s, g);
+    const int ty = blockIdx.y, r0 = A.rows[ty], M = A.rows[ty + 1] - r0;
+    const int m0 = blockIdx.x * OUT_ROWS, m1 = min(M, m0 + OUT_ROWS), n = threadIdx.x;
+    if (m0 >= M) return;
+    const int64_t net = A.fit0 + ty * TF_NET;
+    const double *w4 = A.theta + net + tf_w(3), b4 = w4[FW], wh4 = w4[FW + 1], cE = A.coef->cE;
+    double* g4 = A.grad + net + tf_w(3);
+    const int64_t v3 = net + tf_w(2) + (int64_t)FW * FW;   // b3, w_hat3
+    double so = 0.0;
+    if (n < FW) {
+        const double w = w4[n], wh = A.theta[v3 + FW + n], ydb = wh4 * w, yb = cE * ydb;
+        double s1 = 0.0, s2 = 0.0, sb = 0.0, sh = 0.0;
+#pragma unroll 4
+        for (int m = m0; m < m1; ++m) {
+            const size_t o = (size_t)(r0 + m) * FW + n;
+            const double a = A.a[2][o], gd = 1.0 - a * a, gzy = gd * A.zd[2][o] * ydb;
+            const double zb = wh * (gd * yb - 2.0 * a * gzy);
+            s1 += A.y[2][o];
+            s2 += A.yd[2][o];
+            A.zb[2][o] = zb;
+            A.zdb[2][o] = wh * gd * ydb;
+            sb += zb;
+            sh += a * yb + gzy;
+        }
+        unsafeAtomicAdd(&g4[n], wh4 * (cE * s1 + s2));
+        unsafeAtomicAdd(&A.grad[v3 + n], sb);
+        unsafeAtomicAdd(&A.grad[v3 + FW + n], sh);
+        so = w * (cE * s1 + s2);   // this column's share of sum over the rows of cE o + odot
+    }
+    __shared__ double s_o[4];
+    for (int k = 1; k < 64; k <<= 1) so += __shfl_xor(so, k);
+    if ((threadIdx.x & 63) == 0) s_o[threadIdx.x >> 6] = so;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsafeAtomicAdd(&g4[FW], cE * wh4 * (m1 - m0));
+        unsafeAtomicAdd(&g4[FW + 1], s_o[0] + s_o[1] + s_o[2] + s_o[3] + cE * b4 * (m1 - m0));
+    }
 }
 
-// ---------------------------------------------------------------------------------------------
-// Weight gradient: Wbar[K][N] += A1^T B1 + A2^T (scale2 B2) over the rows, on the FP64 MFMA with
-// the rows as the reduction index; blockIdx.z takes a row range (FP64 atomics into Wbar).
-// ---------------------------------------------------------------------------------------------
-template <bool DUAL>
-__global__ void __launch_bounds__(256) k_tr_wgrad(int M, int N, int K, int rows_per, const double* A1,
-                                                  const double* B1, const double* A2, const double* B2,
-                                                  const double* scale2, double* Wbar)
+// Weight gradients of the three hidden layers, Wbar = X^T Zb + Xd^T Zdb over the rows: 64 x 64 tiles, the
+// rows split over blockIdx.y; FP64 atomics into the gradient.
+constexpr int WG_T1 = (DD / 64) * 4, WG_T2 = 16, WG_TILES = WG_T1 + 2 * WG_T2;
+__global__ void __launch_bounds__(256) k_trf_wgrad(TrfArgs A, int splits)
 {
-    __shared__ double sA[TK][TB + 1], sB[TK][TB + 1];
-    __shared__ double sA2[DUAL ? TK : 1][TB + 1], sB2[DUAL ? TK : 1][TB + 1];
+    constexpr int TB = 64, KC = 16, NLD = TB * KC / 256;
+    __shared__ double sA[KC][TB + 1], sB[KC][TB + 1], sA2[KC][TB + 1], sB2[KC][TB + 1];
+    const int ty = blockIdx.z, row0 = A.rows[ty], M = A.rows[ty + 1] - row0;
+    const int per = ((M + splits - 1) / splits + KC - 1) / KC * KC;
+    const int r0 = blockIdx.y * per, r1 = min(M, r0 + per);
+    if (r0 >= r1) return;
+    const int t = blockIdx.x, l = t < WG_T1 ? 0 : t < WG_T1 + WG_T2 ? 1 : 2, tl = l == 0 ? t : (t - WG_T1) % WG_T2;
+    const int K = tf_in(l), k0 = (tl >> 2) * TB, n0 = (tl & 3) * TB;
+    const double *X = (l == 0 ? A.D : A.y[l - 1]) + (size_t)row0 * K, *X2 = (l == 0 ? A.Dd : A.yd[l - 1]) + (size_t)row0 * K;
+    const double *Z = A.zb[l] + (size_t)row0 * FW, *Z2 = A.zdb[l] + (size_t)row0 * FW;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, lg = lane >> 4, lc = lane & 15;
     const int wr = wave >> 1, wc = wave & 1;
-    const int k0 = blockIdx.y * TB, n0 = blockIdx.x * TB;
-    const int r0 = blockIdx.z * rows_per, r1 = min(M, r0 + rows_per);
-    d4v acc[2][2];
+    double ra[NLD], ra2[NLD], rb[NLD], rb2[NLD];
+    auto load = [&](int m0) {
+#pragma unroll
+        for (int q = 0; q < NLD; ++q) {
+            const int idx = tid + 256 * q, m = m0 + (idx >> 6), c = idx & 63;
+            const size_t mm = min(m, r1 - 1), ok = mm * K + min(k0 + c, K - 1), on = mm * FW + min(n0 + c, FW - 1);
+            const double x = X[ok], x2 = X2[ok], z = Z[on], z2 = Z2[on];
+            const bool kin = m < r1 && k0 + c < K, nin = m < r1 && n0 + c < FW;
+            ra[q] = kin ? x : 0.0;
+            ra2[q] = kin ? x2 : 0.0;
+            rb[q] = nin ? z : 0.0;
+            rb2[q] = nin ? z2 : 0.0;
+        }
+        keep_loads();
+    };
+    d4 acc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = d4v{0.0, 0.0, 0.0, 0.0};
-    for (int m0 = r0; m0 < r1; m0 += TK) {
+        for (int j = 0; j < 2; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+    load(r0);
+#pragma unroll 1
+    for (int m0 = r0; m0 < r1; m0 += KC) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int idx = tid + 256 * q;
-            const int mm = idx >> 6, c = idx & 63;
-            const int m = m0 + mm;
-            const bool row = m < r1;
-            const int k = k0 + c, n = n0 + c;
-            sA[mm][c] = (row && k < K) ? A1[(int64_t)m * K + k] : 0.0;
-            sB[mm][c] = (row && n < N) ? B1[(int64_t)m * N + n] : 0.0;
-            if (DUAL) {
-                sA2[mm][c] = (row && k < K) ? A2[(int64_t)m * K + k] : 0.0;
-                sB2[mm][c] = (row && n < N) ? B2[(int64_t)m * N + n] * (scale2 ? scale2[m] : 1.0) : 0.0;
-            }
+        for (int q = 0; q < NLD; ++q) {
+            const int idx = tid + 256 * q, mm = idx >> 6, c = idx & 63;
+            sA[mm][c] = ra[q];
+            sA2[mm][c] = ra2[q];
+            sB[mm][c] = rb[q];
+            sB2[mm][c] = rb2[q];
         }
         __syncthreads();
+        load(m0 + KC);
 #pragma unroll
-        for (int ks = 0; ks < TK; ks += 4) {
+        for (int ks = 0; ks < KC; ks += 4) {
             double a[2], b[2], a2[2], b2[2];
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 a[i] = sA[ks + lg][wr * 32 + i * 16 + lc];
                 b[i] = sB[ks + lg][wc * 32 + i * 16 + lc];
-                if (DUAL) {
-                    a2[i] = sA2[ks + lg][wr * 32 + i * 16 + lc];
-                    b2[i] = sB2[ks + lg][wc * 32 + i * 16 + lc];
-                }
+                a2[i] = sA2[ks + lg][wr * 32 + i * 16 + lc];
+                b2[i] = sB2[ks + lg][wc * 32 + i * 16 + lc];
             }
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
                 for (int j = 0; j < 2; ++j) {
                     acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
-                    if (DUAL) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a2[i], b2[j], acc[i][j], 0, 0, 0);
+                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a2[i], b2[j], acc[i][j], 0, 0, 0);
                 }
         }
         __syncthreads();
     }
+    double* G = A.grad + A.fit0 + ty * TF_NET + tf_w(l);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -209,446 +363,93 @@ __global__ void __launch_bounds__(256) k_tr_wgrad(int M, int N, int K, int rows_
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int k = k0 + wr * 32 + i * 16 + lg + 4 * r, n = n0 + wc * 32 + j * 16 + lc;
-                if (k < K && n < N) atomicAdd(&Wbar[(int64_t)k * N + n], acc[i][j][r]);
+                if (k < K && n < FW) unsafeAtomicAdd(&G[(size_t)k * FW + n], acc[i][j][r]);
             }
 }
 
-void tr_wgrad(int M, int N, int K, const double* A1, const double* B1, const double* A2, const double* B2,
-              const double* scale2, double* Wbar, hipStream_t s)
+template <int MODE>
+void gemm(const TrfArgs& a, int l, int ncu, hipStream_t s)
 {
-    if (M <= 0) return;
-    const int tiles = ((N + TB - 1) / TB) * ((K + TB - 1) / TB);
-    // about 2,048 blocks, at least 256 rows each
-    int splits = std::max(1, std::min((M + 255) / 256, 2048 / tiles));
-    const int rows_per = ((M + splits - 1) / splits + TK - 1) / TK * TK;
-    splits = (M + rows_per - 1) / rows_per;
-    const dim3 grid((N + TB - 1) / TB, (K + TB - 1) / TB, splits), block(256);
-    if (A2) hipLaunchKernelGGL((k_tr_wgrad<true>), grid, block, 0, s, M, N, K, rows_per, A1, B1, A2, B2, scale2, Wbar);
-    else hipLaunchKernelGGL((k_tr_wgrad<false>), grid, block, 0, s, M, N, K, rows_per, A1, B1, A2, B2, scale2, Wbar);
+    const int N = MODE == TRF_IN ? DD : FW;
+    const int64_t b64 = (int64_t)((N + 63) / 64) * ((a.n + 63) / 64);
+    if (b64 >= (ncu > 0 ? ncu : 256))
+        hipLaunchKernelGGL((k_trf_gemm<MODE, 64>), dim3((N + 63) / 64, (a.max_rows + 63) / 64, a.nt), dim3(256), 0, s, a, l);
+    else
+        hipLaunchKernelGGL((k_trf_gemm<MODE, 32>), dim3((N + 31) / 32, (a.max_rows + 31) / 32, a.nt), dim3(256), 0, s, a, l);
 }
 
 // ---------------------------------------------------------------------------------------------
-// Column sums (bias and w_hat gradients)
+// Loss
 // ---------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) k_tr_colsum(int M, int N, int rows_per, const double* X1, double* o1,
-                                                   const double* X2, double* o2)
+__global__ void __launch_bounds__(256) k_tr_direction(TrLossArgs A)
 {
-    __shared__ double s1[4][64], s2[4][64];
-    const int c = threadIdx.x & 63, r = threadIdx.x >> 6;
-    const int n = blockIdx.x * 64 + c;
-    const int m0 = blockIdx.y * rows_per, m1 = min(M, m0 + rows_per);
-    double a = 0.0, b = 0.0;
-    if (n < N)
-        for (int m = m0 + r; m < m1; m += 4) {
-            a += X1[(int64_t)m * N + n];
-            if (X2) b += X2[(int64_t)m * N + n];
-        }
-    s1[r][c] = a;
-    s2[r][c] = b;
-    __syncthreads();
-    if (r == 0 && n < N) {
-        atomicAdd(&o1[n], s1[0][c] + s1[1][c] + s1[2][c] + s1[3][c]);
-        if (X2) atomicAdd(&o2[n], s2[0][c] + s2[1][c] + s2[2][c] + s2[3][c]);
-    }
-}
-
-void tr_colsum(int M, int N, const double* X1, double* o1, const double* X2, double* o2, hipStream_t s)
-{
-    if (M <= 0) return;
-    const int rows_per = 1024;
-    const dim3 grid((N + 63) / 64, (M + rows_per - 1) / rows_per), block(256);
-    hipLaunchKernelGGL(k_tr_colsum, grid, block, 0, s, M, N, rows_per, X1, o1, X2, o2);
-}
-
-// ---------------------------------------------------------------------------------------------
-// Element-wise adjoint of a tanh layer
-// ---------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) k_tr_adj_elem(int64_t total, int N, const double* A, const double* Zd,
-                                                     const double* sigma, const double* Yb, const double* Ydb,
-                                                     const double* wh, double* Zb, double* Zdb, double* H)
-{
-    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (int64_t)gridDim.x * 256) {
-        const int64_t m = e / N;
-        const int n = (int)(e - m * N);
-        const double a = A[e], gd = 1.0 - a * a, w = wh[n], yb = Yb[e];
-        const double sg = sigma ? sigma[m] : 1.0;
-        const double zd = Zd ? sg * Zd[e] : 0.0, ydb = Ydb ? Ydb[e] : 0.0;
-        Zb[e] = w * gd * yb - 2.0 * w * a * gd * zd * ydb;
-        H[e] = a * yb + gd * zd * ydb;
-        if (Zdb) Zdb[e] = w * gd * ydb;
-    }
-}
-
-// The same with the column sums of zbar and h added into bsum and hsum (the bias and w_hat
-// gradients): 64 columns x a range of rows per block, the four row groups reduced in LDS.
-__global__ void __launch_bounds__(256) k_tr_adj_sum(int M, int N, int rows_per, const double* A, const double* Zd,
-                                                    const double* sigma, const double* Yb, const double* Ydb,
-                                                    const double* wh, double* Zb, double* Zdb, double* bsum,
-                                                    double* hsum)
-{
-    __shared__ double s1[4][64], s2[4][64];
-    const int c = threadIdx.x & 63, rg = threadIdx.x >> 6;
-    const int n = blockIdx.x * 64 + c;
-    const int m0 = blockIdx.y * rows_per, m1 = min(M, m0 + rows_per);
-    double sb = 0.0, sh = 0.0;
-    if (n < N) {
-        const double w = wh[n];
-        for (int m = m0 + rg; m < m1; m += 4) {
-            const int64_t e = (int64_t)m * N + n;
-            const double a = A[e], gd = 1.0 - a * a, yb = Yb[e];
-            const double sg = sigma ? sigma[m] : 1.0;
-            const double zd = Zd ? sg * Zd[e] : 0.0, ydb = Ydb ? Ydb[e] : 0.0;
-            const double zb = w * gd * yb - 2.0 * w * a * gd * zd * ydb;
-            Zb[e] = zb;
-            if (Zdb) Zdb[e] = w * gd * ydb;
-            sb += zb;
-            sh += a * yb + gd * zd * ydb;
-        }
-    }
-    s1[rg][c] = sb;
-    s2[rg][c] = sh;
-    __syncthreads();
-    if (rg == 0 && n < N) {
-        atomicAdd(&bsum[n], s1[0][c] + s1[1][c] + s1[2][c] + s1[3][c]);
-        atomicAdd(&hsum[n], s2[0][c] + s2[1][c] + s2[2][c] + s2[3][c]);
-    }
-}
-
-void tr_adj_sum(int M, int N, const double* A, const double* Zd, const double* sigma, const double* Yb,
-                const double* Ydb, const double* wh, double* Zb, double* Zdb, double* bsum, double* hsum, hipStream_t s)
-{
-    if (M <= 0) return;
-    const int rows_per = 256;
-    const dim3 grid((N + 63) / 64, (M + rows_per - 1) / rows_per), block(256);
-    hipLaunchKernelGGL(k_tr_adj_sum, grid, block, 0, s, M, N, rows_per, A, Zd, sigma, Yb, Ydb, wh, Zb, Zdb, bsum, hsum);
-}
-
-void tr_adj_elem(int M, int N, const double* A, const double* Zd, const double* sigma, const double* Yb,
-                 const double* Ydb, const double* wh, double* Zb, double* Zdb, double* H, hipStream_t s)
-{
-    const int64_t total = (int64_t)M * N;
-    if (total <= 0) return;
-    const int blocks = (int)std::min<int64_t>((total + 255) / 256, 16384);
-    hipLaunchKernelGGL(k_tr_adj_elem, dim3(blocks), dim3(256), 0, s, total, N, A, Zd, sigma, Yb, Ydb, wh, Zb, Zdb, H);
-}
-
-// ---------------------------------------------------------------------------------------------
-// Pair environment and its tangent
-// ---------------------------------------------------------------------------------------------
-// Switching function of eq. switch and ds/dr (the quintic in factored form, as the inference path).
-__device__ __forceinline__ void tr_switch(double r, double rs, double rc, double& s, double& ds)
-{
-    if (r < rs) {
-        s = 1.0 / r;
-        ds = -s * s;
-    } else if (r < rc) {
-        const double w = rc - rs, x = (r - rs) / w, y = 1.0 - x;
-        const double u = y * y * y * (1.0 + x * (3.0 + 6.0 * x)), du = -30.0 * x * x * y * y;
-        s = u / r;
-        ds = du / (w * r) - u / (r * r);
-    } else {
-        s = 0.0;
-        ds = 0.0;
-    }
-}
-
-__global__ void __launch_bounds__(256) k_tr_env(TrEnv E)
-{
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    if (p >= E.P) return;
-    const int64_t slot = (int64_t)E.pa[p] * E.nc + E.ps[p];
-    const double x = E.nl_r[3 * slot], y = E.nl_r[3 * slot + 1], z = E.nl_r[3 * slot + 2];
-    const double r = sqrt(x * x + y * y + z * z), ir = 1.0 / r;
-    double s, ds;
-    tr_switch(r, E.rs, E.rc, s, ds);
-    const double sr = s * ir, ux = x * ir, uy = y * ir, uz = z * ir;
-    double* R = E.R + 4 * (int64_t)p;
-    R[0] = s;
-    R[1] = sr * x;
-    R[2] = sr * y;
-    R[3] = sr * z;
-    E.X0[p] = s;
-    E.ones[p] = 1.0;
-    if (E.vdir) {
-        const int j = E.nl_j[slot], i = E.perm[E.pa[p]];
-        double d[3];
-        for (int k = 0; k < 3; ++k)
-            d[k] = E.vdir[3 * (int64_t)j + k] - E.vdir[3 * (int64_t)i + k] + E.CV[3 * k] * x + E.CV[3 * k + 1] * y +
-                   E.CV[3 * k + 2] * z;
-        const double q = ux * d[0] + uy * d[1] + uz * d[2];   // rate of change of r
-        const double sd = ds * q, c = (ds - sr) * q;
-        E.sigma[p] = sd;
-        double* Rd = E.Rd + 4 * (int64_t)p;
-        Rd[0] = sd;
-        Rd[1] = c * ux + sr * d[0];
-        Rd[2] = c * uy + sr * d[1];
-        Rd[3] = c * uz + sr * d[2];
-    }
-}
-
-void tr_env(const TrEnv& e, hipStream_t s)
-{
-    if (e.P <= 0) return;
-    hipLaunchKernelGGL(k_tr_env, dim3((e.P + 255) / 256), dim3(256), 0, s, e);
-}
-
-// ---------------------------------------------------------------------------------------------
-// Contraction T = N_c^-1 sum G (x) R, its tangent, and D = T T_<^T (one block per atom)
-// ---------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) k_tr_contract(TrContract C)
-{
-    // two atoms per block, 128 threads each: thread m < 100 accumulates T[m][0..3] (and Td) over the
-    // atom's pairs, reading row p of G at column m (consecutive threads, consecutive columns)
-    __shared__ double sT[2][E2][4], sTd[2][E2][4];
-    const int half = threadIdx.x >> 7, m = threadIdx.x & 127;
-    const int a = blockIdx.x * 2 + half;
-    const bool tan = C.Td != nullptr;
-    if (a < C.n && m < E2) {
-        double t[4] = {0, 0, 0, 0}, td[4] = {0, 0, 0, 0};
-        for (int tj = 0; tj < C.nt; ++tj) {
-            const int p0 = C.apo[(int64_t)a * C.nt + tj], cnt = C.nnei[(int64_t)a * C.nt + tj];
-            for (int p = p0; p < p0 + cnt; ++p) {
-                const double g = C.G[(int64_t)p * E2 + m];
-                const double* r = C.R + 4 * (int64_t)p;
-                const double r0 = r[0], r1 = r[1], r2 = r[2], r3 = r[3];
-                t[0] += g * r0; t[1] += g * r1; t[2] += g * r2; t[3] += g * r3;
-                if (tan) {
-                    const double gd = C.sigma[p] * C.Gd[(int64_t)p * E2 + m];
-                    const double* rd = C.Rd + 4 * (int64_t)p;
-                    td[0] += gd * r0 + g * rd[0];
-                    td[1] += gd * r1 + g * rd[1];
-                    td[2] += gd * r2 + g * rd[2];
-                    td[3] += gd * r3 + g * rd[3];
-                }
+    __shared__ double s_p[4];
+    const int k = blockIdx.x * 256 + threadIdx.x;
+    double lf = 0.0;
+    if (k < A.n) {
+        const double q = A.q ? A.q[k] : 1.0;
+        for (int c = 0; c < 3; ++c) {
+            double v = 0.0;
+            if (A.fl) {
+                const double d = A.F[3 * (size_t)k + c] - A.fl[3 * (size_t)k + c];
+                lf += q * d * d;
+                v = -2.0 * A.pf * q * d / (3.0 * A.n) * A.weight;
             }
-        }
-        for (int k = 0; k < 4; ++k) {
-            t[k] *= C.inv_nc;
-            sT[half][m][k] = t[k];
-            C.T[((int64_t)a * E2 + m) * 4 + k] = t[k];
-            if (tan) {
-                td[k] *= C.inv_nc;
-                sTd[half][m][k] = td[k];
-                C.Td[((int64_t)a * E2 + m) * 4 + k] = td[k];
-            }
+            A.vdir[3 * (size_t)k + c] = v;
         }
     }
+    for (int m = 1; m < 64; m <<= 1) lf += __shfl_xor(lf, m);
+    if ((threadIdx.x & 63) == 0) s_p[threadIdx.x >> 6] = lf;
     __syncthreads();
-    if (a >= C.n) return;
-    for (int e = m; e < DD; e += 128) {
-        const int mm = e / AX, nn = e - mm * AX;
-        double d = 0.0, dd = 0.0;
-        for (int k = 0; k < 4; ++k) {
-            d += sT[half][mm][k] * sT[half][nn][k];
-            if (tan) dd += sTd[half][mm][k] * sT[half][nn][k] + sT[half][mm][k] * sTd[half][nn][k];
+    if (threadIdx.x == 0) A.part[blockIdx.x] = s_p[0] + s_p[1] + s_p[2] + s_p[3];
+}
+
+__global__ void __launch_bounds__(64) k_tr_loss(TrLossArgs A, int nblocks)
+{
+    double lf = 0.0;
+    for (int b = threadIdx.x; b < nblocks; b += 64) lf += A.part[b];
+    for (int m = 1; m < 64; m <<= 1) lf += __shfl_xor(lf, m);
+    if (threadIdx.x) return;
+    TrCoef* c = A.coef;
+    const double N = A.n;
+    double le = 0.0, lv = 0.0;
+    c->cE = 0.0;
+    if (A.has_e) {
+        const double d = c->ev[0] - A.el;
+        le = d * d / N;
+        c->cE = 2.0 * A.pe * d / N * A.weight;
+    }
+    for (int k = 0; k < 9; ++k) {
+        c->CV[k] = 0.0;
+        if (A.has_v) {
+            const double d = c->ev[1 + k] - A.vl[k];
+            lv += d * d;
+            c->CV[k] = -2.0 * A.pv * d / (9.0 * N) * A.weight;
         }
-        C.D[(int64_t)a * DD + e] = d;
-        if (tan) C.Dd[(int64_t)a * DD + e] = dd;
     }
-}
-
-void tr_contract(const TrContract& c, hipStream_t s)
-{
-    if (c.n <= 0) return;
-    hipLaunchKernelGGL(k_tr_contract, dim3((c.n + 1) / 2), dim3(256), 0, s, c);
+    lv /= 9.0 * N;
+    lf /= 3.0 * N;
+    c->loss[0] = A.pe * le + A.pf * lf + A.pv * lv;
+    c->loss[1] = le;
+    c->loss[2] = lf;
+    c->loss[3] = lv;
 }
 
 // ---------------------------------------------------------------------------------------------
-// Adjoint of D = T T_<^T
+// Packing, Adam
 // ---------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) k_tr_dT(const double* T, const double* Td, const double* Db, const double* Ddb,
-                                               double* Tb, double* Tdb)
+__global__ void __launch_bounds__(256) k_tr_map(const double* packed, int64_t n, int* map)
 {
-    __shared__ double sT[E2][4], sTd[E2][4], sDb[DD], sDdb[DD];
-    const int a = blockIdx.x;
-    const bool tan = Ddb != nullptr;
-    for (int e = threadIdx.x; e < E2 * 4; e += 256) {
-        sT[e >> 2][e & 3] = T[(int64_t)a * E2 * 4 + e];
-        if (tan) sTd[e >> 2][e & 3] = Td[(int64_t)a * E2 * 4 + e];
-    }
-    for (int e = threadIdx.x; e < DD; e += 256) {
-        sDb[e] = Db[(int64_t)a * DD + e];
-        if (tan) sDdb[e] = Ddb[(int64_t)a * DD + e];
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < E2 * 4; e += 256) {
-        const int p = e >> 2, k = e & 3;
-        double tb = 0.0, tdb = 0.0;
-        for (int n = 0; n < AX; ++n) {
-            tb += sDb[p * AX + n] * sT[n][k];
-            if (tan) {
-                tb += sDdb[p * AX + n] * sTd[n][k];
-                tdb += sDdb[p * AX + n] * sT[n][k];
-            }
-        }
-        if (p < AX)
-            for (int m = 0; m < E2; ++m) {
-                tb += sDb[m * AX + p] * sT[m][k];
-                if (tan) {
-                    tb += sDdb[m * AX + p] * sTd[m][k];
-                    tdb += sDdb[m * AX + p] * sT[m][k];
-                }
-            }
-        Tb[(int64_t)a * E2 * 4 + e] = tb;
-        if (tan) Tdb[(int64_t)a * E2 * 4 + e] = tdb;
-    }
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n) map[i] = (int)packed[i] - 1;
 }
 
-void tr_dT(int n, const double* T, const double* Td, const double* Db, const double* Ddb, double* Tb, double* Tdb,
-           hipStream_t s)
+__global__ void __launch_bounds__(256) k_tr_pack(const double* theta, const int* map, int64_t n, double* packed)
 {
-    if (n <= 0) return;
-    hipLaunchKernelGGL(k_tr_dT, dim3(n), dim3(256), 0, s, T, Td, Db, Ddb, Tb, Tdb);
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n) packed[i] = map[i] >= 0 ? theta[map[i]] : 0.0;
 }
 
-// ---------------------------------------------------------------------------------------------
-// Fitting output layer (one wave per row)
-// ---------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) k_tr_fit_out(int M, const double* Y, const double* Yd, const double* W4,
-                                                    const double* b4, const double* wh4, double cE, double* Ei,
-                                                    double* sums, double* Yb, double* Ydb)
-{
-    const int m = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (m >= M) return;
-    double o = 0.0, od = 0.0;
-    for (int n = lane; n < FW; n += 64) {
-        const double w = W4[n];
-        o += Y[(int64_t)m * FW + n] * w;
-        if (Yd) od += Yd[(int64_t)m * FW + n] * w;
-        Yb[(int64_t)m * FW + n] = cE * wh4[0] * w;
-        if (Ydb) Ydb[(int64_t)m * FW + n] = wh4[0] * w;
-    }
-    for (int s = 32; s > 0; s >>= 1) {
-        o += __shfl_xor(o, s);
-        od += __shfl_xor(od, s);
-    }
-    if (lane == 0) {
-        o += b4[0];
-        Ei[m] = wh4[0] * o;
-        atomicAdd(&sums[0], o);
-        atomicAdd(&sums[1], od);
-    }
-}
-
-void tr_fit_out(int M, const double* Y, const double* Yd, const double* W4, const double* b4, const double* wh4,
-                double cE, double* Ei, double* sums, double* Yb, double* Ydb, hipStream_t s)
-{
-    if (M <= 0) return;
-    hipLaunchKernelGGL(k_tr_fit_out, dim3((M + 3) / 4), dim3(256), 0, s, M, Y, Yd, W4, b4, wh4, cE, Ei, sums, Yb, Ydb);
-}
-
-__global__ void k_tr_out_grad(int M, const double* S1, const double* S2, const double* sums, const double* wh4,
-                              double cE, double* W4b, double* b4b, double* wh4b)
-{
-    for (int n = threadIdx.x; n < FW; n += blockDim.x) W4b[n] += wh4[0] * (cE * S1[n] + (S2 ? S2[n] : 0.0));
-    if (threadIdx.x == 0) {
-        b4b[0] += cE * wh4[0] * M;
-        wh4b[0] += cE * sums[0] + sums[1];
-    }
-}
-
-void tr_out_grad(int M, const double* S1, const double* S2, const double* sums, const double* wh4, double cE,
-                 double* W4b, double* b4b, double* wh4b, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_tr_out_grad, dim3(1), dim3(256), 0, s, M, S1, S2, sums, wh4, cE, W4b, b4b, wh4b);
-}
-
-// ---------------------------------------------------------------------------------------------
-// Pair adjoints
-// ---------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) k_tr_pair_force(TrPairForce f)
-{
-    __shared__ double sv[9][256];
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    double v[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-    if (p < f.P) {
-        const int a = f.pa[p];
-        const int64_t slot = (int64_t)a * f.nc + f.ps[p];
-        const double x = f.nl_r[3 * slot], y = f.nl_r[3 * slot + 1], z = f.nl_r[3 * slot + 2];
-        const double r = sqrt(x * x + y * y + z * z), ir = 1.0 / r;
-        double s, ds;
-        tr_switch(r, f.rs, f.rc, s, ds);
-        const double* R = f.R + 4 * (int64_t)p;
-        const double* G = f.G + (int64_t)p * E2;
-        const double* Gd = f.Gd + (int64_t)p * E2;
-        const double* dT = f.dT + (int64_t)a * E2 * 4;
-        double dR[4] = {0, 0, 0, 0}, h = 0.0;
-        for (int m = 0; m < E2; ++m) {
-            const double g = G[m], gd = Gd[m];
-            const double t0 = dT[4 * m], t1 = dT[4 * m + 1], t2 = dT[4 * m + 2], t3 = dT[4 * m + 3];
-            dR[0] += g * t0;
-            dR[1] += g * t1;
-            dR[2] += g * t2;
-            dR[3] += g * t3;
-            h += gd * (t0 * R[0] + t1 * R[1] + t2 * R[2] + t3 * R[3]);
-        }
-        for (int k = 0; k < 4; ++k) dR[k] *= f.inv_nc;
-        h *= f.inv_nc;
-        const double ux = x * ir, uy = y * ir, uz = z * ir, sr = s * ir;
-        const double q = dR[1] * ux + dR[2] * uy + dR[3] * uz;
-        const double rad = (dR[0] + h) * ds + q * (ds - sr);
-        const double gx = rad * ux + sr * dR[1], gy = rad * uy + sr * dR[2], gz = rad * uz + sr * dR[3];
-        const int j = f.nl_j[slot], i = f.perm[a];
-        atomicAdd(&f.F[3 * (int64_t)i], gx);
-        atomicAdd(&f.F[3 * (int64_t)i + 1], gy);
-        atomicAdd(&f.F[3 * (int64_t)i + 2], gz);
-        atomicAdd(&f.F[3 * (int64_t)j], -gx);
-        atomicAdd(&f.F[3 * (int64_t)j + 1], -gy);
-        atomicAdd(&f.F[3 * (int64_t)j + 2], -gz);
-        v[0] = -gx * x; v[1] = -gx * y; v[2] = -gx * z;
-        v[3] = -gy * x; v[4] = -gy * y; v[5] = -gy * z;
-        v[6] = -gz * x; v[7] = -gz * y; v[8] = -gz * z;
-    }
-    for (int k = 0; k < 9; ++k) sv[k][threadIdx.x] = v[k];
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w)
-            for (int k = 0; k < 9; ++k) sv[k][threadIdx.x] += sv[k][threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x < 9) atomicAdd(&f.vir[threadIdx.x], sv[threadIdx.x][0]);
-}
-
-void tr_pair_force(const TrPairForce& f, hipStream_t s)
-{
-    if (f.P <= 0) return;
-    hipLaunchKernelGGL(k_tr_pair_force, dim3((f.P + 255) / 256), dim3(256), 0, s, f);
-}
-
-__global__ void __launch_bounds__(256) k_tr_pair_adj(int64_t total, double inv_nc, const int* pa, const double* Tb,
-                                                     const double* Tdb, const double* R, const double* Rd, double* Yb,
-                                                     double* Ydb)
-{
-    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (int64_t)gridDim.x * 256) {
-        const int64_t p = e / E2;
-        const int m = (int)(e - p * E2);
-        const int a = pa[p];
-        const double* tb = Tb + ((int64_t)a * E2 + m) * 4;
-        const double* tdb = Tdb + ((int64_t)a * E2 + m) * 4;
-        const double* r = R + 4 * p;
-        const double* rd = Rd + 4 * p;
-        double yb = 0.0, ydb = 0.0;
-        for (int k = 0; k < 4; ++k) {
-            yb += tb[k] * r[k] + tdb[k] * rd[k];
-            ydb += tdb[k] * r[k];
-        }
-        Yb[e] = inv_nc * yb;
-        Ydb[e] = inv_nc * ydb;
-    }
-}
-
-void tr_pair_adj(int P, double inv_nc, const int* pa, const double* Tb, const double* Tdb, const double* R,
-                 const double* Rd, double* Yb, double* Ydb, hipStream_t s)
-{
-    const int64_t total = (int64_t)P * E2;
-    if (total <= 0) return;
-    const int blocks = (int)std::min<int64_t>((total + 255) / 256, 16384);
-    hipLaunchKernelGGL(k_tr_pair_adj, dim3(blocks), dim3(256), 0, s, total, inv_nc, pa, Tb, Tdb, R, Rd, Yb, Ydb);
-}
-
-// ---------------------------------------------------------------------------------------------
-// Adam and zero fill
-// ---------------------------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) k_tr_adam(int64_t n, double* th, double* g, double* m, double* v, double lr,
                                                  double b1, double b2, double eps, double c1, double c2)
 {
@@ -662,24 +463,46 @@ __global__ void __launch_bounds__(256) k_tr_adam(int64_t n, double* th, double* 
     }
 }
 
+}  // namespace
+
+void trf_run(const TrfArgs& a, int ncu, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_trf_desc, dim3(a.n), dim3(256), 0, s, a);
+    for (int l = 0; l < 3; ++l) gemm<TRF_FWD>(a, l, ncu, s);
+    hipLaunchKernelGGL(k_trf_out, dim3((a.max_rows + OUT_ROWS - 1) / OUT_ROWS, a.nt), dim3(256), 0, s, a);
+    gemm<TRF_BWD>(a, 2, ncu, s);
+    gemm<TRF_BWD>(a, 1, ncu, s);
+    gemm<TRF_IN>(a, 0, ncu, s);
+    const int splits = (int)std::max<int64_t>(1, std::min<int64_t>((a.max_rows + 255) / 256, 4LL * ncu / (WG_TILES * a.nt)));
+    hipLaunchKernelGGL(k_trf_wgrad, dim3(WG_TILES, splits, a.nt), dim3(256), 0, s, a, splits);
+    hipLaunchKernelGGL(k_trf_desc_adj, dim3(a.n), dim3(256), 0, s, a);
+}
+
+int tr_loss_blocks(int n) { return (n + 255) / 256; }
+
+void tr_loss(const TrLossArgs& a, hipStream_t s)
+{
+    const int nb = tr_loss_blocks(a.n);
+    hipLaunchKernelGGL(k_tr_direction, dim3(nb), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_tr_loss, dim3(1), dim3(64), 0, s, a, nb);
+}
+
+void tr_map(const double* packed, int64_t n, int* map, hipStream_t s)
+{
+    if (n > 0) hipLaunchKernelGGL(k_tr_map, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, packed, n, map);
+}
+
+void tr_pack(const double* theta, const int* map, int64_t n, double* packed, hipStream_t s)
+{
+    if (n > 0) hipLaunchKernelGGL(k_tr_pack, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, theta, map, n, packed);
+}
+
 void tr_adam(int64_t n, double* theta, double* g, double* m, double* v, double lr, double b1, double b2, double eps,
              double c1, double c2, hipStream_t s)
 {
     if (n <= 0) return;
     const int blocks = (int)std::min<int64_t>((n + 255) / 256, 4096);
     hipLaunchKernelGGL(k_tr_adam, dim3(blocks), dim3(256), 0, s, n, theta, g, m, v, lr, b1, b2, eps, c1, c2);
-}
-
-__global__ void __launch_bounds__(256) k_tr_zero(double* p, int64_t n)
-{
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) p[i] = 0.0;
-}
-
-void tr_zero(double* p, int64_t n, hipStream_t s)
-{
-    if (n <= 0) return;
-    const int blocks = (int)std::min<int64_t>((n + 255) / 256, 4096);
-    hipLaunchKernelGGL(k_tr_zero, dim3(blocks), dim3(256), 0, s, p, n);
 }
 
 }  // namespace dpk

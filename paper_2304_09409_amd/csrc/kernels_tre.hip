@@ -1,0 +1,647 @@
+// kernels_tre.hip -- training-mode backward through the embedding nets (Sec. II.B), FP64.
+//
+// The loss gradient is the derivative of cE E + sum_ij g_ij . rdot_ij (dpk_train.h): a forward-mode
+// tangent along the pair displacements rdot_ij, then reverse mode through the model and its tangent.
+// The net's input is the scalar s, so its tangent is sdot times the unit tangent d/ds.
+//   k_tre_tan    Td = N_c^-1 sum_j (sdot Gd_j (x) R_j + G_j (x) Rdot_j), with G and Gd = dG/ds
+//                re-evaluated per chunk of 16 neighbours as in the inference kernels;
+//   k_tre_adj    per chunk: the adjoints (ybar, ydbar) of G and sdot Gd from (Tbar, Tdbar), reverse
+//                through the three layers, z = x W + b, a = tanh z, y = w_hat a + skip(x):
+//                  zbar = w_hat (1 - a^2) ybar - 2 w_hat a (1 - a^2) zdot ydbar, zdbar = w_hat (1 - a^2) ydbar,
+//                  hbar = a ybar + (1 - a^2) zdot ydbar (w_hat's gradient),
+//                  xbar = W zbar + skip^T ybar, xdbar = W zdbar + skip^T ydbar;
+//                the operands of the weight gradients go to memory as they stand in registers;
+//   k_tre_wgrad  Wbar_l = sum over the pairs of x zbar^T + xdot zdbar^T, and bbar_l as the row of a
+//                padding feature of x that is set to 1.
+// Layouts as in the embedding kernels: features in registers and lane groups, one pair per lane column,
+// in the skip-aligned order, so every skip and its transpose stay in a lane. One wave per SIMD (up to
+// 512 registers: the layers' values, the running adjoints and the w_hat sums).
+// Bound: the FP64 unit (k_tre_tan 252, k_tre_adj 532, k_tre_wgrad 288 products of 65 cycles per chunk,
+// plus the vector work) and, for k_tre_wgrad, reading the 68 KB per chunk that k_tre_adj wrote.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "dpk_device.h"
+#include "dpk_internal.h"
+#include "dpk_launch.h"
+#include "dpk_train.h"
+#include "emb_device.h"
+
+namespace dpk {
+namespace {
+
+typedef PF64 P;
+typedef EmbCfg<PF64> Cfg;
+typedef P::frag frag;
+constexpr int NW = 4;                          // waves per block, one per SIMD
+constexpr int NU1 = Cfg::NU1, NU2 = Cfg::NU2;  // registers in use of layers 1 and 2 (of 8 and 16)
+// Padding registers whose lane group 0 carries the constant 1 of the bias gradients
+constexpr int ONE1 = 7, ONE2 = 14;
+static_assert(ONE1 >= NU1 && ONE2 >= NU2, "padding registers");
+// One chunk's operands: registers [u][64 lanes] of each quantity
+constexpr int D_Z3 = 0, D_ZD3 = 28, D_Y2 = 56, D_YD2 = 72, D_Z2 = 88, D_ZD2 = 104, D_Y1 = 120, D_YD1 = 128;
+static_assert((D_YD1 + 8) * 64 == TRE_CHUNK, "operand block of a chunk");
+// Offsets inside one net's block of the parameter vector
+constexpr int G_W1 = 0, G_B1 = 25, G_H1 = 50, G_W2 = 75, G_B2 = G_W2 + E0 * E1, G_H2 = G_B2 + E1, G_W3 = G_H2 + E1,
+              G_B3 = G_W3 + E1 * E2, G_H3 = G_B3 + E2, G_NET = TRE_NET;
+static_assert(G_H3 + E2 == G_NET, "parameters of a net");
+
+// Environment row and its tangent of one pair: r_ij, rdot_ij = v_j - v_i + CV r_ij.
+struct Pair {
+    double s, sd, R[4], Rd[4];
+};
+__device__ __forceinline__ void pair_env(const EmbArgs& A, const TrCoef* co, double inv_w, double x, double y, double z,
+                                         const double* vj, const double* vi, bool valid, Pair& o)
+{
+    o.s = o.sd = 0.0;
+    for (int k = 0; k < 4; ++k) o.R[k] = o.Rd[k] = 0.0;
+    if (!valid) return;
+    const double r = sqrt(x * x + y * y + z * z), ir = 1.0 / r;
+    double s, ds, d[3];
+    switch_fn(r, ir, A.rs, A.rc, inv_w, s, ds);
+    const double sr = s * ir, ux = x * ir, uy = y * ir, uz = z * ir;
+    for (int k = 0; k < 3; ++k) d[k] = vj[k] - vi[k] + co->CV[3 * k] * x + co->CV[3 * k + 1] * y + co->CV[3 * k + 2] * z;
+    const double q = ux * d[0] + uy * d[1] + uz * d[2], c = (ds - sr) * q;   // q: rate of change of r
+    o.s = s;
+    o.sd = ds * q;
+    o.R[0] = s; o.R[1] = sr * x; o.R[2] = sr * y; o.R[3] = sr * z;
+    o.Rd[0] = o.sd; o.Rd[1] = c * ux + sr * d[0]; o.Rd[2] = c * uy + sr * d[1]; o.Rd[3] = c * uz + sr * d[2];
+}
+
+__global__ void __launch_bounds__(64 * NW, 1) k_tre_tan(TreArgs K)
+{
+    const EmbArgs& A = K.e;
+    __shared__ double s_vec[EVEC];
+    __shared__ __attribute__((aligned(16))) char s_w2[N2P * Cfg::ROW2];
+    __shared__ __attribute__((aligned(16))) char s_w3[N3P * Cfg::ROW3];
+    // layer 2 and its unit tangent, neighbour-major, for the skip into the untransposed layer 3
+    __shared__ double s_z2[NW][2][16][Z2S];
+    __shared__ __attribute__((aligned(16))) double s_R[NW][16][10];   // R, Rdot, sdot (a pad) per pair
+    __shared__ double s_th[TH_N];
+
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
+    const double inv_w = 1.0 / (A.rc - A.rs);
+    const int APB = A.apb, APW = (APB + NW - 1) / NW;
+    const int a0 = blockIdx.x * APB, a1 = min(a0 + APB, A.natoms);
+    if (a0 >= a1) return;
+    tanh_tab_fill(s_th);
+    const int t_lo = A.itype[a0], t_hi = A.itype[a1 - 1];
+    for (int ti = t_lo; ti <= t_hi; ++ti)
+        for (int tj = 0; tj < A.ntypes; ++tj) {
+            const int net = A.type_one_side ? tj : ti * A.ntypes + tj;
+            __syncthreads();
+            stage_net<P>(A, net, s_vec, s_w2, s_w3);
+            __syncthreads();
+            ChunkWalk<> w;
+            w.i = 0;
+            w.c0 = 0;
+            w.ac = 0;
+            w.have = w.template find_atom<true>(A, nullptr, a0, a1, wave, NW, APW, ti, tj, false);
+            w.template fetch<true>(A, tj, c16);
+            d4 Tacc[7];
+            while (w.have) {
+                const double x = w.px, y = w.py, z = w.pz;
+                const int ca = w.a, cc0 = w.c0, cnp = w.np;
+                double vj[3], vi[3];
+                for (int k = 0; k < 3; ++k) {
+                    vj[k] = K.vdir[3 * (size_t)max(w.pj, 0) + k];
+                    vi[k] = K.vdir[3 * (size_t)w.ac + k];
+                }
+                bool last = false;
+                w.c0 += 16;
+                if (w.c0 >= w.np) {
+                    ++w.i;
+                    w.c0 = 0;
+                    w.have = w.template find_atom<true>(A, nullptr, a0, a1, wave, NW, APW, ti, tj, false);
+                    last = true;
+                }
+                w.template fetch<true>(A, tj, c16);
+                if (cc0 == 0)
+                    for (int t = 0; t < 7; ++t) zero4(Tacc[t]);
+                Pair pr;
+                pair_env(A, K.coef, inv_w, x, y, z, vj, vi, cc0 + c16 < cnp, pr);
+                const double s = pr.s;
+                wave_sync();
+                if (g == 0) {
+                    for (int k = 0; k < 4; ++k) {
+                        s_R[wave][c16][k] = pr.R[k];
+                        s_R[wave][c16][4 + k] = pr.Rd[k];
+                    }
+                    s_R[wave][c16][8] = pr.sd;
+                }
+                frag B1[Cfg::NC1], B1d[Cfg::NC1];
+                double z1[8], z1d[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    z1[u] = z1d[u] = 0;
+                    if (u >= NU1) continue;
+                    const int k = P::kidx(u / 4, g, u % 4);
+                    const double w1 = s_vec[EV_W1 + k], wh = s_vec[EV_WH1 + k];
+                    const double t1 = P::act(s * w1 + s_vec[EV_B1 + k], s_th);
+                    z1[u] = wh * t1;
+                    z1d[u] = wh * (1 - t1 * t1) * w1;
+                }
+#pragma unroll
+                for (int c = 0; c < Cfg::NC1; ++c) {
+                    B1[c] = P::make(&z1[4 * c]);
+                    B1d[c] = P::make(&z1d[4 * c]);
+                }
+                d4 acc2[4], acc2d[4];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    zero4(acc2[t]);
+                    zero4(acc2d[t]);
+#pragma unroll
+                    for (int c = 0; c < Cfg::NC1; ++c) {
+                        const frag W = lds_frag<P>(s_w2, Cfg::ROW2, 16 * t + c16, 4 * c + g);
+                        P::mma(acc2[t], W, B1[c], Cfg::ku(NU1, c));
+                        P::mma(acc2d[t], W, B1d[c], Cfg::ku(NU1, c));
+                    }
+                }
+                wave_sync();
+                double zt[16], ztd[16];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) {
+                    zt[u] = ztd[u] = 0;
+                    if (u >= NU2) continue;
+                    const int n = 16 * (u >> 2) + P::orow(g, u & 3);
+                    const double t2 = P::act_b(acc2[u >> 2][u & 3], s_vec[EV_B2 + n], s_th), wh = s_vec[EV_WH2 + n];
+                    zt[u] = wh * t2 + z1[u >> 1];
+                    ztd[u] = wh * (1 - t2 * t2) * acc2d[u >> 2][u & 3] + z1d[u >> 1];
+                    s_z2[wave][0][c16][n] = zt[u];
+                    s_z2[wave][1][c16][n] = ztd[u];
+                }
+                frag A3[Cfg::NC2], A3d[Cfg::NC2];
+#pragma unroll
+                for (int c = 0; c < Cfg::NC2; ++c) {
+                    A3[c] = P::make(&zt[4 * c]);
+                    A3d[c] = P::make(&ztd[4 * c]);
+                }
+                auto mm3 = [&](int tm, d4& o, d4& od) {
+                    zero4(o);
+                    zero4(od);
+#pragma unroll
+                    for (int c = 0; c < Cfg::NC2; ++c) {
+                        const frag Bw = lds_frag<P>(s_w3, Cfg::ROW3, 16 * tm + c16, 4 * c + g);
+                        P::mma(o, A3[c], Bw, Cfg::ku(NU2, c));
+                        P::mma(od, A3d[c], Bw, Cfg::ku(NU2, c));
+                    }
+                };
+                const int gc = P::ogrp(c16), rc = P::oreg(c16);
+                auto epi3 = [&](int tm, const d4& o, const d4& od) {
+                    const int m = 16 * tm + c16;
+                    const int u2 = (4 * tm + rc) >> 1;
+                    const int n2 = 16 * (u2 >> 2) + P::orow(gc, u2 & 3);
+                    const double wh = s_vec[EV_WH3 + m], bb = s_vec[EV_B3 + m];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int q = P::orow(g, r);
+
+                        const double t3 = P::act_b(o[r], bb, s_th);
+                        const double G = wh * t3 + s_z2[wave][0][q][n2];
+                        const double Gd = (wh * (1 - t3 * t3) * od[r] + s_z2[wave][1][q][n2]) * s_R[wave][q][8];
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) Tacc[tm][k] += Gd * s_R[wave][q][k] + G * s_R[wave][q][4 + k];
+                    }
+                };
+                wave_sync();
+                d4 a3[2], a3d[2];
+                mm3(0, a3[0], a3d[0]);
+#pragma unroll
+                for (int tm = 0; tm < 7; ++tm) {
+                    if (tm + 1 < 7) mm3(tm + 1, a3[(tm + 1) & 1], a3d[(tm + 1) & 1]);
+                    epi3(tm, a3[tm & 1], a3d[tm & 1]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (last) {
+                    double Tprev[7];
+                    for (int tm = 0; tm < 7; ++tm) {
+                        const int f = emb_feat(3, gc, 4 * tm + rc);
+                        Tprev[tm] = (tj > 0 && f >= 0) ? K.Td[((size_t)ca * E2 + f) * 4 + ksel(g)] : 0.0;
+                    }
+                    for (int tm = 0; tm < 7; ++tm) {
+                        const double tv[4] = {Tacc[tm][0], Tacc[tm][1], Tacc[tm][2], Tacc[tm][3]};
+                        const double v = sum_groups4(tv);
+                        const int f = emb_feat(3, gc, 4 * tm + rc);
+                        if (f >= 0) K.Td[((size_t)ca * E2 + f) * 4 + ksel(g)] = v * A.inv_nc + Tprev[tm];
+                    }
+                }
+            }
+        }
+}
+
+// A fragment of W itself (rows = the layer's inputs) from the staged W^T: input 16 t + c16, outputs
+// 16 c + orow(g, v) (row pitch rowb, K order of the staged rows).
+__device__ __forceinline__ frag lds_frag_t(const char* base, int rowb, int t, int c, int g, int c16)
+{
+    const char* p = base + (16 * c + g) * rowb + (4 * t + (c16 & 3)) * P::GB + (c16 >> 2) * 8;
+    frag f;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) f.v[v] = *reinterpret_cast<const double*>(p + 4 * v * rowb);
+    return f;
+}
+
+__global__ void __launch_bounds__(64 * NW, 1) k_tre_adj(TreArgs K)
+{
+    const EmbArgs& A = K.e;
+    __shared__ double s_vec[EVEC];
+    __shared__ __attribute__((aligned(16))) char s_w2[N2P * Cfg::ROW2];
+    __shared__ __attribute__((aligned(16))) char s_w3[N3P * Cfg::ROW3];
+    // Tbar and Tdbar of the wave's current atom by layer-3 row position (padding rows zero)
+    __shared__ __attribute__((aligned(16))) double s_tb[NW][N3P][8];
+    __shared__ double s_th[TH_N];
+
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
+    const double inv_w = 1.0 / (A.rc - A.rs);
+    const int APB = A.apb, APW = (APB + NW - 1) / NW;
+    const int a0 = blockIdx.x * APB, a1 = min(a0 + APB, A.natoms);
+    if (a0 >= a1) return;
+    tanh_tab_fill(s_th);
+    for (int e = lane; e < N3P * 8; e += 64) s_tb[wave][e >> 3][e & 7] = 0.0;
+    const int t_lo = A.itype[a0], t_hi = A.itype[a1 - 1];
+    for (int ti = t_lo; ti <= t_hi; ++ti)
+        for (int tj = 0; tj < A.ntypes; ++tj) {
+            const int net = A.type_one_side ? tj : ti * A.ntypes + tj;
+            __syncthreads();
+            stage_net<P>(A, net, s_vec, s_w2, s_w3);
+            __syncthreads();
+            ChunkWalk<> w;
+            w.i = 0;
+            w.c0 = 0;
+            w.ac = 0;
+            w.have = w.template find_atom<true>(A, nullptr, a0, a1, wave, NW, APW, ti, tj, true);
+            w.template fetch<true>(A, tj, c16);
+            // sums over the wave's pairs of this net: w_hat's gradient of every layer, and W1's and b1's
+            double h3[28], h2[NU2], h1[NU1], gw1[NU1], gb1[NU1];
+#pragma unroll
+            for (int u = 0; u < 28; ++u) h3[u] = 0.0;
+#pragma unroll
+            for (int u = 0; u < NU2; ++u) h2[u] = 0.0;
+#pragma unroll
+            for (int u = 0; u < NU1; ++u) h1[u] = gw1[u] = gb1[u] = 0.0;
+            const bool any = w.have;
+            while (w.have) {
+                const double x = w.px, y = w.py, z = w.pz;
+                const int ca = w.a, cc0 = w.c0, cnp = w.np;
+                double vj[3], vi[3];
+                for (int k = 0; k < 3; ++k) {
+                    vj[k] = K.vdir[3 * (size_t)max(w.pj, 0) + k];
+                    vi[k] = K.vdir[3 * (size_t)w.ac + k];
+                }
+                if (cc0 == 0) {
+                    wave_sync();
+                    for (int e = lane; e < E2 * 4; e += 64) {
+                        int gf = 0, uf = 0;
+                        emb_reg3(e >> 2, gf, uf);
+                        const int row = 16 * (uf >> 2) + P::orow(gf, uf & 3);
+                        s_tb[wave][row][e & 3] = K.Tb[(size_t)ca * E2 * 4 + e] * A.inv_nc;
+                        s_tb[wave][row][4 + (e & 3)] = K.Tdb[(size_t)ca * E2 * 4 + e] * A.inv_nc;
+                    }
+                    wave_sync();
+                }
+                w.c0 += 16;
+                if (w.c0 >= w.np) {
+                    ++w.i;
+                    w.c0 = 0;
+                    w.have = w.template find_atom<true>(A, nullptr, a0, a1, wave, NW, APW, ti, tj, true);
+                }
+                w.template fetch<true>(A, tj, c16);
+                double* dump = K.dump + (size_t)(K.coff[(size_t)tj * (A.natoms + 1) + ca] + (cc0 >> 4)) * TRE_CHUNK + lane;
+                auto put = [&](int at, int u, double v) { dump[(at + u) * 64] = v; };
+                Pair pr;
+                pair_env(A, K.coef, inv_w, x, y, z, vj, vi, cc0 + c16 < cnp, pr);
+                const double s = pr.s, sd = pr.sd;
+                // forward: the layers' tanh outputs and unit tangents
+                double t1[8], z1[8], z1d[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    t1[u] = z1[u] = z1d[u] = 0;
+                    if (u < NU1) {
+                        const int k = P::kidx(u / 4, g, u % 4);
+                        const double w1 = s_vec[EV_W1 + k], wh = s_vec[EV_WH1 + k];
+                        t1[u] = P::act(s * w1 + s_vec[EV_B1 + k], s_th);
+                        z1[u] = wh * t1[u];
+                        z1d[u] = wh * (1 - t1[u] * t1[u]) * w1;
+                    }
+                    put(D_Y1, u, u == ONE1 ? (g == 0 ? 1.0 : 0.0) : z1[u]);
+                    put(D_YD1, u, sd * z1d[u]);
+                }
+                d4 acc2[4], zd2[4];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    zero4(acc2[t]);
+                    zero4(zd2[t]);
+#pragma unroll
+                    for (int c = 0; c < Cfg::NC1; ++c) {
+                        const frag W = lds_frag<P>(s_w2, Cfg::ROW2, 16 * t + c16, 4 * c + g);
+                        P::mma(acc2[t], W, P::make(&z1[4 * c]), Cfg::ku(NU1, c));
+                        P::mma(zd2[t], W, P::make(&z1d[4 * c]), Cfg::ku(NU1, c));
+                    }
+                }
+                double t2[16], zt[16], ztd[16];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) {
+                    t2[u] = zt[u] = ztd[u] = 0;
+                    if (u < NU2) {
+                        const int n = 16 * (u >> 2) + P::orow(g, u & 3);
+                        const double wh = s_vec[EV_WH2 + n];
+                        t2[u] = P::act_b(acc2[u >> 2][u & 3], s_vec[EV_B2 + n], s_th);
+                        zt[u] = wh * t2[u] + z1[u >> 1];
+                        ztd[u] = wh * (1 - t2[u] * t2[u]) * zd2[u >> 2][u & 3] + z1d[u >> 1];
+                    }
+                    put(D_Y2, u, u == ONE2 ? (g == 0 ? 1.0 : 0.0) : zt[u]);
+                    put(D_YD2, u, sd * ztd[u]);
+                }
+                auto mm3 = [&](int tm, d4& o, d4& od) {
+                    zero4(o);
+                    zero4(od);
+#pragma unroll
+                    for (int c = 0; c < Cfg::NC2; ++c) {
+                        const frag W = lds_frag<P>(s_w3, Cfg::ROW3, 16 * tm + c16, 4 * c + g);
+                        P::mma(o, W, P::make(&zt[4 * c]), Cfg::ku(NU2, c));
+                        P::mma(od, W, P::make(&ztd[4 * c]), Cfg::ku(NU2, c));
+                    }
+                };
+                // layer 3: adjoints of the output, of the pre-activation, and the products with W3
+                double yb2[16], ydb2[16];   // adjoints of layer 2's output: the skip first
+                d4 xb[4], xdb[4];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    zero4(xb[t]);
+                    zero4(xdb[t]);
+                }
+                auto epi3 = [&](int tm, const d4& o, const d4& od) {
+                    d4 zb, zdb;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int u = 4 * tm + r, m = 16 * tm + P::orow(g, r);
+                        const double* tb = s_tb[wave][m];
+                        double yb = 0.0, ydb = 0.0;
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            yb += tb[k] * pr.R[k] + tb[4 + k] * pr.Rd[k];
+                            ydb += tb[4 + k] * pr.R[k];
+                        }
+                        const double t3 = P::act_b(o[r], s_vec[EV_B3 + m], s_th), gd = 1 - t3 * t3, wh = s_vec[EV_WH3 + m];
+                        const double gzy = gd * (sd * od[r]) * ydb;
+                        zb[r] = wh * (gd * yb - 2 * t3 * gzy);
+                        zdb[r] = wh * gd * ydb;
+                        h3[u] += t3 * yb + gzy;
+                        put(D_Z3, u, zb[r]);
+                        put(D_ZD3, u, zdb[r]);
+                        yb2[u >> 1] = (u & 1) ? yb2[u >> 1] + yb : yb;
+                        ydb2[u >> 1] = (u & 1) ? ydb2[u >> 1] + ydb : ydb;
+                    }
+                    frag fb, fdb;
+                    fb.v = zb;
+                    fdb.v = zdb;
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        const frag W = lds_frag_t(s_w3, Cfg::ROW3, t, tm, g, c16);
+                        P::mma(xb[t], W, fb);
+                        P::mma(xdb[t], W, fdb);
+                    }
+                };
+                d4 a3[2], a3d[2];
+                mm3(0, a3[0], a3d[0]);
+#pragma unroll
+                for (int tm = 0; tm < 7; ++tm) {
+                    if (tm + 1 < 7) mm3(tm + 1, a3[(tm + 1) & 1], a3d[(tm + 1) & 1]);
+                    epi3(tm, a3[tm & 1], a3d[tm & 1]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                // layer 2
+                double yb1[8], ydb1[8];
+                d4 xb1[2], xdb1[2];
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    zero4(xb1[t]);
+                    zero4(xdb1[t]);
+                }
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    d4 zb, zdb;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int u = 4 * c + r;
+                        zb[r] = zdb[r] = 0.0;
+                        if (u < NU2) {
+                            const int n = 16 * c + P::orow(g, r);
+                            const double yb = yb2[u] + xb[c][r], ydb = ydb2[u] + xdb[c][r];
+                            const double gd = 1 - t2[u] * t2[u], wh = s_vec[EV_WH2 + n], gzy = gd * (sd * zd2[c][r]) * ydb;
+                            zb[r] = wh * (gd * yb - 2 * t2[u] * gzy);
+                            zdb[r] = wh * gd * ydb;
+                            h2[u] += t2[u] * yb + gzy;
+                            yb1[u >> 1] = (u & 1) ? yb1[u >> 1] + yb : yb;
+                            ydb1[u >> 1] = (u & 1) ? ydb1[u >> 1] + ydb : ydb;
+                        }
+                        put(D_Z2, u, zb[r]);
+                        put(D_ZD2, u, zdb[r]);
+                    }
+                    frag fb, fdb;
+                    fb.v = zb;
+                    fdb.v = zdb;
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) {
+                        const frag W = lds_frag_t(s_w2, Cfg::ROW2, t, c, g, c16);
+                        P::mma(xb1[t], W, fb, Cfg::ku(NU2, c));
+                        P::mma(xdb1[t], W, fdb, Cfg::ku(NU2, c));
+                    }
+                }
+                // layer 1: input s, its tangent sdot
+#pragma unroll
+                for (int u = 0; u < NU1; ++u) {
+                    const int k = P::kidx(u / 4, g, u % 4);
+                    const double yb = yb1[u] + xb1[u >> 2][u & 3], ydb = ydb1[u] + xdb1[u >> 2][u & 3];
+                    const double gd = 1 - t1[u] * t1[u], wh = s_vec[EV_WH1 + k], gzy = gd * (sd * s_vec[EV_W1 + k]) * ydb;
+                    const double zb = wh * (gd * yb - 2 * t1[u] * gzy);
+                    h1[u] += t1[u] * yb + gzy;
+                    gb1[u] += zb;
+                    gw1[u] += s * zb + sd * (wh * gd * ydb);
+                }
+            }
+            // sums over the 16 pair columns, then into the gradient (feature of register u in group g)
+            if (any) {
+                double* gr = K.grad + (size_t)net * G_NET;
+                auto add = [&](int off, int f, double v) {
+                    for (int m = 1; m < 16; m <<= 1) v += __shfl_xor(v, m);
+                    if (c16 == 0 && f >= 0) unsafeAtomicAdd(&gr[off + f], v);
+                };
+#pragma unroll
+                for (int u = 0; u < 28; ++u) add(G_H3, emb_feat(3, g, u), h3[u]);
+#pragma unroll
+                for (int u = 0; u < NU2; ++u) add(G_H2, emb_feat(2, g, u), h2[u]);
+#pragma unroll
+                for (int u = 0; u < NU1; ++u) {
+                    const int f = emb_feat(1, g, u);
+                    add(G_H1, f, h1[u]);
+                    add(G_B1, f, gb1[u]);
+                    add(G_W1, f, gw1[u]);
+                }
+            }
+        }
+}
+
+// Weight and bias gradients of layers 2 and 3. The chunks (grouped by net) are split evenly over the
+// blocks; of a block's eight waves, wave w takes the output tiles w % 4 and w % 4 + 4 of W3 and w % 4 of W2
+// for every second chunk; the two halves meet in LDS and the sums go to the gradient with atomics. An
+// operand tile is a register dump [4][64 lanes] of 16 features x 16 pairs: lane (i, g) of an MFMA takes
+// feature row i and the pairs 4g..4g+3, which are consecutive there (the pairs are the summation index,
+// in any order).
+__global__ void __launch_bounds__(512, 2) k_tre_wgrad(TreArgs K)
+{
+    const EmbArgs& A = K.e;
+    __shared__ d4 s_red[4][10][64];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), w = wave & 3, half = wave >> 2;
+    const int lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
+    const int nt = A.ntypes, n = A.natoms;
+    const int64_t ld = n + 1;
+    const int total = K.coff[(size_t)(nt - 1) * ld + n];
+    const int b0 = (int)((int64_t)total * blockIdx.x / gridDim.x), b1 = (int)((int64_t)total * (blockIdx.x + 1) / gridDim.x);
+    const int off = 64 * (c16 >> 2) + 16 * (c16 & 3) + 4 * g;
+    auto tile = [&](const double* d, int u0) { return *reinterpret_cast<const d4*>(d + u0 * 64 + off); };
+    for (int tj = 0; tj < nt; ++tj)
+        for (int ti = 0; ti < (A.type_one_side ? 1 : nt); ++ti) {
+            const int net = A.type_one_side ? tj : ti * nt + tj;
+            const int n0 = K.coff[tj * ld + (A.type_one_side ? 0 : K.toff[ti])], n1 = K.coff[tj * ld + (A.type_one_side ? n : K.toff[ti + 1])];
+            const int lo = max(b0, n0), hi = min(b1, n1);
+            if (lo >= hi) continue;   // (uniform over the block)
+            d4 a3[2][4], a2[2];       // W3: [output tile][input tile]; W2: [input tile]
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                zero4(a2[q]);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) zero4(a3[q][t]);
+            }
+            const int m1 = min(w + 4, 6);   // (wave 3 has one output tile of W3: it repeats tile 6, not added)
+#pragma unroll 1
+            for (int c = lo + half; c < hi; c += 2) {
+                const double* d = K.dump + (size_t)c * TRE_CHUNK;
+                d4 y[4], yd[4];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    y[t] = tile(d, D_Y2 + 4 * t);
+                    yd[t] = tile(d, D_YD2 + 4 * t);
+                }
+                const d4 z0 = tile(d, D_Z3 + 4 * w), zd0 = tile(d, D_ZD3 + 4 * w), z1 = tile(d, D_Z3 + 4 * m1), zd1 = tile(d, D_ZD3 + 4 * m1);
+                const d4 x0 = tile(d, D_Y1), x1 = tile(d, D_Y1 + 4), xd0 = tile(d, D_YD1), xd1 = tile(d, D_YD1 + 4);
+                const d4 q = tile(d, D_Z2 + 4 * w), qd = tile(d, D_ZD2 + 4 * w);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        a3[0][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(y[t][v], z0[v], a3[0][t], 0, 0, 0);
+                        a3[1][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(y[t][v], z1[v], a3[1][t], 0, 0, 0);
+                    }
+                    a2[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x0[v], q[v], a2[0], 0, 0, 0);
+                    a2[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(x1[v], q[v], a2[1], 0, 0, 0);
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        a3[0][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(yd[t][v], zd0[v], a3[0][t], 0, 0, 0);
+                        a3[1][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(yd[t][v], zd1[v], a3[1][t], 0, 0, 0);
+                    }
+                    a2[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(xd0[v], qd[v], a2[0], 0, 0, 0);
+                    a2[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(xd1[v], qd[v], a2[1], 0, 0, 0);
+                }
+            }
+            __syncthreads();
+            if (half)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    s_red[w][t][lane] = a3[0][t];
+                    s_red[w][4 + t][lane] = a3[1][t];
+                    if (t < 2) s_red[w][8 + t][lane] = a2[t];
+                }
+            __syncthreads();
+            if (!half) {
+                double* gr = K.grad + (size_t)net * G_NET;
+                // rows g + 4r of input tile t, column c16 of output tile m: W[input][output], or the bias
+                // where the input is the padding register that holds 1
+                auto out = [&](int l, int t, int m, const d4& v, const d4& o, int W, int B, int width) {
+                    const int fo = emb_feat(l, c16 & 3, 4 * m + (c16 >> 2));
+                    if (fo < 0) return;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int u = 4 * t + r, fi = emb_feat(l - 1, g, u);
+                        if (fi >= 0) unsafeAtomicAdd(&gr[W + fi * width + fo], v[r] + o[r]);
+                        else if (g == 0 && u == (l == 3 ? ONE2 : ONE1)) unsafeAtomicAdd(&gr[B + fo], v[r] + o[r]);
+                    }
+                };
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    out(3, t, w, a3[0][t], s_red[w][t][lane], G_W3, G_B3, E2);
+                    if (w + 4 < 7) out(3, t, w + 4, a3[1][t], s_red[w][4 + t][lane], G_W3, G_B3, E2);
+                    if (t < 2) out(2, t, w, a2[t], s_red[w][8 + t][lane], G_W2, G_B2, E1);
+                }
+            }
+        }
+}
+
+// Chunk offsets: coff[tj][a] = the first chunk of atom a's block of neighbours of type tj (chunks of 16
+// kept neighbours, by neighbour type, then atom); coff[tj][n] ends the type. One block.
+__global__ void __launch_bounds__(1024) k_tre_offsets(int n, int nt, const int* nnei, int* coff)
+{
+    __shared__ int s_w[16];
+    __shared__ int s_base;
+    if (threadIdx.x == 0) s_base = 0;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int tj = 0; tj < nt; ++tj)
+        for (int a0 = 0; a0 < n; a0 += 1024) {
+            __syncthreads();
+            const int a = a0 + threadIdx.x;
+            const int own = a < n ? (nnei[(size_t)a * nt + tj] + 15) >> 4 : 0;
+            int v = own;
+            for (int m = 1; m < 64; m <<= 1) {
+                const int o = __shfl_up(v, m);
+                if (lane >= m) v += o;
+            }
+            if (lane == 63) s_w[wave] = v;
+            __syncthreads();
+            int pre = s_base, all = 0;
+            for (int q = 0; q < 16; ++q) {
+                if (q < wave) pre += s_w[q];
+                all += s_w[q];
+            }
+            if (a < n) coff[(size_t)tj * (n + 1) + a] = pre + v - own;
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                s_base += all;
+                if (a0 + 1024 >= n) coff[(size_t)tj * (n + 1) + n] = s_base;
+            }
+        }
+}
+
+}  // namespace
+
+// Blocks of four waves, an even share of the atoms per CU, at most eight atoms per wave.
+static int tre_apb(int64_t n, int64_t ncu)
+{
+    if (ncu <= 0) ncu = 256;
+    const int64_t rounds = std::max<int64_t>(1, (n + ncu * 8 * NW - 1) / (ncu * 8 * NW));
+    return (int)std::max<int64_t>(NW, (n + ncu * rounds - 1) / (ncu * rounds));
+}
+
+void tre_offsets(int n, int nt, const int* nnei, int* coff, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_tre_offsets, dim3(1), dim3(1024), 0, s, n, nt, nnei, coff);
+}
+
+void tre_tangent(const TreArgs& k0, hipStream_t s)
+{
+    TreArgs k = k0;
+    k.e.apb = tre_apb(k.e.natoms, k.e.ncu);
+    hipLaunchKernelGGL(k_tre_tan, dim3((k.e.natoms + k.e.apb - 1) / k.e.apb), dim3(64 * NW), 0, s, k);
+}
+
+void tre_gradient(const TreArgs& k0, hipStream_t s)
+{
+    TreArgs k = k0;
+    k.e.apb = tre_apb(k.e.natoms, k.e.ncu);
+    hipLaunchKernelGGL(k_tre_adj, dim3((k.e.natoms + k.e.apb - 1) / k.e.apb), dim3(64 * NW), 0, s, k);
+    hipLaunchKernelGGL(k_tre_wgrad, dim3(k.e.ncu > 0 ? k.e.ncu : 256), dim3(512), 0, s, k);
+}
+
+}  // namespace dpk
