@@ -115,12 +115,13 @@ __global__ void __launch_bounds__(256) k_trf_desc_adj(TrfArgs A)
 enum { TRF_FWD, TRF_BWD, TRF_IN };
 
 template <int MODE, int TM>
-__global__ void __launch_bounds__(256) k_trf_gemm(TrfArgs A, int l)
+__global__ void __launch_bounds__(256, 2) k_trf_gemm(TrfArgs A, int l, int nt)
 {
     constexpr int KC = TM == 64 ? 32 : 64, IT = TM / 32, NLD = TM * KC / 256;
     __shared__ double sA[TM][KC + 1], sA2[TM][KC + 1], sB[KC][TM + 1];
-    const int ty = blockIdx.z, r0 = A.rows[ty], M = A.rows[ty + 1] - r0;
-    const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TM;
+    // The column tiles of a row tile run on one XCD, one after the other: X is read from memory once.
+    const int xi = blockIdx.x >> 3, m0 = (xi / nt * 8 + (blockIdx.x & 7)) * TM, n0 = xi % nt * TM;
+    const int ty = blockIdx.y, r0 = A.rows[ty], M = A.rows[ty + 1] - r0;
     if (m0 >= M) return;
     const int K = MODE == TRF_FWD ? tf_in(l) : FW, N = MODE == TRF_IN ? DD : FW;
     const double* X = (MODE != TRF_FWD ? A.zb[l] : l == 0 ? A.D : A.y[l - 1]) + (size_t)r0 * K;
@@ -130,21 +131,19 @@ __global__ void __launch_bounds__(256) k_trf_gemm(TrfArgs A, int l)
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, lg = lane >> 4, lc = lane & 15;
     const int wr = wave >> 1, wc = wave & 1;
     double ra[NLD], ra2[NLD], rb[NLD];
-    // (reads past the edges are clamped and cleared, so that none stands under a branch)
+    // Reads past the edges are clamped here and cleared on the way to LDS: nothing waits for them before
+    // the products of the chunk at hand.
     auto load = [&](int k0) {
 #pragma unroll
         for (int q = 0; q < NLD; ++q) {
-            const int idx = tid + 256 * q, r = idx / KC, kk = idx % KC, m = m0 + r, k = k0 + kk;
-            const bool in = m < M && k < K;
-            const size_t o = (size_t)min(m, M - 1) * K + min(k, K - 1);
-            const double v = X[o], v2 = X2[o];
-            ra[q] = in ? v : 0.0;
-            ra2[q] = in ? v2 : 0.0;
+            const int idx = tid + 256 * q, r = idx / KC, kk = idx % KC;
+            const size_t o = (size_t)min(m0 + r, M - 1) * K + min(k0 + kk, K - 1);
+            ra[q] = X[o];
+            ra2[q] = X2[o];
             // B[k][n] = W[k][n] forward, W[n][k] in reverse
             const int kb = MODE == TRF_FWD ? idx / TM : idx % KC, c = MODE == TRF_FWD ? idx % TM : idx / KC;
             const int n = min(n0 + c, N - 1), k2 = min(k0 + kb, K - 1);
-            const double b = MODE == TRF_FWD ? W[(size_t)k2 * N + n] : W[(size_t)n * K + k2];
-            rb[q] = k0 + kb < K && n0 + c < N ? b : 0.0;
+            rb[q] = MODE == TRF_FWD ? W[(size_t)k2 * N + n] : W[(size_t)n * K + k2];
         }
         keep_loads();
     };
@@ -158,11 +157,12 @@ __global__ void __launch_bounds__(256) k_trf_gemm(TrfArgs A, int l)
     for (int k0 = 0; k0 < K; k0 += KC) {
 #pragma unroll
         for (int q = 0; q < NLD; ++q) {
-            const int idx = tid + 256 * q;
-            sA[idx / KC][idx % KC] = ra[q];
-            sA2[idx / KC][idx % KC] = ra2[q];
-            if (MODE == TRF_FWD) sB[idx / TM][idx % TM] = rb[q];
-            else sB[idx % KC][idx / KC] = rb[q];
+            const int idx = tid + 256 * q, r = idx / KC, kk = idx % KC;
+            const bool in = m0 + r < M && k0 + kk < K;
+            sA[r][kk] = in ? ra[q] : 0.0;
+            sA2[r][kk] = in ? ra2[q] : 0.0;
+            const int kb = MODE == TRF_FWD ? idx / TM : kk, c = MODE == TRF_FWD ? idx % TM : r;
+            sB[kb][c] = k0 + kb < K && n0 + c < N ? rb[q] : 0.0;
         }
         __syncthreads();
         load(min(k0 + KC, K - 1));
@@ -288,15 +288,15 @@ __global__ void __launch_bounds__(256) k_trf_out(TrfArgs A)
 // Weight gradients of the three hidden layers, Wbar = X^T Zb + Xd^T Zdb over the rows: 64 x 64 tiles, the
 // rows split over blockIdx.y; FP64 atomics into the gradient.
 constexpr int WG_T1 = (DD / 64) * 4, WG_T2 = 16, WG_TILES = WG_T1 + 2 * WG_T2;
-__global__ void __launch_bounds__(256) k_trf_wgrad(TrfArgs A, int splits)
+__global__ void __launch_bounds__(256, 2) k_trf_wgrad(TrfArgs A, int splits, int grp)
 {
     constexpr int TB = 64, KC = 16, NLD = TB * KC / 256;
     __shared__ double sA[KC][TB + 1], sB[KC][TB + 1], sA2[KC][TB + 1], sB2[KC][TB + 1];
-    const int ty = blockIdx.z, row0 = A.rows[ty], M = A.rows[ty + 1] - row0;
+    const int ty = blockIdx.y, row0 = A.rows[ty], M = A.rows[ty + 1] - row0;
     const int per = ((M + splits - 1) / splits + KC - 1) / KC * KC;
-    const int r0 = blockIdx.y * per, r1 = min(M, r0 + per);
+    const int xi = blockIdx.x / grp, r0 = (xi / WG_TILES * grp + blockIdx.x % grp) * per, r1 = min(M, r0 + per);
     if (r0 >= r1) return;
-    const int t = blockIdx.x, l = t < WG_T1 ? 0 : t < WG_T1 + WG_T2 ? 1 : 2, tl = l == 0 ? t : (t - WG_T1) % WG_T2;
+    const int t = xi % WG_TILES, l = t < WG_T1 ? 0 : t < WG_T1 + WG_T2 ? 1 : 2, tl = l == 0 ? t : (t - WG_T1) % WG_T2;
     const int K = tf_in(l), k0 = (tl >> 2) * TB, n0 = (tl & 3) * TB;
     const double *X = (l == 0 ? A.D : A.y[l - 1]) + (size_t)row0 * K, *X2 = (l == 0 ? A.Dd : A.yd[l - 1]) + (size_t)row0 * K;
     const double *Z = A.zb[l] + (size_t)row0 * FW, *Z2 = A.zdb[l] + (size_t)row0 * FW;
@@ -308,12 +308,10 @@ __global__ void __launch_bounds__(256) k_trf_wgrad(TrfArgs A, int splits)
         for (int q = 0; q < NLD; ++q) {
             const int idx = tid + 256 * q, m = m0 + (idx >> 6), c = idx & 63;
             const size_t mm = min(m, r1 - 1), ok = mm * K + min(k0 + c, K - 1), on = mm * FW + min(n0 + c, FW - 1);
-            const double x = X[ok], x2 = X2[ok], z = Z[on], z2 = Z2[on];
-            const bool kin = m < r1 && k0 + c < K, nin = m < r1 && n0 + c < FW;
-            ra[q] = kin ? x : 0.0;
-            ra2[q] = kin ? x2 : 0.0;
-            rb[q] = nin ? z : 0.0;
-            rb2[q] = nin ? z2 : 0.0;
+            ra[q] = X[ok];
+            ra2[q] = X2[ok];
+            rb[q] = Z[on];
+            rb2[q] = Z2[on];
         }
         keep_loads();
     };
@@ -328,10 +326,11 @@ __global__ void __launch_bounds__(256) k_trf_wgrad(TrfArgs A, int splits)
 #pragma unroll
         for (int q = 0; q < NLD; ++q) {
             const int idx = tid + 256 * q, mm = idx >> 6, c = idx & 63;
-            sA[mm][c] = ra[q];
-            sA2[mm][c] = ra2[q];
-            sB[mm][c] = rb[q];
-            sB2[mm][c] = rb2[q];
+            const bool kin = m0 + mm < r1 && k0 + c < K, nin = m0 + mm < r1 && n0 + c < FW;
+            sA[mm][c] = kin ? ra[q] : 0.0;
+            sA2[mm][c] = kin ? ra2[q] : 0.0;
+            sB[mm][c] = nin ? rb[q] : 0.0;
+            sB2[mm][c] = nin ? rb2[q] : 0.0;
         }
         __syncthreads();
         load(m0 + KC);
@@ -372,10 +371,11 @@ void gemm(const TrfArgs& a, int l, int ncu, hipStream_t s)
 {
     const int N = MODE == TRF_IN ? DD : FW;
     const int64_t b64 = (int64_t)((N + 63) / 64) * ((a.n + 63) / 64);
+    auto grid = [&](int tm) { return dim3((a.max_rows + 8 * tm - 1) / (8 * tm) * 8 * ((N + tm - 1) / tm), a.nt); };
     if (b64 >= (ncu > 0 ? ncu : 256))
-        hipLaunchKernelGGL((k_trf_gemm<MODE, 64>), dim3((N + 63) / 64, (a.max_rows + 63) / 64, a.nt), dim3(256), 0, s, a, l);
+        hipLaunchKernelGGL((k_trf_gemm<MODE, 64>), grid(64), dim3(256), 0, s, a, l, (N + 63) / 64);
     else
-        hipLaunchKernelGGL((k_trf_gemm<MODE, 32>), dim3((N + 31) / 32, (a.max_rows + 31) / 32, a.nt), dim3(256), 0, s, a, l);
+        hipLaunchKernelGGL((k_trf_gemm<MODE, 32>), grid(32), dim3(256), 0, s, a, l, (N + 31) / 32);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -473,8 +473,11 @@ void trf_run(const TrfArgs& a, int ncu, hipStream_t s)
     gemm<TRF_BWD>(a, 2, ncu, s);
     gemm<TRF_BWD>(a, 1, ncu, s);
     gemm<TRF_IN>(a, 0, ncu, s);
-    const int splits = (int)std::max<int64_t>(1, std::min<int64_t>((a.max_rows + 255) / 256, 4LL * ncu / (WG_TILES * a.nt)));
-    hipLaunchKernelGGL(k_trf_wgrad, dim3(WG_TILES, splits, a.nt), dim3(256), 0, s, a, splits);
+    // Row ranges in groups of 8: all tiles of a range on one XCD, which reads its rows once. Short ranges
+    // would only add atomics: one range below 2048 rows.
+    const int grp = a.max_rows < 2048 ? 1 : 8;
+    const int splits = grp * (int)std::max<int64_t>(1, std::min<int64_t>(a.max_rows / (256 * grp), 4LL * ncu / (WG_TILES * grp * a.nt)));
+    hipLaunchKernelGGL(k_trf_wgrad, dim3(WG_TILES * splits, a.nt), dim3(256), 0, s, a, splits, grp);
     hipLaunchKernelGGL(k_trf_desc_adj, dim3(a.n), dim3(256), 0, s, a);
 }
 
