@@ -2523,7 +2523,7 @@ void dpk_server_free(dpk_server* s)
 // candidate-buffer retry as dpk_compute, and the network queued behind it; the geometry's error flags
 // are waited for here, while the network runs.
 int dpk::frame_network(dpk_ctx* c, int64_t natoms, const double* coord, const int32_t* atype, const double* box,
-                       double* ev, FrameNet* f)
+                       double* ev, int* coff, int* chunks, FrameNet* f)
 {
     if (!c || !coord || !atype || !f) return fail(DPK_E_INVALID_ARG, "NULL argument");
     if (natoms < 1 || natoms > (1LL << 30)) return fail(DPK_E_INVALID_ARG, "natoms = %lld", (long long)natoms);
@@ -2558,7 +2558,10 @@ int dpk::frame_network(dpk_ctx* c, int64_t natoms, const double* coord, const in
         HIPCHK(hipMemcpyAsync(c->h_coord, coord, sizeof(double) * 3 * natoms, hipMemcpyHostToDevice, s));
         HIPCHK(hipMemcpyAsync(c->h_atype, atype, sizeof(int) * natoms, hipMemcpyHostToDevice, s));
         enqueue_geometry(c, n, c->h_coord, c->h_atype, gp, c->F, s, false, nullptr);
+        const int nt = c->model->desc.ntypes;
+        tre_offsets(n, nt, c->nnei, coff, s);
         HIPCHK(hipMemcpyAsync(c->pin_stats, c->stats, sizeof(DevStats), hipMemcpyDeviceToHost, s));
+        HIPCHK(hipMemcpyAsync(chunks, coff + (size_t)nt * (n + 1) - 1, sizeof(int), hipMemcpyDeviceToHost, s));
         HIPCHK(hipEventRecord(c->stats_copied, s));
         run_network(c, n, gp, c->F, nullptr, true, nullptr, nullptr, s);
         launch_finalize(embed_bwd_blocks(c->precision, c->tab, n, c->ncu, is_e3(c), 1), c->vir_part, ev, ev + 1, c->stats, s);

@@ -32,10 +32,10 @@ struct FrameNet {
 };
 // Partition, bin and search one host frame on the context's device and stream and queue the network and
 // its adjoint with the context's packed weights; E and the virial [9] go to ev (device, 10 doubles). Waits
-// for the geometry only (its errors are reported here). The context keeps the buffers until its next
-// frame.
+// for the geometry only (its errors are reported here), and for the chunk offsets: coff (device, nt (n + 1))
+// is filled and *chunks (pinned) their number. The context keeps the buffers until its next frame.
 int frame_network(dpk_ctx* c, int64_t natoms, const double* coord, const int32_t* atype, const double* box, double* ev,
-                  FrameNet* f);
+                  int* coff, int* chunks, FrameNet* f);
 // The context's packed FP64 weights (device) in four buffers: embedding vectors and matrices, fitting
 // vectors and matrices.
 struct PackedWeights {
@@ -75,18 +75,22 @@ void tr_loss(const TrLossArgs& a, hipStream_t s);
 // Embedding nets. Chunks of 16 kept neighbours of one atom and neighbour type; coff [nt][n + 1] their
 // offsets (by neighbour type, then atom). dump: TRE_CHUNK doubles per chunk.
 constexpr int TRE_CHUNK = 136 * 64;
+// Adjoints of T and Td of an atom, over N_c: [layer-3 row position][T 4, Td 4], padding rows zero
+constexpr int TRE_TB = N3P * 8;
 constexpr int TRE_NET = 3 * E0 + E0 * E1 + 2 * E1 + E1 * E2 + 2 * E2;   // parameters of one embedding net
 struct TreArgs {
     EmbArgs e;
     const int* toff;
     const int* coff;
+    int4* cmap;                   // [chunks]
     const double* vdir;
     const TrCoef* coef;
     double* Td;                   // [n][100][4] (tangent pass output)
-    const double *Tb, *Tdb;       // [n][100][4] adjoints of T and Td
+    const double* Tb;             // [n][TRE_TB] adjoints of T and Td
     double* dump;
     double* grad;                 // gradient in the parameter layout (embedding nets first)
 };
+// Chunk offsets; coff[nt - 1][n] is the number of chunks.
 void tre_offsets(int n, int nt, const int* nnei, int* coff, hipStream_t s);
 void tre_tangent(const TreArgs& k, hipStream_t s);    // Td
 void tre_gradient(const TreArgs& k, hipStream_t s);   // embedding gradients (added)
@@ -99,14 +103,15 @@ struct TrfArgs {
     double* grad;
     int64_t fit0;                 // parameter offset of the first fitting net
     const double *T, *Td;
-    double *Tb, *Tdb;
+    double* Tb;                   // [n][TRE_TB]
+    double inv_nc;
     const TrCoef* coef;
     double *D, *Dd, *Db, *Ddb;    // [n][1600] descriptor, its tangent, their adjoints
     double *a[3], *y[3], *zd[3], *yd[3];   // [n][240] per layer: tanh, output, tangents of z and y
     double *zb[3], *zdb[3];       // [n][240] adjoints of the pre-activation and its tangent
     double *yb, *ydb;             // [n][240] adjoints of layer 2's output
 };
-// Forward with tangents from T and Td, reverse to Tb and Tdb, every fitting gradient added.
+// Forward with tangents from T and Td, reverse to Tb, every fitting gradient added.
 void trf_run(const TrfArgs& a, int ncu, hipStream_t s);
 
 // Adam (Kingma and Ba): m = b1 m + (1 - b1) g, v = b2 v + (1 - b2) g^2,

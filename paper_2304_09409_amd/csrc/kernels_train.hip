@@ -59,7 +59,7 @@ __global__ void __launch_bounds__(256) k_trf_desc(TrfArgs A)
 }
 
 // Its adjoint: Tb[p] = sum_n Db[p][n] T[n] + Ddb[p][n] Td[n], Tdb[p] = sum_n Ddb[p][n] T[n], and for p < 16
-// also the sums over m of the transposed terms.
+// also the sums over m of the transposed terms; over N_c, in the order of TRE_TB.
 __global__ void __launch_bounds__(256) k_trf_desc_adj(TrfArgs A)
 {
     __shared__ __attribute__((aligned(16))) double sT[E2][4], sTd[E2][4];
@@ -99,8 +99,15 @@ __global__ void __launch_bounds__(256) k_trf_desc_adj(TrfArgs A)
                 tb += s_r[q][e];
                 tdb += s_rd[q][e];
             }
-        A.Tb[a * E2 * 4 + e] = tb;
-        A.Tdb[a * E2 * 4 + e] = tdb;
+        int g = 0, u = 0;
+        emb_reg3(p, g, u);
+        double* o = A.Tb + a * TRE_TB + (16 * (u >> 2) + g + 4 * (u & 3)) * 8 + k;
+        o[0] = tb * A.inv_nc;
+        o[4] = tdb * A.inv_nc;
+    }
+    for (int e = threadIdx.x; e < TRE_TB; e += 256) {
+        const int r = e >> 3;
+        if (emb_feat(3, r & 3, 4 * (r >> 4) + ((r & 15) >> 2)) < 0) A.Tb[a * TRE_TB + e] = 0.0;
     }
 }
 

@@ -69,6 +69,81 @@ __device__ __forceinline__ void pair_env(const EmbArgs& A, const TrCoef* co, dou
     o.Rd[0] = o.sd; o.Rd[1] = c * ux + sr * d[0]; o.Rd[2] = c * uy + sr * d[1]; o.Rd[3] = c * uz + sr * d[2];
 }
 
+// Per-wave walk over the chunks [c, end) of one net. The items of the next chunk are loaded while the
+// current one is worked on, in two steps, since vdir_j needs the neighbour's index: fetch() at its start,
+// fetch_v() in its middle. Nothing then waits for a load behind the stores of the current chunk (the
+// counter of vector memory operations is in order). The map is read one chunk further ahead.
+struct TreWalk {
+    int c, end;
+    int4 m;                      // the chunk's map entry
+    double x, y, z, vj[3], vi[3];
+    int4 m1, m2;                 // of the next chunk and the one after it
+    double nx, ny, nz, nvj[3], nvi[3];
+    int nj;
+    __device__ __forceinline__ int4 map(const TreArgs& K, int k) const { return K.cmap[min(k, end - 1)]; }
+    __device__ __forceinline__ int4 uniform(int4 v) const
+    {
+        return int4{__builtin_amdgcn_readfirstlane(v.x), __builtin_amdgcn_readfirstlane(v.y),
+                    __builtin_amdgcn_readfirstlane(v.z), __builtin_amdgcn_readfirstlane(v.w)};
+    }
+    // (a lane past its atom's neighbours reads another slot of the atom's row, which holds finite values)
+    __device__ __forceinline__ void fetch(const TreArgs& K, int tj, int c16)
+    {
+        m1 = uniform(m2);
+        m2 = map(K, c + 2);
+        const size_t slot = (size_t)m1.x * K.e.nc + min(K.e.off[tj] + m1.z + c16, K.e.nc - 1);
+        const double* v = K.e.nl_r + 3 * slot;
+        nx = v[0];
+        ny = v[1];
+        nz = v[2];
+        nj = K.e.nl_j[slot];
+        keep_loads();
+    }
+    __device__ __forceinline__ void fetch_v(const TreArgs& K)
+    {
+        for (int k = 0; k < 3; ++k) {
+            nvj[k] = K.vdir[3 * (size_t)max(nj, 0) + k];
+            nvi[k] = K.vdir[3 * (size_t)m1.y + k];
+        }
+        keep_loads();
+    }
+    __device__ __forceinline__ void take()
+    {
+        m = m1;
+        x = nx;
+        y = ny;
+        z = nz;
+        for (int k = 0; k < 3; ++k) {
+            vj[k] = nvj[k];
+            vi[k] = nvi[k];
+        }
+    }
+    // c < end
+    __device__ __forceinline__ void start(const TreArgs& K, int tj, int c16, int lo, int hi)
+    {
+        c = lo - 1;
+        end = hi;
+        m2 = map(K, lo);
+        fetch(K, tj, c16);
+        fetch_v(K);
+        c = lo;
+        take();
+    }
+};
+
+// The chunk range of wave `wave` of this block in the net (ti, tj); false if the block has none there.
+__device__ __forceinline__ bool net_range(const TreArgs& K, int ti, int tj, int wave, int& lo, int& hi)
+{
+    const int nt = K.e.ntypes, n = K.e.natoms, side = K.e.type_one_side;
+    const int64_t ld = n + 1, total = K.coff[(nt - 1) * ld + n];
+    const int b0 = (int)(total * blockIdx.x / gridDim.x), b1 = (int)(total * (blockIdx.x + 1) / gridDim.x);
+    const int c0 = max(b0, K.coff[tj * ld + (side ? 0 : K.toff[ti])]), c1 = min(b1, K.coff[tj * ld + (side ? n : K.toff[ti + 1])]);
+    if (c0 >= c1) return false;
+    lo = c0 + (int)((int64_t)(c1 - c0) * wave / NW);
+    hi = c0 + (int)((int64_t)(c1 - c0) * (wave + 1) / NW);
+    return true;
+}
+
 __global__ void __launch_bounds__(64 * NW, 1) k_tre_tan(TreArgs K)
 {
     const EmbArgs& A = K.e;
@@ -83,45 +158,23 @@ __global__ void __launch_bounds__(64 * NW, 1) k_tre_tan(TreArgs K)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
     const double inv_w = 1.0 / (A.rc - A.rs);
-    const int APB = A.apb, APW = (APB + NW - 1) / NW;
-    const int a0 = blockIdx.x * APB, a1 = min(a0 + APB, A.natoms);
-    if (a0 >= a1) return;
     tanh_tab_fill(s_th);
-    const int t_lo = A.itype[a0], t_hi = A.itype[a1 - 1];
-    for (int ti = t_lo; ti <= t_hi; ++ti)
-        for (int tj = 0; tj < A.ntypes; ++tj) {
-            const int net = A.type_one_side ? tj : ti * A.ntypes + tj;
+    for (int tj = 0; tj < A.ntypes; ++tj)
+        for (int ti = 0; ti < (A.type_one_side ? 1 : A.ntypes); ++ti) {
+            int lo, hi;
+            if (!net_range(K, ti, tj, wave, lo, hi)) continue;   // (uniform over the block)
             __syncthreads();
-            stage_net<P>(A, net, s_vec, s_w2, s_w3);
+            stage_net<P>(A, A.type_one_side ? tj : ti * A.ntypes + tj, s_vec, s_w2, s_w3);
             __syncthreads();
-            ChunkWalk<> w;
-            w.i = 0;
-            w.c0 = 0;
-            w.ac = 0;
-            w.have = w.template find_atom<true>(A, nullptr, a0, a1, wave, NW, APW, ti, tj, false);
-            w.template fetch<true>(A, tj, c16);
+            if (lo >= hi) continue;
+            TreWalk w;
+            w.start(K, tj, c16, lo, hi);
             d4 Tacc[7];
-            while (w.have) {
-                const double x = w.px, y = w.py, z = w.pz;
-                const int ca = w.a, cc0 = w.c0, cnp = w.np;
-                double vj[3], vi[3];
-                for (int k = 0; k < 3; ++k) {
-                    vj[k] = K.vdir[3 * (size_t)max(w.pj, 0) + k];
-                    vi[k] = K.vdir[3 * (size_t)w.ac + k];
-                }
-                bool last = false;
-                w.c0 += 16;
-                if (w.c0 >= w.np) {
-                    ++w.i;
-                    w.c0 = 0;
-                    w.have = w.template find_atom<true>(A, nullptr, a0, a1, wave, NW, APW, ti, tj, false);
-                    last = true;
-                }
-                w.template fetch<true>(A, tj, c16);
-                if (cc0 == 0)
-                    for (int t = 0; t < 7; ++t) zero4(Tacc[t]);
+            for (int t = 0; t < 7; ++t) zero4(Tacc[t]);
+            for (;;) {
+                w.fetch(K, tj, c16);
                 Pair pr;
-                pair_env(A, K.coef, inv_w, x, y, z, vj, vi, cc0 + c16 < cnp, pr);
+                pair_env(A, K.coef, inv_w, w.x, w.y, w.z, w.vj, w.vi, w.m.z + c16 < w.m.w, pr);
                 const double s = pr.s;
                 wave_sync();
                 if (g == 0) {
@@ -179,6 +232,7 @@ __global__ void __launch_bounds__(64 * NW, 1) k_tre_tan(TreArgs K)
                     A3[c] = P::make(&zt[4 * c]);
                     A3d[c] = P::make(&ztd[4 * c]);
                 }
+                w.fetch_v(K);
                 auto mm3 = [&](int tm, d4& o, d4& od) {
                     zero4(o);
                     zero4(od);
@@ -215,19 +269,21 @@ __global__ void __launch_bounds__(64 * NW, 1) k_tre_tan(TreArgs K)
                     epi3(tm, a3[tm & 1], a3d[tm & 1]);
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                if (last) {
-                    double Tprev[7];
-                    for (int tm = 0; tm < 7; ++tm) {
-                        const int f = emb_feat(3, gc, 4 * tm + rc);
-                        Tprev[tm] = (tj > 0 && f >= 0) ? K.Td[((size_t)ca * E2 + f) * 4 + ksel(g)] : 0.0;
-                    }
+                const bool more = w.c + 1 < w.end;
+                if (!more || w.m1.x != w.m.x) {
+                    // the atom's (or the wave's) last chunk here: its share of Td
+#pragma unroll
                     for (int tm = 0; tm < 7; ++tm) {
                         const double tv[4] = {Tacc[tm][0], Tacc[tm][1], Tacc[tm][2], Tacc[tm][3]};
                         const double v = sum_groups4(tv);
                         const int f = emb_feat(3, gc, 4 * tm + rc);
-                        if (f >= 0) K.Td[((size_t)ca * E2 + f) * 4 + ksel(g)] = v * A.inv_nc + Tprev[tm];
+                        if (f >= 0) unsafeAtomicAdd(&K.Td[((size_t)w.m.x * E2 + f) * 4 + ksel(g)], v * A.inv_nc);
+                        zero4(Tacc[tm]);
                     }
                 }
+                if (!more) break;
+                ++w.c;
+                w.take();
             }
         }
 }
@@ -256,24 +312,19 @@ __global__ void __launch_bounds__(64 * NW, 1) k_tre_adj(TreArgs K)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
     const double inv_w = 1.0 / (A.rc - A.rs);
-    const int APB = A.apb, APW = (APB + NW - 1) / NW;
-    const int a0 = blockIdx.x * APB, a1 = min(a0 + APB, A.natoms);
-    if (a0 >= a1) return;
     tanh_tab_fill(s_th);
-    for (int e = lane; e < N3P * 8; e += 64) s_tb[wave][e >> 3][e & 7] = 0.0;
-    const int t_lo = A.itype[a0], t_hi = A.itype[a1 - 1];
-    for (int ti = t_lo; ti <= t_hi; ++ti)
-        for (int tj = 0; tj < A.ntypes; ++tj) {
+    for (int tj = 0; tj < A.ntypes; ++tj)
+        for (int ti = 0; ti < (A.type_one_side ? 1 : A.ntypes); ++ti) {
             const int net = A.type_one_side ? tj : ti * A.ntypes + tj;
+            int lo, hi;
+            if (!net_range(K, ti, tj, wave, lo, hi)) continue;   // (uniform over the block)
             __syncthreads();
             stage_net<P>(A, net, s_vec, s_w2, s_w3);
             __syncthreads();
-            ChunkWalk<> w;
-            w.i = 0;
-            w.c0 = 0;
-            w.ac = 0;
-            w.have = w.template find_atom<true>(A, nullptr, a0, a1, wave, NW, APW, ti, tj, true);
-            w.template fetch<true>(A, tj, c16);
+            if (lo >= hi) continue;
+            TreWalk w;
+            w.start(K, tj, c16, lo, hi);
+            int atom = -1;   // whose adjoints s_tb holds
             // sums over the wave's pairs of this net: w_hat's gradient of every layer, and W1's and b1's
             double h3[28], h2[NU2], h1[NU1], gw1[NU1], gb1[NU1];
 #pragma unroll
@@ -282,37 +333,24 @@ __global__ void __launch_bounds__(64 * NW, 1) k_tre_adj(TreArgs K)
             for (int u = 0; u < NU2; ++u) h2[u] = 0.0;
 #pragma unroll
             for (int u = 0; u < NU1; ++u) h1[u] = gw1[u] = gb1[u] = 0.0;
-            const bool any = w.have;
-            while (w.have) {
-                const double x = w.px, y = w.py, z = w.pz;
-                const int ca = w.a, cc0 = w.c0, cnp = w.np;
-                double vj[3], vi[3];
-                for (int k = 0; k < 3; ++k) {
-                    vj[k] = K.vdir[3 * (size_t)max(w.pj, 0) + k];
-                    vi[k] = K.vdir[3 * (size_t)w.ac + k];
-                }
-                if (cc0 == 0) {
-                    wave_sync();
-                    for (int e = lane; e < E2 * 4; e += 64) {
-                        int gf = 0, uf = 0;
-                        emb_reg3(e >> 2, gf, uf);
-                        const int row = 16 * (uf >> 2) + P::orow(gf, uf & 3);
-                        s_tb[wave][row][e & 3] = K.Tb[(size_t)ca * E2 * 4 + e] * A.inv_nc;
-                        s_tb[wave][row][4 + (e & 3)] = K.Tdb[(size_t)ca * E2 * 4 + e] * A.inv_nc;
-                    }
+            while (w.c < w.end) {
+                wave_sync();
+                if (w.m.x != atom) {
+                    atom = w.m.x;
+                    const double2* tb = reinterpret_cast<const double2*>(K.Tb + (size_t)atom * TRE_TB);
+                    double2 v[TRE_TB / 128];
+#pragma unroll
+                    for (int q = 0; q < TRE_TB / 128; ++q) v[q] = tb[lane + 64 * q];
+#pragma unroll
+                    for (int q = 0; q < TRE_TB / 128; ++q) reinterpret_cast<double2*>(&s_tb[wave][0][0])[lane + 64 * q] = v[q];
                     wave_sync();
                 }
-                w.c0 += 16;
-                if (w.c0 >= w.np) {
-                    ++w.i;
-                    w.c0 = 0;
-                    w.have = w.template find_atom<true>(A, nullptr, a0, a1, wave, NW, APW, ti, tj, true);
-                }
-                w.template fetch<true>(A, tj, c16);
-                double* dump = K.dump + (size_t)(K.coff[(size_t)tj * (A.natoms + 1) + ca] + (cc0 >> 4)) * TRE_CHUNK + lane;
+                int lo = lane;
+                asm volatile("" : "+v"(lo));   // (or the 17 store offsets are kept in registers over the loop)
+                double* dump = K.dump + (size_t)w.c * TRE_CHUNK + lo;
                 auto put = [&](int at, int u, double v) { dump[(at + u) * 64] = v; };
                 Pair pr;
-                pair_env(A, K.coef, inv_w, x, y, z, vj, vi, cc0 + c16 < cnp, pr);
+                pair_env(A, K.coef, inv_w, w.x, w.y, w.z, w.vj, w.vi, w.m.z + c16 < w.m.w, pr);
                 const double s = pr.s, sd = pr.sd;
                 // forward: the layers' tanh outputs and unit tangents
                 double t1[8], z1[8], z1d[8];
@@ -366,8 +404,7 @@ __global__ void __launch_bounds__(64 * NW, 1) k_tre_adj(TreArgs K)
                     }
                 };
                 // layer 3: adjoints of the output, of the pre-activation, and the products with W3
-                double yb2[16], ydb2[16];   // adjoints of layer 2's output: the skip first
-                d4 xb[4], xdb[4];
+                d4 xb[4], xdb[4];   // adjoints of layer 2's output; the skip is added to the accumulators
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
                     zero4(xb[t]);
@@ -392,8 +429,8 @@ __global__ void __launch_bounds__(64 * NW, 1) k_tre_adj(TreArgs K)
                         h3[u] += t3 * yb + gzy;
                         put(D_Z3, u, zb[r]);
                         put(D_ZD3, u, zdb[r]);
-                        yb2[u >> 1] = (u & 1) ? yb2[u >> 1] + yb : yb;
-                        ydb2[u >> 1] = (u & 1) ? ydb2[u >> 1] + ydb : ydb;
+                        xb[u >> 3][(u >> 1) & 3] += yb;
+                        xdb[u >> 3][(u >> 1) & 3] += ydb;
                     }
                     frag fb, fdb;
                     fb.v = zb;
@@ -410,11 +447,12 @@ __global__ void __launch_bounds__(64 * NW, 1) k_tre_adj(TreArgs K)
 #pragma unroll
                 for (int tm = 0; tm < 7; ++tm) {
                     if (tm + 1 < 7) mm3(tm + 1, a3[(tm + 1) & 1], a3d[(tm + 1) & 1]);
+                    if (tm == 4) w.fetch(K, tj, c16);
                     epi3(tm, a3[tm & 1], a3d[tm & 1]);
                     __builtin_amdgcn_sched_barrier(0);
                 }
+                w.fetch_v(K);
                 // layer 2
-                double yb1[8], ydb1[8];
                 d4 xb1[2], xdb1[2];
 #pragma unroll
                 for (int t = 0; t < 2; ++t) {
@@ -430,13 +468,13 @@ __global__ void __launch_bounds__(64 * NW, 1) k_tre_adj(TreArgs K)
                         zb[r] = zdb[r] = 0.0;
                         if (u < NU2) {
                             const int n = 16 * c + P::orow(g, r);
-                            const double yb = yb2[u] + xb[c][r], ydb = ydb2[u] + xdb[c][r];
+                            const double yb = xb[c][r], ydb = xdb[c][r];
                             const double gd = 1 - t2[u] * t2[u], wh = s_vec[EV_WH2 + n], gzy = gd * (sd * zd2[c][r]) * ydb;
                             zb[r] = wh * (gd * yb - 2 * t2[u] * gzy);
                             zdb[r] = wh * gd * ydb;
                             h2[u] += t2[u] * yb + gzy;
-                            yb1[u >> 1] = (u & 1) ? yb1[u >> 1] + yb : yb;
-                            ydb1[u >> 1] = (u & 1) ? ydb1[u >> 1] + ydb : ydb;
+                            xb1[u >> 3][(u >> 1) & 3] += yb;
+                            xdb1[u >> 3][(u >> 1) & 3] += ydb;
                         }
                         put(D_Z2, u, zb[r]);
                         put(D_ZD2, u, zdb[r]);
@@ -455,16 +493,18 @@ __global__ void __launch_bounds__(64 * NW, 1) k_tre_adj(TreArgs K)
 #pragma unroll
                 for (int u = 0; u < NU1; ++u) {
                     const int k = P::kidx(u / 4, g, u % 4);
-                    const double yb = yb1[u] + xb1[u >> 2][u & 3], ydb = ydb1[u] + xdb1[u >> 2][u & 3];
+                    const double yb = xb1[u >> 2][u & 3], ydb = xdb1[u >> 2][u & 3];
                     const double gd = 1 - t1[u] * t1[u], wh = s_vec[EV_WH1 + k], gzy = gd * (sd * s_vec[EV_W1 + k]) * ydb;
                     const double zb = wh * (gd * yb - 2 * t1[u] * gzy);
                     h1[u] += t1[u] * yb + gzy;
                     gb1[u] += zb;
                     gw1[u] += s * zb + sd * (wh * gd * ydb);
                 }
+                ++w.c;
+                w.take();
             }
             // sums over the 16 pair columns, then into the gradient (feature of register u in group g)
-            if (any) {
+            {
                 double* gr = K.grad + (size_t)net * G_NET;
                 auto add = [&](int off, int f, double v) {
                     for (int m = 1; m < 16; m <<= 1) v += __shfl_xor(v, m);
@@ -614,34 +654,40 @@ __global__ void __launch_bounds__(1024) k_tre_offsets(int n, int nt, const int* 
         }
 }
 
-}  // namespace
-
-// Blocks of four waves, an even share of the atoms per CU, at most eight atoms per wave.
-static int tre_apb(int64_t n, int64_t ncu)
+// The chunk map (atom, its caller index, first neighbour, number of neighbours in the block) and Td = 0.
+__global__ void __launch_bounds__(256) k_tre_map(TreArgs K)
 {
-    if (ncu <= 0) ncu = 256;
-    const int64_t rounds = std::max<int64_t>(1, (n + ncu * 8 * NW - 1) / (ncu * 8 * NW));
-    return (int)std::max<int64_t>(NW, (n + ncu * rounds - 1) / (ncu * rounds));
+    const int n = K.e.natoms, nt = K.e.ntypes;
+    for (int64_t k = blockIdx.x * 256 + threadIdx.x; k < (int64_t)n * E2 * 4; k += 256 * gridDim.x) {
+        K.Td[k] = 0.0;
+        if (k >= (int64_t)n * nt) continue;
+        const int tj = (int)(k / n), a = (int)(k % n);
+        const int np = K.e.nnei[(size_t)a * nt + tj], c = K.coff[tj * (int64_t)(n + 1) + a];
+        for (int q = 0; 16 * q < np; ++q) K.cmap[c + q] = int4{a, K.e.perm[a], 16 * q, np};
+    }
 }
+
+}  // namespace
 
 void tre_offsets(int n, int nt, const int* nnei, int* coff, hipStream_t s)
 {
     hipLaunchKernelGGL(k_tre_offsets, dim3(1), dim3(1024), 0, s, n, nt, nnei, coff);
 }
 
-void tre_tangent(const TreArgs& k0, hipStream_t s)
+// One block per CU, each with an even share of the chunks (of two or three nets at most where there are
+// many): four waves, one per SIMD.
+void tre_tangent(const TreArgs& k, hipStream_t s)
 {
-    TreArgs k = k0;
-    k.e.apb = tre_apb(k.e.natoms, k.e.ncu);
-    hipLaunchKernelGGL(k_tre_tan, dim3((k.e.natoms + k.e.apb - 1) / k.e.apb), dim3(64 * NW), 0, s, k);
+    const int blocks = k.e.ncu > 0 ? k.e.ncu : 256;
+    hipLaunchKernelGGL(k_tre_map, dim3(std::min<int64_t>(((int64_t)k.e.natoms * E2 * 4 + 255) / 256, 8 * blocks)), dim3(256), 0, s, k);
+    hipLaunchKernelGGL(k_tre_tan, dim3(blocks), dim3(64 * NW), 0, s, k);
 }
 
-void tre_gradient(const TreArgs& k0, hipStream_t s)
+void tre_gradient(const TreArgs& k, hipStream_t s)
 {
-    TreArgs k = k0;
-    k.e.apb = tre_apb(k.e.natoms, k.e.ncu);
-    hipLaunchKernelGGL(k_tre_adj, dim3((k.e.natoms + k.e.apb - 1) / k.e.apb), dim3(64 * NW), 0, s, k);
-    hipLaunchKernelGGL(k_tre_wgrad, dim3(k.e.ncu > 0 ? k.e.ncu : 256), dim3(512), 0, s, k);
+    const int blocks = k.e.ncu > 0 ? k.e.ncu : 256;
+    hipLaunchKernelGGL(k_tre_adj, dim3(blocks), dim3(64 * NW), 0, s, k);
+    hipLaunchKernelGGL(k_tre_wgrad, dim3(blocks), dim3(512), 0, s, k);
 }
 
 }  // namespace dpk

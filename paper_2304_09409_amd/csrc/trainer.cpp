@@ -76,10 +76,10 @@ struct dpk_trainer {
     IBuf map[4];
     DBuf theta, grad, mom1, mom2;
     // frame workspace
-    IBuf coff;
-    DBuf fl, q, vdir, part, coef, Td, Tb, Tdb, dump;
+    IBuf coff, cmap;
+    DBuf fl, q, vdir, part, coef, Td, Tb, dump;
     DBuf D, Dd, Db, Ddb, a[3], y[3], zd[3], yd[3], zb[3], zdb[3], yb, ydb;
-    TrCoef* pin = nullptr;        // pinned copy of coef
+    TrCoef* pin = nullptr;        // pinned copy of coef, and behind it the number of chunks
     ~dpk_trainer() {
         if (pin) hipHostFree(pin);
         if (geo) dpk_ctx_free(geo);
@@ -101,20 +101,24 @@ int frame(dpk_trainer* t, int64_t natoms, const double* coord, const int32_t* at
     }
     TrCoef* coef = (TrCoef*)t->coef.p;
     FrameNet f;
-    int rc = frame_network(t->geo, natoms, coord, atype, box, coef->ev, &f);
+    if (natoms > 0 && natoms <= (1LL << 30)) TRCHK(t->coff.ensure((size_t)(natoms + 1) * t->nt));
+    int* pin_chunks = (int*)(t->pin + 1);
+    int rc = frame_network(t->geo, natoms, coord, atype, box, coef->ev, t->coff.p, pin_chunks, &f);
     if (rc) return rc;
     hipStream_t s = f.stream;
     const int n = f.n, nt = t->nt;
-    // workspace
-    int64_t chunks = 0;   // at most: every type block full
-    for (int ty = 0; ty < nt; ++ty) chunks += (t->desc.sel[ty] + 15) / 16;
-    const size_t nz = n;
-    TRCHK(t->coff.ensure((nz + 1) * nt));
-    TRCHK(t->dump.ensure((size_t)chunks * nz * TRE_CHUNK));
+    // workspace (the chunks as found, not as many as sel would allow; an eighth more for the next frame)
+    const size_t nz = n, chunks = std::max(1, *pin_chunks);
+    TRCHK(t->cmap.ensure(4 * chunks));
+    if (chunks * TRE_CHUNK > t->dump.n && t->dump.ensure((chunks + chunks / 8) * TRE_CHUNK) != hipSuccess) {
+        hipGetLastError();
+        TRCHK(t->dump.ensure(chunks * TRE_CHUNK));
+    }
     for (DBuf* b : {&t->fl, &t->vdir}) TRCHK(b->ensure(3 * nz));
     TRCHK(t->q.ensure(nz));
     TRCHK(t->part.ensure(tr_loss_blocks(n)));
-    for (DBuf* b : {&t->Td, &t->Tb, &t->Tdb}) TRCHK(b->ensure(E2 * 4 * nz));
+    TRCHK(t->Td.ensure(E2 * 4 * nz));
+    TRCHK(t->Tb.ensure(TRE_TB * nz));
     for (DBuf* b : {&t->D, &t->Dd, &t->Db, &t->Ddb}) TRCHK(b->ensure((size_t)DD * nz));
     for (int l = 0; l < 3; ++l)
         for (DBuf* b : {&t->a[l], &t->y[l], &t->zd[l], &t->yd[l], &t->zb[l], &t->zdb[l]}) TRCHK(b->ensure((size_t)FW * nz));
@@ -149,11 +153,11 @@ int frame(dpk_trainer* t, int64_t natoms, const double* coord, const int32_t* at
     e.e = f.emb;
     e.toff = f.toff;
     e.coff = t->coff.p;
+    e.cmap = (int4*)t->cmap.p;
     e.vdir = t->vdir.p;
     e.coef = coef;
     e.Td = t->Td.p;
     e.Tb = t->Tb.p;
-    e.Tdb = t->Tdb.p;
     e.dump = t->dump.p;
     e.grad = t->grad.p;
     TrfArgs a;
@@ -171,7 +175,7 @@ int frame(dpk_trainer* t, int64_t natoms, const double* coord, const int32_t* at
     a.T = f.T;
     a.Td = t->Td.p;
     a.Tb = t->Tb.p;
-    a.Tdb = t->Tdb.p;
+    a.inv_nc = f.emb.inv_nc;
     a.coef = coef;
     a.D = t->D.p;
     a.Dd = t->Dd.p;
@@ -187,7 +191,6 @@ int frame(dpk_trainer* t, int64_t natoms, const double* coord, const int32_t* at
     }
     a.yb = t->yb.p;
     a.ydb = t->ydb.p;
-    tre_offsets(n, nt, f.nnei, t->coff.p, s);
     tre_tangent(e, s);
     trf_run(a, f.ncu, s);
     tre_gradient(e, s);
@@ -233,7 +236,7 @@ int dpk_trainer_create(const dpk_model* m, int device, dpk_trainer** out)
     }
     if (t->theta.ensure(np) != hipSuccess || t->grad.ensure(np) != hipSuccess || t->mom1.ensure(np) != hipSuccess ||
         t->mom2.ensure(np) != hipSuccess || t->coef.ensure(sizeof(TrCoef) / sizeof(double)) != hipSuccess ||
-        hipHostMalloc((void**)&t->pin, sizeof(TrCoef)) != hipSuccess) {
+        hipHostMalloc((void**)&t->pin, sizeof(TrCoef) + sizeof(int)) != hipSuccess) {
         hipGetLastError();
         delete t;
         return set_error(DPK_E_OOM, "hipMalloc of the trainer's parameter buffers failed");
