@@ -74,7 +74,7 @@ void tr_loss(const TrLossArgs& a, hipStream_t s);
 
 // Embedding nets. Chunks of 16 kept neighbours of one atom and neighbour type; coff [nt][n + 1] their
 // offsets (by neighbour type, then atom). dump: TRE_CHUNK doubles per chunk.
-constexpr int TRE_CHUNK = 136 * 64;
+constexpr int TRE_CHUNK = 130 * 64;
 // Adjoints of T and Td of an atom, over N_c: [layer-3 row position][T 4, Td 4], padding rows zero
 constexpr int TRE_TB = N3P * 8;
 constexpr int TRE_NET = 3 * E0 + E0 * E1 + 2 * E1 + E1 * E2 + 2 * E2;   // parameters of one embedding net

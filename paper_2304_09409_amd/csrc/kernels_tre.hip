@@ -34,13 +34,17 @@ namespace {
 typedef PF64 P;
 typedef EmbCfg<PF64> Cfg;
 typedef P::frag frag;
+typedef double d2 __attribute__((ext_vector_type(2)));
 constexpr int NW = 4;                          // waves per block, one per SIMD
 constexpr int NU1 = Cfg::NU1, NU2 = Cfg::NU2;  // registers in use of layers 1 and 2 (of 8 and 16)
 // Padding registers whose lane group 0 carries the constant 1 of the bias gradients
-constexpr int ONE1 = 7, ONE2 = 14;
-static_assert(ONE1 >= NU1 && ONE2 >= NU2, "padding registers");
+constexpr int ONE1 = NU1, ONE2 = NU2;
+static_assert(ONE1 < 8 && ONE2 < 16, "padding registers");
 // One chunk's operands: registers [u][64 lanes] of each quantity
-constexpr int D_Z3 = 0, D_ZD3 = 28, D_Y2 = 56, D_YD2 = 72, D_Z2 = 88, D_ZD2 = 104, D_Y1 = 120, D_YD1 = 128;
+// (padding registers are left out where the rows or columns they make are not read: a tile that runs over
+// into the next quantity fills such rows only)
+constexpr int D_Z3 = 0, D_ZD3 = 28, D_Z2 = 56, D_ZD2 = D_Z2 + NU2, D_Y2 = D_ZD2 + NU2, D_YD2 = D_Y2 + NU2 + 1,
+              D_Y1 = D_YD2 + NU2 + 1, D_YD1 = D_Y1 + 8;
 static_assert((D_YD1 + 8) * 64 == TRE_CHUNK, "operand block of a chunk");
 // Offsets inside one net's block of the parameter vector
 constexpr int G_W1 = 0, G_B1 = 25, G_H1 = 50, G_W2 = 75, G_B2 = G_W2 + E0 * E1, G_H2 = G_B2 + E1, G_W3 = G_H2 + E1,
@@ -348,7 +352,7 @@ __global__ void __launch_bounds__(64 * NW, 1) k_tre_adj(TreArgs K)
                 int lo = lane;
                 asm volatile("" : "+v"(lo));   // (or the 17 store offsets are kept in registers over the loop)
                 double* dump = K.dump + (size_t)w.c * TRE_CHUNK + lo;
-                auto put = [&](int at, int u, double v) { dump[(at + u) * 64] = v; };
+                auto put = [&](int at, int u, double v) { __builtin_nontemporal_store(v, &dump[(at + u) * 64]); };
                 Pair pr;
                 pair_env(A, K.coef, inv_w, w.x, w.y, w.z, w.vj, w.vi, w.m.z + c16 < w.m.w, pr);
                 const double s = pr.s, sd = pr.sd;
@@ -390,6 +394,7 @@ __global__ void __launch_bounds__(64 * NW, 1) k_tre_adj(TreArgs K)
                         zt[u] = wh * t2[u] + z1[u >> 1];
                         ztd[u] = wh * (1 - t2[u] * t2[u]) * zd2[u >> 2][u & 3] + z1d[u >> 1];
                     }
+                    if (u > ONE2) continue;
                     put(D_Y2, u, u == ONE2 ? (g == 0 ? 1.0 : 0.0) : zt[u]);
                     put(D_YD2, u, sd * ztd[u]);
                 }
@@ -476,6 +481,7 @@ __global__ void __launch_bounds__(64 * NW, 1) k_tre_adj(TreArgs K)
                             xb1[u >> 3][(u >> 1) & 3] += yb;
                             xdb1[u >> 3][(u >> 1) & 3] += ydb;
                         }
+                        if (u >= NU2) continue;
                         put(D_Z2, u, zb[r]);
                         put(D_ZD2, u, zdb[r]);
                     }
@@ -527,22 +533,25 @@ __global__ void __launch_bounds__(64 * NW, 1) k_tre_adj(TreArgs K)
 
 // Weight and bias gradients of layers 2 and 3. The chunks (grouped by net) are split evenly over the
 // blocks; of a block's eight waves, wave w takes the output tiles w % 4 and w % 4 + 4 of W3 and w % 4 of W2
-// for every second chunk; the two halves meet in LDS and the sums go to the gradient with atomics. An
-// operand tile is a register dump [4][64 lanes] of 16 features x 16 pairs: lane (i, g) of an MFMA takes
+// for half of each chunk's pairs; the two halves meet in LDS and the sums go to the gradient with atomics.
+// An operand tile is a register dump [4][64 lanes] of 16 features x 16 pairs: lane (i, g) of an MFMA takes
 // feature row i and the pairs 4g..4g+3, which are consecutive there (the pairs are the summation index,
-// in any order).
+// in any order). The chunks pass through two LDS buffers, each read from memory once, a chunk ahead:
+// with every wave loading its own tiles the block moved 176 KB per chunk and waited for them.
 __global__ void __launch_bounds__(512, 2) k_tre_wgrad(TreArgs K)
 {
     const EmbArgs& A = K.e;
-    __shared__ d4 s_red[4][10][64];
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), w = wave & 3, half = wave >> 2;
-    const int lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
+    constexpr int NLD = (TRE_CHUNK / 2 + 511) / 512;
+    __shared__ __attribute__((aligned(16))) double s_buf[2][TRE_CHUNK];
+    static_assert(sizeof(s_buf) >= sizeof(d4) * 4 * 10 * 64, "the halves' exchange lies over the buffers");
+    d4 (*s_red)[10][64] = reinterpret_cast<d4 (*)[10][64]>(&s_buf[0][0]);
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), w = wave & 3, half = wave >> 2;
+    const int lane = tid & 63, g = lane >> 4, c16 = lane & 15;
     const int nt = A.ntypes, n = A.natoms;
     const int64_t ld = n + 1;
     const int total = K.coff[(size_t)(nt - 1) * ld + n];
     const int b0 = (int)((int64_t)total * blockIdx.x / gridDim.x), b1 = (int)((int64_t)total * (blockIdx.x + 1) / gridDim.x);
-    const int off = 64 * (c16 >> 2) + 16 * (c16 & 3) + 4 * g;
-    auto tile = [&](const double* d, int u0) { return *reinterpret_cast<const d4*>(d + u0 * 64 + off); };
+    const int off = 64 * (c16 >> 2) + 16 * (c16 & 3) + 4 * g + 2 * half;
     for (int tj = 0; tj < nt; ++tj)
         for (int ti = 0; ti < (A.type_one_side ? 1 : nt); ++ti) {
             const int net = A.type_one_side ? tj : ti * nt + tj;
@@ -557,35 +566,45 @@ __global__ void __launch_bounds__(512, 2) k_tre_wgrad(TreArgs K)
                 for (int t = 0; t < 4; ++t) zero4(a3[q][t]);
             }
             const int m1 = min(w + 4, 6);   // (wave 3 has one output tile of W3: it repeats tile 6, not added)
+            d2 st[NLD];
+            auto load = [&](int c) {
+                const d2* src = reinterpret_cast<const d2*>(K.dump + (size_t)min(c, hi - 1) * TRE_CHUNK);
+#pragma unroll
+                for (int q = 0; q < NLD; ++q) st[q] = src[min(tid + 512 * q, TRE_CHUNK / 2 - 1)];
+                keep_loads();
+            };
+            auto store = [&](int b) {
+#pragma unroll
+                for (int q = 0; q < NLD; ++q) reinterpret_cast<d2*>(s_buf[b])[min(tid + 512 * q, TRE_CHUNK / 2 - 1)] = st[q];
+            };
+            load(lo);
+            __syncthreads();   // (the exchange of the previous net is done)
+            store(lo & 1);
+            load(lo + 1);
+            __syncthreads();
 #pragma unroll 1
-            for (int c = lo + half; c < hi; c += 2) {
-                const double* d = K.dump + (size_t)c * TRE_CHUNK;
-                d4 y[4], yd[4];
+            for (int c = lo; c < hi; ++c) {
+                const double* d = s_buf[c & 1];
+                auto tile = [&](int u0) { return *reinterpret_cast<const d2*>(d + u0 * 64 + off); };
+                auto mma = [&](const d2& x, const d2& y, d4& acc) {
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x.x, y.x, acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x.y, y.y, acc, 0, 0, 0);
+                };
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    y[t] = tile(d, D_Y2 + 4 * t);
-                    yd[t] = tile(d, D_YD2 + 4 * t);
-                }
-                const d4 z0 = tile(d, D_Z3 + 4 * w), zd0 = tile(d, D_ZD3 + 4 * w), z1 = tile(d, D_Z3 + 4 * m1), zd1 = tile(d, D_ZD3 + 4 * m1);
-                const d4 x0 = tile(d, D_Y1), x1 = tile(d, D_Y1 + 4), xd0 = tile(d, D_YD1), xd1 = tile(d, D_YD1 + 4);
-                const d4 q = tile(d, D_Z2 + 4 * w), qd = tile(d, D_ZD2 + 4 * w);
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
+                for (int p = 0; p < 2; ++p) {   // the values, then the tangents
+                    const d2 z0 = tile((p ? D_ZD3 : D_Z3) + 4 * w), z1 = tile((p ? D_ZD3 : D_Z3) + 4 * m1);
+                    const d2 q = tile((p ? D_ZD2 : D_Z2) + 4 * w);
 #pragma unroll
                     for (int t = 0; t < 4; ++t) {
-                        a3[0][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(y[t][v], z0[v], a3[0][t], 0, 0, 0);
-                        a3[1][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(y[t][v], z1[v], a3[1][t], 0, 0, 0);
+                        const d2 y = tile((p ? D_YD2 : D_Y2) + 4 * t);
+                        mma(y, z0, a3[0][t]);
+                        mma(y, z1, a3[1][t]);
+                        if (t < 2) mma(tile((p ? D_YD1 : D_Y1) + 4 * t), q, a2[t]);
                     }
-                    a2[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x0[v], q[v], a2[0], 0, 0, 0);
-                    a2[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(x1[v], q[v], a2[1], 0, 0, 0);
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        a3[0][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(yd[t][v], zd0[v], a3[0][t], 0, 0, 0);
-                        a3[1][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(yd[t][v], zd1[v], a3[1][t], 0, 0, 0);
-                    }
-                    a2[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(xd0[v], qd[v], a2[0], 0, 0, 0);
-                    a2[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(xd1[v], qd[v], a2[1], 0, 0, 0);
                 }
+                store((c + 1) & 1);
+                load(c + 2);
+                __syncthreads();
             }
             __syncthreads();
             if (half)
