@@ -369,7 +369,7 @@ size_t layout_ws(dpk_ctx* c, int64_t n, int64_t ncell, char* base)
     p = take(sizeof(int) * (MAXT + 1)); if (base) c->toff = (int*)p;
     p = take(sizeof(int) * MAXT * ((n + PREP_BLOCK - 1) / PREP_BLOCK)); if (base) c->bcount = (int*)p;
     p = take(sizeof(int) * MAXT * ((n + PREP_BLOCK - 1) / PREP_BLOCK)); if (base) c->boff = (int*)p;
-    p = take(sizeof(int) * STATS_WORDS); if (base) c->stats = (DevStats*)p;   // with the drop counters
+    p = take(STATS_BYTES); if (base) c->stats = (DevStats*)p;   // with the drop counters
     p = take(sizeof(double) * 3 * n); if (base) c->pos = (double*)p;
     p = take(sizeof(int) * n); if (base) c->cell_of = (int*)p;
     p = take(sizeof(int) * n); if (base) c->cell_tmp = (int*)p;
@@ -548,6 +548,7 @@ int setup_geometry(dpk_ctx* c, const double* box, const double* bbox, GeomParams
         }
         gp.cap = NL_CAP;   // clusters can be locally dense: largest buffer
     }
+    gp.set_runs();
     return DPK_OK;
 }
 
@@ -877,10 +878,10 @@ int frame_geometry(dpk_ctx* c, const BatchFrame& f, GeomParams& gp)
 }
 
 // Layout of a batch: per-frame geometry and offsets, total atoms and concatenated bins (ncell + 1
-// entries per frame), the largest stencil and candidate buffer. Outputs of frame f start at
+// entries per frame), the most stencil runs and largest candidate buffer. Outputs of frame f start at
 // fd[f].out_off doubles: E, virial[9], F[3n] and, if asked for, E_i[n].
 int batch_plan(dpk_ctx* c, int nf, const BatchFrame* fr, GeomParams* gps, FrameDesc* fd, int64_t* natoms,
-               int64_t* ncells, int* max_stencil, int* max_cap, int64_t* out_doubles)
+               int64_t* ncells, int* max_runs, int* max_cap, int64_t* out_doubles)
 {
     if (nf < 1 || nf > BATCH_MAX_FRAMES) return fail(DPK_E_INVALID_ARG, "batch of %d frames", nf);
     int64_t n = 0, nc = 0, out = 0;
@@ -902,12 +903,12 @@ int batch_plan(dpk_ctx* c, int nf, const BatchFrame* fr, GeomParams* gps, FrameD
         n += fr[f].natoms;
         nc += ncell + 1;
         out += 10 + (fr[f].want_ei ? 4 : 3) * fr[f].natoms;
-        ms = std::max(ms, (2 * gps[f].K[0] + 1) * (2 * gps[f].K[1] + 1) * (2 * gps[f].K[2] + 1));
+        ms = std::max(ms, gps[f].runs);
         mc = std::max(mc, gps[f].cap);
     }
     *natoms = n;
     *ncells = nc;
-    *max_stencil = ms;
+    *max_runs = ms;
     *max_cap = mc;
     *out_doubles = out;
     return DPK_OK;

@@ -126,6 +126,22 @@ struct GeomParams {
     int ntypes, nc;
     int sel[MAXT], off[MAXT];
     int cap;            // candidate buffer entries per atom (256, 512 or NL_CAP)
+    // Runs of the stencil: in a row of bins along the first axis (whose bins are consecutive in memory)
+    // the bins of one periodic image are one range of candidates, at most row_runs of them per row.
+    // Set by set_runs from nb and K, with what replaces the divisions of the kernels: 1 / nb of the first
+    // two axes, and 2^16 / row_runs and 2^16 / (2 K[1] + 1) rounded up (exact for run indices below 343).
+    int row_runs, runs;
+    int m_row, m_w1;
+    double rnb[2];
+    void set_runs()
+    {
+        const int w1 = 2 * K[1] + 1;
+        row_runs = periodic ? (2 * K[0] - 1) / nb[0] + 2 : 1;
+        runs = row_runs * w1 * (2 * K[2] + 1);
+        m_row = (65536 + row_runs - 1) / row_runs;
+        m_w1 = (65536 + w1 - 1) / w1;
+        for (int k = 0; k < 2; ++k) rnb[k] = 1.0 / nb[k];
+    }
 };
 
 // Device-side error / statistics block of one frame.
@@ -138,15 +154,23 @@ struct DevStats {
     int order_local;    // consecutive internal atoms that share a bin (tabulated backward's order)
 };
 
-// Neighbours dropped by sel are counted per atom into NL_DROP_SLOTS counters that follow the
-// statistics block in memory (atom a adds to counter a mod NL_DROP_SLOTS: one shared counter
-// serialised every atom's atomic), cleared with the block at the start of a frame and added into
-// nbr_dropped by the frame's final reduction.
+// Neighbours dropped by sel are counted per atom into NL_DROP_SLOTS counters (atom a adds to counter a mod
+// NL_DROP_SLOTS) that follow the statistics block in memory, cleared with the block at the start of a frame
+// and added into nbr_dropped by the frame's final reduction. They start on a cache line of their own: every
+// atom reads max_cand, and on a shared line that read waited for the adds of all atoms before it (32,000
+// fcc atoms that all drop neighbours: 313 us for the neighbour list against 225).
 constexpr int NL_DROP_SLOTS = 256;
-constexpr int STATS_WORDS = (int)((sizeof(DevStats) + sizeof(unsigned long long) * NL_DROP_SLOTS) / 4);
+constexpr size_t STATS_HEAD = (sizeof(DevStats) + 127) / 128 * 128;
+constexpr size_t STATS_BYTES = STATS_HEAD + sizeof(unsigned long long) * NL_DROP_SLOTS;
 __host__ __device__ inline unsigned long long* drop_slots(DevStats* st)
 {
-    return reinterpret_cast<unsigned long long*>(st + 1);
+    return reinterpret_cast<unsigned long long*>(reinterpret_cast<char*>(st) + STATS_HEAD);
+}
+// All cleared by one block.
+__device__ inline void clear_stats(DevStats* st, int tid, int nthreads)
+{
+    for (int w = tid; w < (int)(sizeof(DevStats) / 4); w += nthreads) reinterpret_cast<int*>(st)[w] = 0;
+    for (int k = tid; k < NL_DROP_SLOTS; k += nthreads) drop_slots(st)[k] = 0;
 }
 
 // One frame of a batch evaluated in shared launches (serving).

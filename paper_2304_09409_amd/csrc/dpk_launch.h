@@ -34,7 +34,7 @@ bool launch_prep_small(int n, const double* coord, const int* atype, int ntypes,
 void launch_nlist(int n, const double* pos, const int* perm, const int* inv_perm, const int* cell_of,
                   const int* cell_start, const double4* cand, const GeomParams& gp, int* nl_j, double* nl_r,
                   int* nnei, DevStats* st, hipStream_t s, const GeomParams* gps = nullptr,
-                  const FrameDesc* fd = nullptr, const int* frame_of = nullptr, int max_stencil = 0, int max_cap = 0);
+                  const FrameDesc* fd = nullptr, const int* frame_of = nullptr, int max_runs = 0, int max_cap = 0);
 // Batched frames (each at most prep_small_max_atoms() atoms and prep_small_max_cells() bins).
 void launch_batch_prep(int nframes, int ntypes, const double* coord, const int* atype, const GeomParams* gps,
                        FrameDesc* fd, int* tcount, int* toff, int* perm, int* inv_perm, int* itype, int* frame_of,

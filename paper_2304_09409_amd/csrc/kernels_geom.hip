@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "dpk_internal.h"
 #include "dpk_launch.h"
@@ -142,7 +143,7 @@ __device__ __forceinline__ void prep_frame(int f, int n, int nlocal, int atom_of
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     if (!BATCH)
-        for (int w = tid; w < STATS_WORDS; w += PS_THREADS) reinterpret_cast<int*>(st)[w] = 0;
+        clear_stats(st, tid, PS_THREADS);
     for (int c = tid; c < ncell; c += PS_THREADS) s_cnt[c] = 0;
     if (BATCH && tid < ntypes) s_base[tid] = type_base[tid];
     __syncthreads();   // the statistics block is zero before anything raises a flag in it
@@ -352,7 +353,7 @@ __global__ void __launch_bounds__(1024) k_prep_scan(int nblocks, int ntypes, con
     __shared__ int part[1024];
     __shared__ int carry;
     const int tid = threadIdx.x;
-    for (int w = tid; w < STATS_WORDS; w += (int)blockDim.x) reinterpret_cast<int*>(st)[w] = 0;
+    clear_stats(st, tid, (int)blockDim.x);
     // types: block offsets within each type (type t's atoms follow those of types < t)
     int acc = 0;
     for (int t = 0; t < ntypes; ++t) {
@@ -463,7 +464,7 @@ __global__ void __launch_bounds__(256) k_batch_count(const int* atype, int ntype
 // batch, frames in order within a type); zeroes the statistics block of the batch.
 __global__ void k_batch_scan(int nframes, int ntypes, FrameDesc* fd, int* tcount, int* toff, DevStats* st)
 {
-    for (int w = threadIdx.x; w < STATS_WORDS; w += (int)blockDim.x) reinterpret_cast<int*>(st)[w] = 0;
+    clear_stats(st, threadIdx.x, (int)blockDim.x);
     __syncthreads();
     if (threadIdx.x != 0) return;
     int acc = 0, bad = 0;
@@ -500,16 +501,22 @@ __global__ void __launch_bounds__(PS_THREADS) k_prep_batch(const double* coord, 
 // Candidate records are stored in bin order (by the preparation): position and a tag holding the
 // internal index, the caller index and the type (30 + 30 + 4 bits), so one 32-B load gives
 // everything the candidate test and the output need.
-// The wave first loads the ranges of all stencil bins at once (one lane per bin) and scans their
-// sizes; it then sweeps the flat candidate range, several candidates per lane in flight (each
-// lane finds its candidate's bin by binary search in the scanned offsets).
+// The wave first loads the candidate ranges of the stencil's runs at once (one lane per run of bins along
+// the first axis) and scans their sizes; it then sweeps the flat candidate range, several candidates per
+// lane in flight.
 // Candidates within r_c are compacted into LDS as 128-bit keys that compare like
 // (type, r^2, caller index j, image n0, n1, n2):
-//   hi = type << 59 | bits(r^2) >> 5
-//   lo = (bits(r^2) & 31) << 59 | j << 21 | code(n)
-// (r^2 is a non-negative double, whose bit pattern orders like its value). A bitonic sort in LDS
-// orders them; the first sel[t] of each type fill that type's block of slots, the rest are
-// counted as dropped; unfilled slots get index -1.
+//   hi = type << 59 | bits(r^2) - bits(r_c^2 2^-128)
+//   lo = j << 30 | code(n) << 9 | run
+// (r^2 is a non-negative double, whose bit pattern orders like its value). They are ranked; the first
+// sel[t] of each type fill that type's block of slots, the rest are counted as dropped; unfilled slots
+// get index -1.
+// Bound: VALU issue (about 1,450 instructions per atom of 90 neighbours, 90 % busy at 110,592 atoms); at a
+// few waves per SIMD the chain of loads (ranges, candidates, the output's second look at them). One run for
+// the three bins of a row instead of a range per bin, found by walking on instead of a binary search, type
+// counts from the keys instead of per candidate, ranks on 32-bit words and the output written from
+// registers: 12,288 water atoms 78 -> 44 us, 110,592 470 -> 290, 192 (latency alone) 21 -> 18; 32,000 fcc
+// atoms, 182 neighbours, 320 -> 227 with the counters off the statistics' cache line.
 
 __device__ __forceinline__ bool key_less(unsigned long long ah, unsigned long long al,
                                          unsigned long long bh, unsigned long long bl)
@@ -530,6 +537,41 @@ __device__ __forceinline__ void image_shift(const GeomParams& gp, int n0, int n1
 constexpr int NL_UNROLL = 4;
 constexpr int RANK_MAX = 256;   // hits per atom up to which the neighbour list ranks instead of sorting
 
+// Sort key of a neighbour, 128 bits: (type, r^2, caller index, image code), and its run of the stencil. r^2 < r_c^2 as the distance of
+// its bit pattern from that of r_c^2 2^-128 (smaller ones all at 0), 59 bits: the high 32 bits of the key
+// then hold the type and 20 bits below the exponent, enough to tell almost any two neighbours apart.
+__device__ __forceinline__ unsigned long long nl_key_base(double rc2)
+{
+    const unsigned long long b = (unsigned long long)__double_as_longlong(rc2);
+    return b > (1ull << 59) ? b - (1ull << 59) : 0;
+}
+
+constexpr int NL_RUN_BITS = 9;
+static_assert(NL_STENCIL <= 1 << NL_RUN_BITS, "run index in the key");
+
+// One candidate per lane into the hits: those within r_c are compacted behind the count (wave-uniform) of
+// hits so far. Hits past the CAP stored ones are only counted, by type: lane t holds those of type t.
+template <int CAP>
+__device__ __forceinline__ void nl_push(bool pass, int t, double r2, int j, int code, int run, int src, unsigned long long kbase,
+                                        int ntypes, int lane, int& count, int& over, unsigned long long* khi,
+                                        unsigned long long* klo, int* kq)
+{
+    const unsigned long long m = __ballot(pass);
+    const int idx = count + __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+    if (pass && idx < CAP) {
+        const unsigned long long rb = (unsigned long long)__double_as_longlong(r2);
+        khi[idx] = ((unsigned long long)t << 59) | (rb > kbase ? rb - kbase : 0ull);
+        klo[idx] = ((unsigned long long)j << 30) | (unsigned long long)((code << NL_RUN_BITS) | run);
+        kq[idx] = src;
+    }
+    count += __popcll(m);
+    if (count > CAP)
+        for (int q = 0; q < ntypes; ++q) {
+            const int c = __popcll(__ballot(pass && idx >= CAP && t == q));
+            if (lane == q) over += c;
+        }
+}
+
 // Ordering of LDS traffic between the lanes of the (single-wave) workgroup.
 __device__ __forceinline__ void wave_barrier()
 {
@@ -538,18 +580,17 @@ __device__ __forceinline__ void wave_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
-// Rank sort of count <= RANK_MAX keys in LDS, EA = ceil(count / 64) of them per lane (key lane +
-// 64 e): a key's position is the number of smaller keys, counted against every stored key read once
-// from LDS (one broadcast per key, no exchange chain). The high words decide unless two are equal
-// (equal type and r^2 to 2^-47, i.e. in practice equal distances): equal ranks then collide in a
-// slot check and the ranks are recounted on the full 128-bit keys, which are unique. The keys end
-// sorted in LDS.
+// Ranks of count <= RANK_MAX keys in LDS, EA = ceil(count / 64) of them per lane (key lane + 64 e): a
+// key's position is the number of smaller keys, counted against every stored key read once from LDS (a
+// broadcast of two keys per read, no exchange chain). The high 32 bits decide unless two are equal: equal
+// ranks then collide in a slot check and the ranks are recounted on the full 128-bit keys, which are
+// unique.
 template <int EA>
 __device__ __forceinline__ void rank_keys(int count, int lane, unsigned long long* khi, unsigned long long* klo,
-                                          int* kq)
+                                          int* kq, unsigned long long (&kh)[EA], unsigned long long (&kl)[EA],
+                                          int (&kx)[EA], int (&rk)[EA])
 {
-    unsigned long long kh[EA], kl[EA];
-    int kx[EA], rk[EA];
+    unsigned k32[EA];
 #pragma unroll
     for (int e = 0; e < EA; ++e) {
         const int i = lane + 64 * e;
@@ -557,14 +598,21 @@ __device__ __forceinline__ void rank_keys(int count, int lane, unsigned long lon
         kh[e] = have ? khi[i] : ~0ull;
         kl[e] = have ? klo[i] : ~0ull;
         kx[e] = have ? kq[i] : 0;
+        k32[e] = (unsigned)(kh[e] >> 32);
         rk[e] = 0;
     }
-    for (int q = 0; q < count; ++q) {
-        const unsigned long long h = khi[q];
-#pragma unroll
-        for (int e = 0; e < EA; ++e) rk[e] += h < kh[e] ? 1 : 0;
-    }
+    if (lane < ((4 - count) & 3)) khi[count + lane] = ~0ull;   // whole groups of four (RANK_MAX is one)
     wave_barrier();
+    const ulonglong2* k2 = reinterpret_cast<const ulonglong2*>(khi);
+#pragma unroll 2
+    for (int q = 0; q < count; q += 4) {
+        const ulonglong2 h0 = k2[q >> 1], h1 = k2[(q >> 1) + 1];
+        const unsigned h[4] = {(unsigned)(h0.x >> 32), (unsigned)(h0.y >> 32), (unsigned)(h1.x >> 32), (unsigned)(h1.y >> 32)};
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int e = 0; e < EA; ++e) rk[e] += h[c] < k32[e] ? 1 : 0;
+    }
 #pragma unroll
     for (int e = 0; e < EA; ++e)
         if (lane + 64 * e < count) kq[rk[e]] = lane + 64 * e;
@@ -582,15 +630,6 @@ __device__ __forceinline__ void rank_keys(int count, int lane, unsigned long lon
             for (int e = 0; e < EA; ++e) rk[e] += key_less(h, l, kh[e], kl[e]) ? 1 : 0;
         }
     }
-    wave_barrier();
-#pragma unroll
-    for (int e = 0; e < EA; ++e)
-        if (lane + 64 * e < count) {
-            khi[rk[e]] = kh[e];
-            klo[rk[e]] = kl[e];
-            kq[rk[e]] = kx[e];
-        }
-    wave_barrier();
 }
 
 // Bitonic sort in LDS of count keys (padded to a power of two with keys that order last): the path
@@ -623,13 +662,13 @@ __device__ void bitonic_keys_lds(int count, int lane, unsigned long long* khi, u
         }
 }
 
-// The selection of one atom's list from its count hits (keys in LDS: type, r^2, caller index,
-// image code; kq the candidate each key came from; tcount the hits per type, which may exceed the
-// CAP stored keys): keys sorted in LDS, the first sel[t] of each type block written to row a of
-// the list (fetch(kq, code, r, j) gives the candidate's r_ij and caller index), padding -1, the
-// kept counts, and the neighbours dropped by sel.
+// The selection of one atom's list from its count hits (keys in LDS; kq the candidate each key came from;
+// over: this lane's count of hits of type `lane` past the CAP stored ones): the first sel[t] of each type
+// block in the order of the keys written to row a of the list (fetch(kq, run, r, j) gives the candidate's
+// r_ij and caller index), padding -1, the kept counts, and the neighbours dropped by sel. What belongs to
+// a type is held by the lane of its number.
 template <int CAP, class Fetch>
-__device__ __forceinline__ void nlist_select(int a, int lane, int count, int* tcount, const GeomParams& gp,
+__device__ __forceinline__ void nlist_select(int a, int lane, int count, int over, const GeomParams& gp,
                                              unsigned long long* khi, unsigned long long* klo, int* kq, int* nl_j,
                                              double* nl_r, int* nnei, DevStats* st, Fetch&& fetch)
 {
@@ -638,75 +677,112 @@ __device__ __forceinline__ void nlist_select(int a, int lane, int count, int* tc
         atomicMax(&st->max_cand, count);
         if (count > CAP) atomicExch(&st->err_overflow, 1);
     }
-    const bool overflow = count > CAP;   // wave-uniform; the frame is flagged and its list incomplete
-    if (overflow) count = CAP;
-    __syncthreads();
-    // the keys are put in order in LDS
-    static_assert(RANK_MAX <= 256, "rank sort dispatch covers at most four keys per lane");
-    if (count <= RANK_MAX) {
-        const int ER = (count + 63) >> 6;
-        if (ER <= 1) rank_keys<1>(count, lane, khi, klo, kq);
-        else if (ER == 2) rank_keys<2>(count, lane, khi, klo, kq);
-        else if (ER == 3) rank_keys<3>(count, lane, khi, klo, kq);
-        else rank_keys<4>(count, lane, khi, klo, kq);
-    } else {
-        bitonic_keys_lds(count, lane, khi, klo, kq);
-    }
-    // per-type counts of the sorted keys: every hit, unless the buffer overflowed; then only the
-    // stored hits count, so that each type block starts where its keys do and every slot the
-    // list claims is written (the overflowed frame is reported and not used)
-    int tsorted[MAXT];
-    for (int t = 0; t < gp.ntypes; ++t) tsorted[t] = tcount[t];
-    if (overflow) {
-        for (int t = 0; t < gp.ntypes; ++t) {
-            int c = 0;
-            for (int q0 = 0; q0 < count; q0 += 64) {
-                const int q = q0 + lane;
-                c += __popcll(__ballot(q < count && (int)(khi[q] >> 59) == t));
+    // An overflowed frame is flagged and its list incomplete: the type blocks hold the stored hits, so that
+    // each starts where its keys do and every slot the list claims is written.
+    count = min(count, CAP);
+    const int nt = gp.ntypes;
+    const int sel = lane < nt ? gp.sel[lane] : 0, off = lane < nt ? gp.off[lane] : 0;
+    int have = 0, start = 0;   // stored hits of the lane's type, and of the types before it
+    wave_barrier();
+    const size_t row = (size_t)a * gp.nc;
+    auto counted = [&](auto&& stored) {   // stored(t): stored hits of type t (wave-uniform)
+        int acc = 0;
+        for (int t = 0; t < nt; ++t) {
+            const int c = stored(t);
+            if (lane == t) {
+                have = c;
+                start = acc;
             }
-            tsorted[t] = c;
+            acc += c;
         }
-    }
-    int tstart[MAXT], kept[MAXT];
-    int acc = 0, drops = 0;
-    for (int t = 0; t < gp.ntypes; ++t) {
-        tstart[t] = acc;
-        acc += tsorted[t];
-        kept[t] = tsorted[t] < gp.sel[t] ? tsorted[t] : gp.sel[t];
-        drops += tcount[t] - kept[t];
-    }
-    const size_t rowj = (size_t)a * gp.nc;
-    for (int q = lane; q < count; q += 64) {
-        const unsigned long long kh = khi[q], kl = klo[q];
-        const int t = (int)(kh >> 59);
-        const int rank = q - tstart[t];
-        if (rank < gp.sel[t]) {
+    };
+    // slot of the hit at position q of the sorted hits (every lane takes part in the shuffles: one under the
+    // condition would read 0 from a lane that does not meet it)
+    auto place = [&](int q, int t) {
+        const int st_t = __shfl(start, t), sel_t = __shfl(sel, t), off_t = __shfl(off, t), rank = q - st_t;
+        return rank < sel_t ? off_t + rank : -1;
+    };
+    auto write = [&](int slot, const double* r, int j) {
+        nl_j[row + slot] = j;
+        for (int c = 0; c < 3; ++c) nl_r[3 * (row + slot) + c] = r[c];
+    };
+    auto ranked = [&](auto ea) {
+        constexpr int EA = decltype(ea)::value;
+        unsigned long long kh[EA], kl[EA];
+        int kx[EA], rk[EA], slot[EA], j[EA];
+        double r[EA][3];
+        rank_keys<EA>(count, lane, khi, klo, kq, kh, kl, kx, rk);
+        counted([&](int t) {
+            int c = 0;
+#pragma unroll
+            for (int e = 0; e < EA; ++e) c += __popcll(__ballot((int)(kh[e] >> 59) == t));
+            return c;
+        });
+#pragma unroll
+        for (int e = 0; e < EA; ++e) {
+            const bool in = lane + 64 * e < count;
+            slot[e] = place(rk[e], in ? (int)(kh[e] >> 59) : 0);
+            if (!in) slot[e] = -1;
+            fetch(kx[e], in ? (int)kl[e] & ((1 << NL_RUN_BITS) - 1) : 0, r[e], j[e]);   // (no hit: candidate 0)
+        }
+#pragma unroll
+        for (int e = 0; e < EA; ++e)
+            if (slot[e] >= 0) write(slot[e], r[e], j[e]);
+    };
+    static_assert(RANK_MAX <= 256, "rank sort dispatch covers at most four keys per lane");
+    if (count <= 64) ranked(std::integral_constant<int, 1>());
+    else if (count <= 128) ranked(std::integral_constant<int, 2>());
+    else if (count <= 192) ranked(std::integral_constant<int, 3>());
+    else if (count <= RANK_MAX) ranked(std::integral_constant<int, 4>());
+    else {
+        bitonic_keys_lds(count, lane, khi, klo, kq);
+        counted([&](int t) {
+            int c = 0;
+            for (int q0 = 0; q0 < count; q0 += 64) c += __popcll(__ballot(q0 + lane < count && (int)(khi[q0 + lane] >> 59) == t));
+            return c;
+        });
+        for (int q0 = 0; q0 < count; q0 += 64) {
+            const int q = min(q0 + lane, count - 1);
+            const int slot = place(q, (int)(khi[q] >> 59));
             double r[3];
             int j;
-            fetch(kq[q], (int)(kl & ((1ull << 21) - 1)), r, j);
-            const size_t slot = rowj + gp.off[t] + rank;
-            nl_j[slot] = j;
-            nl_r[3 * slot + 0] = r[0];
-            nl_r[3 * slot + 1] = r[1];
-            nl_r[3 * slot + 2] = r[2];
+            fetch(kq[q], (int)klo[q] & ((1 << NL_RUN_BITS) - 1), r, j);
+            if (slot >= 0 && q0 + lane < count) write(slot, r, j);
         }
     }
-    for (int s2 = lane; s2 < gp.nc; s2 += 64) {
-        int t = 0;
-        while (t + 1 < gp.ntypes && s2 >= gp.off[t + 1]) ++t;
-        if (s2 - gp.off[t] >= kept[t]) {
-            nl_j[rowj + s2] = -1;
-            for (int c = 0; c < 3; ++c) nl_r[3 * (rowj + s2) + c] = 0.0;
-        }
+    const int kept = min(have, sel);
+    const double zero[3] = {0.0, 0.0, 0.0};
+    for (int t = 0; t < nt; ++t) {
+        const int k = __shfl(kept, t), e = __shfl(sel, t), o = __shfl(off, t);
+        for (int s2 = k + lane; s2 < e; s2 += 64) write(o + s2, zero, -1);
     }
-    if (lane < gp.ntypes) nnei[(size_t)a * gp.ntypes + lane] = kept[lane];
-    if (lane == 0 && drops) atomicAdd(drop_slots(st) + (a & (NL_DROP_SLOTS - 1)), (unsigned long long)drops);
+    if (lane < nt) nnei[(size_t)a * nt + lane] = kept;
+    const int dropped = have + over - kept;
+    if (__ballot(dropped > 0)) {
+        int drops = dropped;
+        for (int o = 32; o > 0; o >>= 1) drops += __shfl_xor(drops, o);
+        if (lane == 0) atomicAdd(&drop_slots(st)[a & (NL_DROP_SLOTS - 1)], (unsigned long long)drops);
+    }
+}
+
+struct NlRun {
+    double sh[3];   // image shift
+    int off;        // candidate index of flat position q: q + off
+    int code;       // image code
+};
+// Periodic image of bin index t on an axis of nb bins: floor division; at least K bins leave t within one
+// box length of the cell, so the image is -1, 0 or 1.
+__device__ __forceinline__ int image_of(int t, int nb, int K)
+{
+    if (nb >= K) return t < 0 ? -1 : (t >= nb ? 1 : 0);
+    return t >= 0 ? t / nb : -((nb - 1 - t) / nb);
 }
 
 // BATCH: atom a belongs to frame frame_of[a]; its geometry is gps[frame] and its bins start at
-// fd[frame].cell_off of the concatenated cell_start (candidate records hold batch-wide indices).
+// fd[frame].cell_off of the concatenated cell_start (candidate records hold batch-wide indices). Six waves
+// per SIMD: two spilled registers against 83 in use and five waves, 5 to 8 % faster.
 template <int CAP, bool BATCH>
-__global__ void __launch_bounds__(64) k_nlist(int n, const double* pos, const int* perm, const int* inv_perm,
+__global__ void __launch_bounds__(64, 6) k_nlist(int n, const double* pos, const int* perm, const int* inv_perm,
                                               const int* cell_of, const int* cell_start0, const double4* cand,
                                               GeomParams gp0, const GeomParams* gps, const FrameDesc* fd,
                                               const int* frame_of, int* nl_j, double* nl_r, int* nnei, DevStats* st)
@@ -714,156 +790,104 @@ __global__ void __launch_bounds__(64) k_nlist(int n, const double* pos, const in
     const int fr = BATCH ? frame_of[blockIdx.x] : 0;
     const GeomParams& gp = BATCH ? gps[fr] : gp0;
     const int* cell_start = BATCH ? cell_start0 + fd[fr].cell_off : cell_start0;
-    // LDS sized per launch (nlist_lds_bytes): keys of CAP candidates, then the stencil tables
+    // LDS sized per launch: keys of CAP candidates, then the stencil's runs
     extern __shared__ __attribute__((aligned(16))) unsigned long long nl_lds[];
     unsigned long long* khi = nl_lds;
     unsigned long long* klo = khi + CAP;
-    const int S = (2 * gp.K[0] + 1) * (2 * gp.K[1] + 1) * (2 * gp.K[2] + 1);
-    double* s_sh = reinterpret_cast<double*>(klo + CAP);   // [S][3] image shift of each stencil bin
-    int* kq = reinterpret_cast<int*>(s_sh + 3 * S);       // flat candidate index, moved with its key
-    int* s_base = kq + CAP;                        // [S + 1]
-    int* s_start = s_base + S + 1;                 // [S]
-    int* s_code = s_start + S;                     // [S]
+    const int M = gp.row_runs, w1 = 2 * gp.K[1] + 1, R = gp.runs;
+    NlRun* s_run = reinterpret_cast<NlRun*>(klo + CAP);   // [R]
+    int* kq = reinterpret_cast<int*>(s_run + R);          // candidate index, moved with its key
+    int* s_base = kq + CAP;                               // [R + 1] flat position of each run's first candidate
     const int a = blockIdx.x, lane = threadIdx.x;
     const double pi[3] = {pos[3 * (size_t)a], pos[3 * (size_t)a + 1], pos[3 * (size_t)a + 2]};
-    const long long self_tag = (long long)a;
     const int ci = cell_of[a];
-    const int bi[3] = {ci % gp.nb[0], (ci / gp.nb[0]) % gp.nb[1], ci / (gp.nb[0] * gp.nb[1])};
-    const int w1 = 2 * gp.K[1] + 1, w2 = 2 * gp.K[2] + 1;
+    const int nb0 = gp.nb[0], nb1 = gp.nb[1], nb2 = gp.nb[2];
+    // (bin coordinates: with half a unit added the products stay clear of the integers, below 2^24 bins)
+    const int c12 = (int)((ci + 0.5) * gp.rnb[0]), b0 = ci - c12 * nb0;
+    const int b2 = (int)((c12 + 0.5) * gp.rnb[1]), b1 = c12 - b2 * nb1;
     const int self_code = (64 << 14) | (64 << 7) | 64;
-    const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    const unsigned long long kbase = nl_key_base(gp.rc2);
 
-    // ranges of every stencil bin, scanned across the wave
-    int total = 0;   // wave-uniform
-    // stencil index -> offsets: divisions by w2 and w1 w2 (at most 49) of an index below 343 as a
-    // multiply by ceil(2^16 / d) and a shift, exact in that range
-    const unsigned m2 = (65536u + w2 - 1) / w2, m12 = (65536u + w1 * w2 - 1) / (w1 * w2);
-    for (int sb = 0; sb < S; sb += 64) {
-        const int sidx = sb + lane;
-        int cnt = 0, start = 0, code = 0;
-        if (sidx < S) {
-            const int d12 = (int)(((unsigned)sidx * m12) >> 16), d2 = (int)(((unsigned)sidx * m2) >> 16);
-            const int o0 = d12 - gp.K[0];
-            const int o1 = d2 - d12 * w1 - gp.K[1];
-            const int o2 = sidx - d2 * w2 - gp.K[2];
-            const int tg[3] = {bi[0] + o0, bi[1] + o1, bi[2] + o2};
-            int nn[3], bb[3];
-            bool skip = false;
-            for (int c = 0; c < 3; ++c) {
-                if (gp.periodic) {
-                    // image (floor division by the bins per axis); at least K bins per axis leave
-                    // tg within one box length of the cell, so the image is -1, 0 or 1
-                    int q;
-                    if (gp.nb[c] >= gp.K[c]) {
-                        q = tg[c] < 0 ? -1 : (tg[c] >= gp.nb[c] ? 1 : 0);
-                    } else {
-                        q = tg[c] / gp.nb[c];
-                        if ((tg[c] % gp.nb[c] != 0) && (tg[c] < 0)) --q;
-                    }
-                    nn[c] = q;
-                    bb[c] = tg[c] - q * gp.nb[c];
-                } else {
-                    nn[c] = 0;
-                    bb[c] = tg[c];
-                    if (tg[c] < 0 || tg[c] >= gp.nb[c]) skip = true;
-                }
-            }
-            code = ((nn[0] + 64) << 14) | ((nn[1] + 64) << 7) | (nn[2] + 64);
-            if (!skip) {
-                const int cell = (bb[2] * gp.nb[1] + bb[1]) * gp.nb[0] + bb[0];
-                start = cell_start[cell];
-                cnt = cell_start[cell + 1] - start;
-            }
+    // the non-empty runs, one per lane: range, image, and their flat positions scanned across the wave
+    int total = 0, nr = 0;   // wave-uniform
+    for (int s0 = 0; s0 < R; s0 += 64) {
+        const int k = s0 + lane, rw = (k * gp.m_row) >> 16, o2 = (rw * gp.m_w1) >> 16;
+        const int tg1 = b1 + rw - o2 * w1 - gp.K[1], tg2 = b2 + o2 - gp.K[2];
+        int cnt = 0, start = 0, n0 = 0, n1 = 0, n2 = 0;
+        bool in = k < R;
+        int x0 = b0 - gp.K[0], x1 = b0 + gp.K[0];
+        if (gp.periodic) {
+            n0 = image_of(x0, nb0, gp.K[0]) + k - rw * M;
+            n1 = image_of(tg1, nb1, gp.K[1]);
+            n2 = image_of(tg2, nb2, gp.K[2]);
+        } else {
+            in = in && tg1 >= 0 && tg1 < nb1 && tg2 >= 0 && tg2 < nb2;
+        }
+        x0 = max(x0 - n0 * nb0, 0);
+        x1 = min(x1 - n0 * nb0, nb0 - 1);
+        if (in && x0 <= x1) {
+            const int cell = ((tg2 - n2 * nb2) * nb1 + tg1 - n1 * nb1) * nb0;
+            start = cell_start[cell + x0];
+            cnt = cell_start[cell + x1 + 1] - start;
         }
         int incl = cnt;
         for (int o = 1; o < 64; o <<= 1) {
             const int v = __shfl_up(incl, o);
             if (lane >= o) incl += v;
         }
-        if (sidx < S) {
-            s_base[sidx] = total + incl - cnt;
-            s_start[sidx] = start;
-            s_code[sidx] = code;
-            // the bin's image shift, once (the same expression the output uses, so the same bits)
-            double sh[3];
-            image_shift(gp, (code >> 14) - 64, ((code >> 7) & 127) - 64, (code & 127) - 64, sh);
-            for (int c = 0; c < 3; ++c) s_sh[3 * sidx + c] = sh[c];
+        const unsigned long long m = __ballot(cnt > 0);
+        if (cnt > 0) {
+            const int at = nr + __popcll(m & ((1ull << lane) - 1)), base = total + incl - cnt;
+            NlRun r;
+            image_shift(gp, n0, n1, n2, r.sh);
+            r.off = start - base;
+            r.code = ((n0 + 64) << 14) | ((n1 + 64) << 7) | (n2 + 64);
+            s_run[at] = r;
+            s_base[at] = base;
         }
+        nr += __popcll(m);
         total += __shfl(incl, 63);
     }
-    if (lane == 0) s_base[S] = total;
-    __syncthreads();
+    if (lane == 0) s_base[nr] = total;
+    wave_barrier();
 
-    int count = 0;   // wave-uniform
-    int tcount[MAXT];   // wave-uniform, per type (may exceed CAP)
-    for (int t = 0; t < MAXT; ++t) tcount[t] = 0;
-    int b = 0;       // this lane's current stencil bin
+    // One flat sweep over the candidates of all runs. A lane's position grows by 64 a step, about the
+    // length of a run (three bins of r_c): its run is found by walking on from the last one.
+    int count = 0, over = 0;   // count: wave-uniform
+    int b = 0;                 // this lane's current run
     for (int q0 = 0; q0 < total; q0 += 64 * NL_UNROLL) {
         double4 c4[NL_UNROLL];
-        int bin[NL_UNROLL], cq[NL_UNROLL];
+        int run[NL_UNROLL], cq[NL_UNROLL];
 #pragma unroll
         for (int u = 0; u < NL_UNROLL; ++u) {
-            const int q = q0 + 64 * u + lane;
-            bin[u] = -1;
-            if (q < total) {
-                // bin of flat candidate q: the last b with s_base[b] <= q (s_base is non-decreasing
-                // with s_base[S] = total > q); q only grows, so the search starts at the last bin
-                int hi = S;
-                while (hi - b > 1) {
-                    const int mid = (b + hi) >> 1;
-                    if (s_base[mid] <= q) b = mid;
-                    else hi = mid;
-                }
-                bin[u] = b;
-                cq[u] = s_start[b] + (q - s_base[b]);
-                c4[u] = cand[cq[u]];
-            }
+            const int q = min(q0 + 64 * u + lane, total - 1);
+            while (s_base[b + 1] <= q) ++b;
+            run[u] = b;
+            cq[u] = q + s_run[b].off;
+            c4[u] = cand[cq[u]];
         }
 #pragma unroll
         for (int u = 0; u < NL_UNROLL; ++u) {
-            bool pass = false;
-            double r2 = 0.0;
-            long long tag = 0;
-            int code = 0;
-            if (bin[u] >= 0) {
-                code = s_code[bin[u]];
-                tag = __double_as_longlong(c4[u].w);
-                const double* sh = s_sh + 3 * bin[u];
-                if (!((tag & 0x3fffffffll) == self_tag && code == self_code)) {
-                    const double d0 = (c4[u].x + sh[0]) - pi[0];
-                    const double d1 = (c4[u].y + sh[1]) - pi[1];
-                    const double d2 = (c4[u].z + sh[2]) - pi[2];
-                    r2 = d0 * d0 + d1 * d1 + d2 * d2;
-                    pass = r2 < gp.rc2;
-                }
-            }
-            const unsigned long long m = __ballot(pass);
-            const int tj = (int)((unsigned long long)tag >> 60);
-            if (pass) {
-                const int idx = count + __popcll(m & lt);
-                if (idx < CAP) {
-                    const unsigned long long jo = ((unsigned long long)tag >> 30) & 0x3fffffffull;
-                    const unsigned long long rb = (unsigned long long)__double_as_longlong(r2);
-                    khi[idx] = ((unsigned long long)tj << 59) | (rb >> 5);
-                    klo[idx] = ((rb & 31ull) << 59) | (jo << 21) | (unsigned long long)code;
-                    kq[idx] = cq[u];
-                }
-            }
-            // per-type counts from ballots (no shared-word atomics)
-            for (int t = 0; t < gp.ntypes; ++t) tcount[t] += __popcll(__ballot(pass && tj == t));
-            count += __popcll(m);
+            if (q0 + 64 * u >= total) break;   // (wave-uniform)
+            const NlRun r = s_run[run[u]];
+            const unsigned long long tag = (unsigned long long)__double_as_longlong(c4[u].w);
+            const double d0 = (c4[u].x + r.sh[0]) - pi[0];
+            const double d1 = (c4[u].y + r.sh[1]) - pi[1];
+            const double d2 = (c4[u].z + r.sh[2]) - pi[2];
+            const double r2 = d0 * d0 + d1 * d1 + d2 * d2;
+            const bool self = (int)(tag & 0x3fffffffull) == a && r.code == self_code;
+            const bool pass = q0 + 64 * u + lane < total && !self && r2 < gp.rc2;
+            nl_push<CAP>(pass, (int)(tag >> 60), r2, (int)((tag >> 30) & 0x3fffffffull), r.code, run[u], cq[u], kbase,
+                         gp.ntypes, lane, count, over, khi, klo, kq);
         }
     }
-    nlist_select<CAP>(a, lane, count, tcount, gp, khi, klo, kq, nl_j, nl_r, nnei, st,
-                      [&](int q, int code, double* r, int& j) {
-                          const int n0 = (code >> 14) - 64, n1 = ((code >> 7) & 127) - 64, n2 = (code & 127) - 64;
+    nlist_select<CAP>(a, lane, count, over, gp, khi, klo, kq, nl_j, nl_r, nnei, st,
+                      [&](int q, int rn, double* r, int& j) {
                           const double4 c4 = cand[q];
                           j = (int)((__double_as_longlong(c4.w) >> 30) & 0x3fffffffll);   // caller index
-                          double sh[3];
-                          image_shift(gp, n0, n1, n2, sh);
-                          r[0] = (c4.x + sh[0]) - pi[0];
-                          r[1] = (c4.y + sh[1]) - pi[1];
-                          r[2] = (c4.z + sh[2]) - pi[2];
+                          r[0] = (c4.x + s_run[rn].sh[0]) - pi[0];
+                          r[1] = (c4.y + s_run[rn].sh[1]) - pi[1];
+                          r[2] = (c4.z + s_run[rn].sh[2]) - pi[2];
                       });
 }
 
@@ -887,10 +911,8 @@ __global__ void __launch_bounds__(64) k_nlist_ext(int ntot, const double* pos, c
     const int ci = perm[a];
     const double pi[3] = {pos[3 * (size_t)a], pos[3 * (size_t)a + 1], pos[3 * (size_t)a + 2]};
     const int b0 = ext_start[ci], b1 = ext_start[ci + 1];
-    const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    int count = 0;   // wave-uniform
-    int tcount[MAXT];
-    for (int t = 0; t < MAXT; ++t) tcount[t] = 0;
+    const unsigned long long kbase = nl_key_base(gp.rc2);
+    int count = 0, over = 0;   // count: wave-uniform
     for (int q0 = b0; q0 < b1; q0 += 64) {
         const int q = q0 + lane;
         bool pass = false;
@@ -908,20 +930,10 @@ __global__ void __launch_bounds__(64) k_nlist_ext(int ntot, const double* pos, c
                 pass = r2 < gp.rc2;
             }
         }
-        const unsigned long long m = __ballot(pass);
-        if (pass) {
-            const int idx = count + __popcll(m & lt);
-            if (idx < CAP) {
-                const unsigned long long rb = (unsigned long long)__double_as_longlong(r2);
-                khi[idx] = ((unsigned long long)tj << 59) | (rb >> 5);
-                klo[idx] = ((rb & 31ull) << 59) | ((unsigned long long)j << 21);   // no image: code 0
-                kq[idx] = jq;
-            }
-        }
-        for (int t = 0; t < gp.ntypes; ++t) tcount[t] += __popcll(__ballot(pass && tj == t));
-        count += __popcll(m);
+        // (no image, no run: 0)
+        nl_push<CAP>(pass, tj, r2, j, 0, 0, jq, kbase, gp.ntypes, lane, count, over, khi, klo, kq);
     }
-    nlist_select<CAP>(a, lane, count, tcount, gp, khi, klo, kq, nl_j, nl_r, nnei, st,
+    nlist_select<CAP>(a, lane, count, over, gp, khi, klo, kq, nl_j, nl_r, nnei, st,
                       [&](int q, int, double* r, int& jj) {
                           jj = perm[q];
                           for (int c = 0; c < 3; ++c) r[c] = pos[3 * (size_t)q + c] - pi[c];
@@ -949,9 +961,8 @@ struct NeumaierSum {
 // neighbours dropped by sel from its per-atom counters (one wave, lane = its lane index).
 __device__ void sum_drop_slots(DevStats* st, int lane)
 {
-    const unsigned long long* ds = drop_slots(st);
     unsigned long long v = 0;
-    for (int i = lane; i < NL_DROP_SLOTS; i += 64) v += ds[i];
+    for (int i = lane; i < NL_DROP_SLOTS; i += 64) v += drop_slots(st)[i];
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
     if (lane == 0) st->nbr_dropped = v;
 }
@@ -1079,17 +1090,17 @@ void launch_bbox(int n, const double* coord, double* out, hipStream_t s)
 void launch_nlist(int n, const double* pos, const int* perm, const int* inv_perm, const int* cell_of,
                   const int* cell_start, const double4* cand, const GeomParams& gp, int* nl_j, double* nl_r,
                   int* nnei, DevStats* st, hipStream_t s, const GeomParams* gps, const FrameDesc* fd,
-                  const int* frame_of, int max_stencil, int max_cap)
+                  const int* frame_of, int max_runs, int max_cap)
 {
     // candidate buffer sized from the expected count within r_c (the synchronous entry point reruns
     // a frame that overflowed with the largest buffer); LDS = 20 B per candidate slot + 36 B per
-    // stencil bin, so small stencils leave room for more resident waves. A batch passes the
-    // largest stencil and buffer of its frames.
+    // run, so small stencils leave room for more resident waves. A batch passes the most runs and
+    // the largest buffer of its frames.
     const bool batch = gps != nullptr;
-    const int S = batch ? max_stencil : (2 * gp.K[0] + 1) * (2 * gp.K[1] + 1) * (2 * gp.K[2] + 1);
+    const int R = batch ? max_runs : gp.runs;
     const int want = batch ? max_cap : gp.cap;
     const int cap = want <= 256 ? 256 : (want <= 512 ? 512 : NL_CAP);
-    const size_t lds = (size_t)cap * 20 + (size_t)S * 24 + (size_t)(3 * S + 1) * 4;
+    const size_t lds = (size_t)cap * 20 + (size_t)R * (sizeof(NlRun) + 4) + 4;
 #define DPK_NL(C, B)                                                                                              \
     hipLaunchKernelGGL((k_nlist<C, B>), dim3(n), dim3(64), lds, s, n, pos, perm, inv_perm, cell_of, cell_start,   \
                        cand, gp, gps, fd, frame_of, nl_j, nl_r, nnei, st)
