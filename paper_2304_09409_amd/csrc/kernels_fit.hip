@@ -15,9 +15,9 @@
 // Blocks are placed so that each XCD (block b runs on XCD b % 8) works on a contiguous range of
 // atoms: with atoms sorted by species, an XCD's L2 mostly holds one species' weights.
 // Bound: the streaming of the weights (4.16 MB per block; small frames) and, in the 64-atom shape, the
-// matrix unit with the LDS reads of the B operands. Measured (mixed; before the split by role and the
-// longer lookahead in brackets): 192 atoms 76 us (91), 12,288 atoms 119 us (128), 110,592 atoms 798 us
-// (900).
+// matrix unit with the LDS reads of the B operands. Measured (mixed; before the split by role, the longer
+// lookahead and, for small frames, the steps, in brackets): 192 atoms 51 us (91), 12,288 atoms 119 us
+// (128), 110,592 atoms 798 us (900).
 #include <hip/hip_runtime.h>
 #include <type_traits>
 #include "dpk_device.h"
@@ -36,6 +36,17 @@ struct F8 {
 
 constexpr int FX_G = 4;    // layer-1 K-chunks per D group
 constexpr int FX_PD = 4;   // weight lookahead (K-chunks) of the 240-wide layers
+
+// The net in one launch, or for small frames (launch_fitx) in steps, so that the two products with W1,
+// three quarters of the weights, are spread over FX_SUB blocks per atom tile: layer 1 split by output
+// features, the 240-wide layers, dD and dT split by the rows m = sub (mod 4). Every sum keeps its order: the
+// results are those of the one launch. A last small launch adds the part-2 partials to the rows m < 16.
+// (Left to the last block of a tile to finish, its fences, which write an XCD's L2 back, took longer the
+// more blocks there were: 37 us for 600 atoms, 89 for 1,890.) Between the launches a block's scratch holds,
+// per layer slot: slot 0 the activations of layer 1 and afterwards part 1 of the rows m < 16 and a place for
+// stores that have no atom; slot 1 the part-2 partials; slot 2 ga1.
+enum { FX_ALL, FX_L1, FX_MID, FX_DD, FX_SUM };
+constexpr int FX_SUB = 4;
 
 // acc += a b with a, b split as hi + lo: lo*hi + hi*lo + hi*hi (SPLIT), or hi*hi only.
 template <bool SPLIT>
@@ -94,13 +105,13 @@ __device__ __forceinline__ void st_half(__bf16* f, int lane, int half, const flo
     if constexpr (SPLIT) *reinterpret_cast<bf4*>(f + 512 + lane * 8 + half * 4) = lo;
 }
 
-template <int NAT, bool SPLIT, int NW, bool ENS>
+template <int NAT, bool SPLIT, int NW, bool ENS, int PH>
 __global__ void __launch_bounds__(64 * NW) k_fitx(FitArgs A_)
 {
     const FitArgs A = ENS ? model_args(A_) : A_;
     constexpr int NA = 16 * NAT;                       // atoms per block
     constexpr int FR = XF_ELEMS, PD = FX_PD;
-    constexpr int TPW = (15 + NW - 1) / NW;            // feature tiles per wave (at most)
+    constexpr int TPW = PH == FX_L1 ? 1 : (15 + NW - 1) / NW;   // feature tiles per wave (at most)
     constexpr int NWA = NW / NAT;                      // waves sharing one atom tile's D fragments
     static_assert(NW % NAT == 0 && NW >= 4, "wave layout");
     static_assert(XF_NCH2 % PD == 0, "prefetch ring slots are compile-time");
@@ -116,7 +127,9 @@ __global__ void __launch_bounds__(64 * NW) k_fitx(FitArgs A_)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform (scalar registers)
     const int lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
     const int nblk = gridDim.x, xcd = blockIdx.x & 7, per = nblk >> 3, rem = nblk & 7;
-    const int blk = xcd * per + min(xcd, rem) + (blockIdx.x >> 3);
+    const int pos = xcd * per + min(xcd, rem) + (blockIdx.x >> 3);
+    // (the sub-blocks of one number, which read the same weights, follow each other)
+    const int ntile = PH == FX_L1 || PH == FX_DD ? nblk / FX_SUB : nblk, sub = pos / ntile, blk = pos - sub * ntile;
     // tile blk of the species-aligned tiling: species t has ceil(count_t / NA) tiles of its own,
     // so that no block runs the net twice for a boundary between species (the grid holds
     // ceil(N / NA) + ntypes blocks, an upper bound; the surplus ones leave here)
@@ -134,11 +147,14 @@ __global__ void __launch_bounds__(64 * NW) k_fitx(FitArgs A_)
         }
     }
     if (a0 < 0) return;
-    const int t_lo = ty, t_hi = ty;
+    const int ti = ty;
     const float* Tg = reinterpret_cast<const float*>(A.T);
     float* dTg = reinterpret_cast<float*>(A.dT);
     float* scr = reinterpret_cast<float*>(A.act) + (size_t)blk * NAT * XF_ACT;
-    const int nown = (15 - wave + NW - 1) / NW;       // feature tiles wave + NW i < 15
+    // feature tiles ftile(i) = first + NW i < 15 (layer 1 on its own: four per block)
+    const int first = PH == FX_L1 ? 4 * sub + wave : wave;
+    const int nown = PH == FX_L1 ? (first < 15 ? 1 : 0) : (15 - wave + NW - 1) / NW;
+    auto ftile = [&](int i) { return first + NW * i; };
 
     // activation scratch of (layer l, feature tile t, atom tile a): this lane's four values
     const int lane16 = lane * 16;
@@ -151,72 +167,80 @@ __global__ void __launch_bounds__(64 * NW) k_fitx(FitArgs A_)
     };
     auto sb = [&](int c, int a) { return s_b + (c * NAT + a) * FR; };
 
-#pragma unroll 1
-    for (int ti = t_lo; ti <= t_hi; ++ti) {
-        const float* fv = reinterpret_cast<const float*>(A.fvec) + (size_t)ti * FVEC;
-        const __bf16* W = reinterpret_cast<const __bf16*>(A.fmat) + (size_t)ti * XF_NFRAG * FR;
-        const rsrc_t wrs = make_rsrc(W, XF_NFRAG * FR * 2);
+    const float* fv = reinterpret_cast<const float*>(A.fvec) + (size_t)ti * FVEC;
+    const __bf16* W = reinterpret_cast<const __bf16*>(A.fmat) + (size_t)ti * XF_NFRAG * FR;
+    const rsrc_t wrs = make_rsrc(W, XF_NFRAG * FR * 2);
 
-        f4 acc[TPW][NAT];
-        float h[TPW][NAT][4];
-        auto zero_acc = [&]() {
+    f4 acc[TPW][NAT];
+    float h[TPW][NAT][4];
+    auto zero_acc = [&]() {
+#pragma unroll
+        for (int i = 0; i < TPW; ++i)
+#pragma unroll
+            for (int a = 0; a < NAT; ++a) acc[i][a] = f4{0.f, 0.f, 0.f, 0.f};
+    };
+    // Weight fragment of K-chunk c of the product at wb for the wave's tile i (a wave without a
+    // tile i reads its last valid tile again: every read is unconditional, since a read skipped
+    // by a branch makes the compiler wait for every read in flight).
+    auto wtile = [&](int i) { return min(ftile(i), 14); };
+    // The first PD K-chunks of the next 240-wide product, requested before the preceding
+    // epilogue and barrier so that their latency is hidden; each product step then requests
+    // the chunk PD ahead (a ring of PD register slots).
+    F8 Apf[PD][TPW];
+    auto prefetch8 = [&](int wb) {
+#pragma unroll
+        for (int d = 0; d < PD; ++d)
+#pragma unroll
+            for (int i = 0; i < TPW; ++i) Apf[d][i] = ld_wfrag<SPLIT>(wrs, lane16, wb + d * 15 + wtile(i));
+    };
+    // acc[i][a] = sum over the 8 K-chunks of W(own tile i, c) B(c, a), B from s_b; Apf must
+    // hold the first chunk of product wb (prefetch8)
+    auto gemm8 = [&](int wb) {
+        zero_acc();
+        F8 Rg[PD][TPW];
+#pragma unroll
+        for (int d = 0; d < PD; ++d)
+#pragma unroll
+            for (int i = 0; i < TPW; ++i) Rg[d][i] = Apf[d][i];
+#pragma unroll
+        for (int c = 0; c < XF_NCH2; ++c) {
+            F8 Ac[TPW];
+#pragma unroll
+            for (int i = 0; i < TPW; ++i) Ac[i] = Rg[c % PD][i];
+            if (c + PD < XF_NCH2) {
+#pragma unroll
+                for (int i = 0; i < TPW; ++i) Rg[c % PD][i] = ld_wfrag<SPLIT>(wrs, lane16, wb + (c + PD) * 15 + wtile(i));
+            }
+            keep_loads();
+            F8 B[NAT];
+#pragma unroll
+            for (int a = 0; a < NAT; ++a) B[a] = ld_frag<SPLIT>(sb(c, a), lane);
 #pragma unroll
             for (int i = 0; i < TPW; ++i)
+                if (i < nown) {
 #pragma unroll
-                for (int a = 0; a < NAT; ++a) acc[i][a] = f4{0.f, 0.f, 0.f, 0.f};
-        };
-        // Weight fragment of K-chunk c of the product at wb for the wave's tile i (a wave without a
-        // tile i reads its last valid tile again: every read is unconditional, since a read skipped
-        // by a branch makes the compiler wait for every read in flight).
-        auto wtile = [&](int i) { return min(wave + NW * i, 14); };
-        // The first PD K-chunks of the next 240-wide product, requested before the preceding
-        // epilogue and barrier so that their latency is hidden; each product step then requests
-        // the chunk PD ahead (a ring of PD register slots).
-        F8 Apf[PD][TPW];
-        auto prefetch8 = [&](int wb) {
-#pragma unroll
-            for (int d = 0; d < PD; ++d)
-#pragma unroll
-                for (int i = 0; i < TPW; ++i) Apf[d][i] = ld_wfrag<SPLIT>(wrs, lane16, wb + d * 15 + wtile(i));
-        };
-        // acc[i][a] = sum over the 8 K-chunks of W(own tile i, c) B(c, a), B from s_b; Apf must
-        // hold the first chunk of product wb (prefetch8)
-        auto gemm8 = [&](int wb) {
-            zero_acc();
-            F8 Rg[PD][TPW];
-#pragma unroll
-            for (int d = 0; d < PD; ++d)
-#pragma unroll
-                for (int i = 0; i < TPW; ++i) Rg[d][i] = Apf[d][i];
-#pragma unroll
-            for (int c = 0; c < XF_NCH2; ++c) {
-                F8 Ac[TPW];
-#pragma unroll
-                for (int i = 0; i < TPW; ++i) Ac[i] = Rg[c % PD][i];
-                if (c + PD < XF_NCH2) {
-#pragma unroll
-                    for (int i = 0; i < TPW; ++i) Rg[c % PD][i] = ld_wfrag<SPLIT>(wrs, lane16, wb + (c + PD) * 15 + wtile(i));
+                    for (int a = 0; a < NAT; ++a) mma32<SPLIT>(acc[i][a], Ac[i], B[a]);
                 }
-                keep_loads();
-                F8 B[NAT];
-#pragma unroll
-                for (int a = 0; a < NAT; ++a) B[a] = ld_frag<SPLIT>(sb(c, a), lane);
-#pragma unroll
-                for (int i = 0; i < TPW; ++i)
-                    if (i < nown) {
-#pragma unroll
-                        for (int a = 0; a < NAT; ++a) mma32<SPLIT>(acc[i][a], Ac[i], B[a]);
-                    }
-            }
-        };
-        auto vec4 = [&](int off, int t) { return *reinterpret_cast<const f4*>(fv + off + 16 * t + 4 * g); };
+        }
+    };
+    auto vec4 = [&](int off, int t) { return *reinterpret_cast<const f4*>(fv + off + 16 * t + 4 * g); };
 
-        __syncthreads();   // s_b, s_e, s_p1 of the previous species are no longer read
+    auto stage_tq = [&]() {
         for (int idx = threadIdx.x; idx < NA * 16; idx += 64 * NW) {
             const int al = idx >> 4, n = idx & 15;
             const int at = a0 + al < A.natoms ? a0 + al : a0;
             *reinterpret_cast<f4*>(&s_tq[al][n][0]) = *reinterpret_cast<const f4*>(Tg + ((size_t)at * E2 + n) * 4);
         }
+    };
+    // feature tile 15 does not exist: the second half of K-chunk 7 is zero
+    auto zero_tile15 = [&]() {
+        const float z[4] = {0.f, 0.f, 0.f, 0.f};
+        if (wave == NW - 1)
+#pragma unroll
+            for (int a = 0; a < NAT; ++a) st_half<SPLIT>(sb(7, a), lane, 1, z);
+    };
+    if constexpr (PH == FX_ALL || PH == FX_L1) {
+        if constexpr (PH == FX_ALL) stage_tq();
         // ------------------------------------------------------------ layer 1: D (1600) -> 240
         // D fragment of K-chunk c for atom tile `wave`: lane group g holds D[2c][4g+r] and
         // D[2c+1][4g+r], D[m][n] = sum_k T[m][k] T[n][k] (Sec. II.A.1, D = T T_<^T).
@@ -313,12 +337,12 @@ __global__ void __launch_bounds__(64 * NW) k_fitx(FitArgs A_)
             static_assert(NGRP % 2 == 1, "the last group has an even number");
             group(NGRP - 1, even);
         }
-        prefetch8(XF_W2F);
+        if constexpr (PH == FX_ALL) prefetch8(XF_W2F);
         // a1 = tanh(W1 D + b1), h1 = wh1 a1
 #pragma unroll
         for (int i = 0; i < TPW; ++i)
             if (i < nown) {
-                const int t = wave + NW * i;
+                const int t = ftile(i);
                 const f4 b = vec4(FV_B1, t), wh = vec4(FV_WH1, t);
 #pragma unroll
                 for (int a = 0; a < NAT; ++a) {
@@ -329,15 +353,33 @@ __global__ void __launch_bounds__(64 * NW) k_fitx(FitArgs A_)
                         h[i][a][r] = wh[r] * av[r];
                     }
                     *sptr(0, t, a) = av;
+                    if constexpr (PH == FX_ALL) st_half<SPLIT>(sb(t >> 1, a), lane, t & 1, h[i][a]);
+                }
+            }
+        if constexpr (PH == FX_ALL) {
+            zero_tile15();
+            __syncthreads();
+        }
+    }
+    if constexpr (PH == FX_MID) {
+        prefetch8(XF_W2F);
+#pragma unroll
+        for (int i = 0; i < TPW; ++i)
+            if (i < nown) {
+                const int t = ftile(i);
+                const f4 wh = vec4(FV_WH1, t);
+#pragma unroll
+                for (int a = 0; a < NAT; ++a) {
+                    const f4 av = *sptr(0, t, a);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) h[i][a][r] = wh[r] * av[r];
                     st_half<SPLIT>(sb(t >> 1, a), lane, t & 1, h[i][a]);
                 }
             }
-        if (wave == NW - 1) {   // feature tile 15 does not exist: the second half of K-chunk 7 is zero
-            const float z[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int a = 0; a < NAT; ++a) st_half<SPLIT>(sb(7, a), lane, 1, z);
-        }
+        zero_tile15();
         __syncthreads();
+    }
+    if constexpr (PH == FX_ALL || PH == FX_MID) {
         // ------------------------------------------------------------ layers 2, 3: h += wh tanh(W h + b)
 #pragma unroll 1
         for (int layer = 2; layer <= 3; ++layer) {
@@ -348,7 +390,7 @@ __global__ void __launch_bounds__(64 * NW) k_fitx(FitArgs A_)
 #pragma unroll
             for (int i = 0; i < TPW; ++i)
                 if (i < nown) {
-                    const int t = wave + NW * i;
+                    const int t = ftile(i);
                     const f4 b = vec4(ob, t), wh = vec4(ow, t);
 #pragma unroll
                     for (int a = 0; a < NAT; ++a) {
@@ -372,7 +414,7 @@ __global__ void __launch_bounds__(64 * NW) k_fitx(FitArgs A_)
 #pragma unroll
             for (int i = 0; i < TPW; ++i)
                 if (i < nown) {
-                    const f4 w4 = vec4(FV_W4, wave + NW * i);
+                    const f4 w4 = vec4(FV_W4, ftile(i));
 #pragma unroll
                     for (int a = 0; a < NAT; ++a)
 #pragma unroll
@@ -391,7 +433,7 @@ __global__ void __launch_bounds__(64 * NW) k_fitx(FitArgs A_)
 #pragma unroll
         for (int i = 0; i < TPW; ++i)
             if (i < nown) {
-                const int t = wave + NW * i;
+                const int t = ftile(i);
                 const f4 w4 = vec4(FV_W4, t), wh = vec4(FV_WH3, t);
 #pragma unroll
                 for (int a = 0; a < NAT; ++a) {
@@ -424,7 +466,7 @@ __global__ void __launch_bounds__(64 * NW) k_fitx(FitArgs A_)
 #pragma unroll
             for (int i = 0; i < TPW; ++i)
                 if (i < nown) {
-                    const int t = wave + NW * i;
+                    const int t = ftile(i);
                     const f4 wh = vec4(ow, t);
 #pragma unroll
                     for (int a = 0; a < NAT; ++a) {
@@ -440,6 +482,30 @@ __global__ void __launch_bounds__(64 * NW) k_fitx(FitArgs A_)
                 }
             __syncthreads();
         }
+    }
+    // what the launch of the dD phase reads and writes in the block's scratch (see FX_ALL above)
+    constexpr int SLOT = 16 * NAT * 256;   // floats per layer slot
+    static_assert(XF_NCH2 * NAT * XF_ELEMS * 2 == SLOT * 4, "ga1 fills a slot");
+    float *p1g = scr, *q2g = scr + SLOT;
+    if constexpr (PH == FX_MID) {
+        for (int e = threadIdx.x; e < SLOT / 4; e += 64 * NW)
+            reinterpret_cast<f4*>(scr + 2 * SLOT)[e] = reinterpret_cast<const f4*>(s_b)[e];
+    }
+    // rows n < 16 of dT: part 1 + the four row groups' part 2 (slot (row group, atom tile) [lane][16])
+    auto add_part2 = [&](auto&& p1, const float* q2) {
+        for (int idx = threadIdx.x; idx < NA * 16; idx += 64 * NW) {
+            const int al = idx >> 4, n = idx & 15;
+            const int at = a0 + al;
+            if (at < A.natoms && A.itype[at] == ti) {
+                const int a = al >> 4, lp = (n >> 2) * 16 + (al & 15), r = n & 3;
+                f4 v = *reinterpret_cast<const f4*>(p1(al, n));
+#pragma unroll
+                for (int w = 0; w < 4; ++w) v += *reinterpret_cast<const f4*>(q2 + ((w * NAT + a) * 64 + lp) * 16 + 4 * r);
+                *reinterpret_cast<f4*>(dTg + ((size_t)at * E2 + n) * 4) = v;
+            }
+        }
+    };
+    if constexpr (PH == FX_ALL) {
         // ------------------------------------------------------------ dD = W1 ga1 and dT
         // D-row tile m of dD holds dD[m][n = 4g + r] for 16 atoms. dT[m][k] collects
         // sum_n dD[m][n] T[n][k] (part 1, reduced over lane groups) and, for rows n < 16,
@@ -576,48 +642,137 @@ __global__ void __launch_bounds__(64 * NW) k_fitx(FitArgs A_)
                             f4{q2[a][r][0], q2[a][r][1], q2[a][r][2], q2[a][r][3]};
                 __syncthreads();
             }
-            // rows n < 16 of dT: part 1 + the four row groups' part 2
-            for (int idx = threadIdx.x; idx < NA * 16; idx += 64 * NW) {
-                const int al = idx >> 4, n = idx & 15;
-                const int at = a0 + al;
-                if (at < A.natoms && A.itype[at] == ti) {
-                    const int a = al >> 4, lp = (n >> 2) * 16 + (al & 15), r = n & 3;
-                    f4 v = *reinterpret_cast<const f4*>(&s_p1[al][n][0]);
-#pragma unroll
-                    for (int w = 0; w < 4; ++w) v += *reinterpret_cast<const f4*>(qs + ((w * NAT + a) * 64 + lp) * 16 + 4 * r);
-                    *reinterpret_cast<f4*>(dTg + ((size_t)at * E2 + n) * 4) = v;
-                }
-            }
+            add_part2([&](int al, int n) { return &s_p1[al][n][0]; }, qs);
         }
     }
+    if constexpr (PH == FX_DD) {
+        // As below, for the rows m = sub + 4 p: waves 0 to 3 form the rows of the passes p = w + 4 j of round
+        // j, wave 4 + a the dT of atom tile a from the round's four rows in the order of p.
+        static_assert(NW == 8 && NAT <= 4, "four product waves, an epilogue wave per atom tile");
+        constexpr int NPASS = E2 / 4, NRND = (NPASS + 3) / 4;
+        float* none = scr + 15 * NAT * 256;
+        for (int e = threadIdx.x; e < SLOT / 4; e += 64 * NW)
+            reinterpret_cast<f4*>(s_b)[e] = reinterpret_cast<const f4*>(scr + 2 * SLOT)[e];
+        stage_tq();
+        auto dslot = [&](int j, int w, int a) { return reinterpret_cast<f4*>(&s_dd[j & 1][w][a][lane][0]); };
+        if (wave < 4) {
+            auto wfrag = [&](int j, int c) {
+                return ld_wfrag<SPLIT>(wrs, lane16, XF_W1B + (sub + 4 * min(wave + 4 * j, NPASS - 1)) * XF_NCH2 + c);
+            };
+            F8 RD[2 * XF_NCH2];
+#pragma unroll
+            for (int d = 0; d < 2 * XF_NCH2; ++d) RD[d] = wfrag(d / XF_NCH2, d % XF_NCH2);
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < NRND; ++j) {
+                f4 dd[NAT];
+#pragma unroll
+                for (int a = 0; a < NAT; ++a) dd[a] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int c = 0; c < XF_NCH2; ++c) {
+                    const int sl = (j & 1) * XF_NCH2 + c;
+                    const F8 Ac = RD[sl];
+                    if (j + 2 < NRND) RD[sl] = wfrag(j + 2, c);
+                    keep_loads();
+                    F8 B[NAT];
+#pragma unroll
+                    for (int a = 0; a < NAT; ++a) B[a] = ld_frag<SPLIT>(sb(c, a), lane);
+#pragma unroll
+                    for (int a = 0; a < NAT; ++a) mma32<SPLIT>(dd[a], Ac, B[a]);
+                }
+#pragma unroll
+                for (int a = 0; a < NAT; ++a) *dslot(j, wave, a) = dd[a];
+                __syncthreads();
+            }
+        } else {
+            const int a = min(wave - 4, NAT - 1), at = a0 + 16 * a + c16;
+            const bool own = wave - 4 < NAT, mined = at < A.natoms && A.itype[at] == ti;
+            const float* Td = Tg + (size_t)(at < A.natoms ? at : a0) * (E2 * 4);
+            float* dst = mined ? dTg + (size_t)at * (E2 * 4) + ksel(g) : none + threadIdx.x;
+            const int dstep = mined ? 4 : 0;
+            f4 tn[4], tm[4];   // T rows 4g..4g+3 of this lane's atom; rows of the round's passes
+            float q2[4][4];
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                tn[r] = *reinterpret_cast<const f4*>(&s_tq[16 * a + c16][4 * g + r][0]);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) q2[r][k] = 0.f;
+            }
+            auto trow = [&](int p) { return *reinterpret_cast<const f4*>(Td + (sub + 4 * min(p, NPASS - 1)) * 4); };
+#pragma unroll
+            for (int w = 0; w < 4; ++w) tm[w] = trow(w);
+#pragma unroll
+            for (int j = 0; j < NRND; ++j) {
+                __syncthreads();
+                if (own) {
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) {
+                        const int p = w + 4 * j, m = sub + 4 * p;
+                        if (p >= NPASS) continue;
+                        const f4 t = tm[w], dd = *dslot(j, w, a);
+                        tm[w] = trow(p + 4);
+                        float part[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) {
+                                part[k] += dd[r] * tn[r][k];
+                                q2[r][k] += dd[r] * t[k];
+                            }
+                        const float pk = sum_groups4(part);   // lane group g: component ksel(g)
+                        if (p < 4) p1g[((16 * a + c16) * 16 + m) * 4 + ksel(g)] = pk;
+                        else dst[m * dstep] = pk;
+                    }
+                }
+            }
+            if (own)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    *reinterpret_cast<f4*>(q2g + ((sub * NAT + a) * 64 + lane) * 16 + 4 * r) = f4{q2[r][0], q2[r][1], q2[r][2], q2[r][3]};
+        }
+    }
+    if constexpr (PH == FX_SUM) add_part2([&](int al, int n) { return p1g + (al * 16 + n) * 4; }, q2g);
 }
 
 }  // namespace
 
-// Block shape: 64 atoms when the frame fills the CUs, so that the weights a block streams serve more
-// atoms; 32 atoms while the 64-atom blocks would leave half of the CUs idle (8,100 atoms: 86 us).
-template <int NAT>
-static void launch_fitx_shape(bool split, const FitArgs& a, hipStream_t s)
+template <int NAT, int NW, int PH>
+static void launch_fitx_phase(bool split, int sub, const FitArgs& a, hipStream_t s)
 {
-    constexpr int NW = 8;
     const bool ens = a.nmodels > 1;
-    dim3 grid((a.natoms + 16 * NAT - 1) / (16 * NAT) + a.ntypes, ens ? a.nmodels : 1), block(64 * NW);
+    dim3 grid(((a.natoms + 16 * NAT - 1) / (16 * NAT) + a.ntypes) * sub, ens ? a.nmodels : 1), block(64 * NW);
     // ens: one launch for a model ensemble, blockIdx.y = model (a separate instantiation)
     if (split) {
-        if (ens) hipLaunchKernelGGL((k_fitx<NAT, true, NW, true>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((k_fitx<NAT, true, NW, false>), grid, block, 0, s, a);
+        if (ens) hipLaunchKernelGGL((k_fitx<NAT, true, NW, true, PH>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((k_fitx<NAT, true, NW, false, PH>), grid, block, 0, s, a);
     } else {
-        if (ens) hipLaunchKernelGGL((k_fitx<NAT, false, NW, true>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((k_fitx<NAT, false, NW, false>), grid, block, 0, s, a);
+        if (ens) hipLaunchKernelGGL((k_fitx<NAT, false, NW, true, PH>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((k_fitx<NAT, false, NW, false, PH>), grid, block, 0, s, a);
     }
 }
 
+// Block shape: 64 atoms when the frame fills the CUs, so that the weights a block streams serve more
+// atoms; 32 atoms while the 64-atom blocks would leave half of the CUs idle (8,100 atoms: 86 us). In steps
+// while the blocks of the split phases fit the CUs at once (a block per CU): 192 atoms 51 us against 76 in
+// one launch, 1,890 atoms 59 against 77; past that the steps lose it again (3,000: 75 and 77, 4,200: 95 and
+// 78).
 void launch_fitx(bool split, const FitArgs& a, hipStream_t s)
 {
     if (a.natoms <= 0) return;
     const int64_t blocks64 = ((int64_t)a.natoms + 63) / 64 * (a.nmodels > 1 ? a.nmodels : 1);
-    if (blocks64 * 2 <= (a.ncu > 0 ? a.ncu : 256)) launch_fitx_shape<2>(split, a, s);
-    else launch_fitx_shape<4>(split, a, s);
+    const int64_t ncu = a.ncu > 0 ? a.ncu : 256, models = a.nmodels > 1 ? a.nmodels : 1;
+    const int64_t blocks32 = (((int64_t)a.natoms + 31) / 32 + a.ntypes) * models;
+    if (blocks32 * FX_SUB <= ncu) {
+        launch_fitx_phase<2, 4, FX_L1>(split, FX_SUB, a, s);
+        launch_fitx_phase<2, 8, FX_MID>(split, 1, a, s);
+        launch_fitx_phase<2, 8, FX_DD>(split, FX_SUB, a, s);
+        launch_fitx_phase<2, 8, FX_SUM>(split, 1, a, s);
+    } else if (blocks64 * 2 <= ncu) {
+        launch_fitx_phase<2, 8, FX_ALL>(split, 1, a, s);
+    } else {
+        launch_fitx_phase<4, 8, FX_ALL>(split, 1, a, s);
+    }
 }
 
 }  // namespace dpk
