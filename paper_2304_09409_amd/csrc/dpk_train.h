@@ -78,6 +78,9 @@ constexpr int TRE_CHUNK = 130 * 64;
 // Adjoints of T and Td of an atom, over N_c: [layer-3 row position][T 4, Td 4], padding rows zero
 constexpr int TRE_TB = N3P * 8;
 constexpr int TRE_NET = 3 * E0 + E0 * E1 + 2 * E1 + E1 * E2 + 2 * E2;   // parameters of one embedding net
+// Copies of the embedding gradients that the blocks add to: a multiple of the XCDs while that is a few MB
+// (with more nets fewer blocks meet at an address).
+inline int tre_copies(int nets) { return nets <= 4 ? 32 : nets <= 9 ? 16 : nets <= 16 ? 8 : 1; }
 struct TreArgs {
     EmbArgs e;
     const int* toff;
@@ -88,6 +91,8 @@ struct TreArgs {
     double* Td;                   // [n][100][4] (tangent pass output)
     const double* Tb;             // [n][TRE_TB] adjoints of T and Td
     double* dump;
+    int nets, nrep;
+    double* rep;                  // [nrep][nets][TRE_NET], zero between frames
     double* grad;                 // gradient in the parameter layout (embedding nets first)
 };
 // Chunk offsets; coff[nt - 1][n] is the number of chunks.

@@ -77,7 +77,7 @@ struct dpk_trainer {
     DBuf theta, grad, mom1, mom2;
     // frame workspace
     IBuf coff, cmap;
-    DBuf fl, q, vdir, part, coef, Td, Tb, dump;
+    DBuf fl, q, vdir, part, coef, Td, Tb, dump, rep;
     DBuf D, Dd, Db, Ddb, a[3], y[3], zd[3], yd[3], zb[3], zdb[3], yb, ydb;
     TrCoef* pin = nullptr;        // pinned copy of coef, and behind it the number of chunks
     ~dpk_trainer() {
@@ -159,6 +159,9 @@ int frame(dpk_trainer* t, int64_t natoms, const double* coord, const int32_t* at
     e.Td = t->Td.p;
     e.Tb = t->Tb.p;
     e.dump = t->dump.p;
+    e.nets = t->nets;
+    e.nrep = tre_copies(t->nets);
+    e.rep = t->rep.p;
     e.grad = t->grad.p;
     TrfArgs a;
     std::memset(&a, 0, sizeof(a));
@@ -236,6 +239,7 @@ int dpk_trainer_create(const dpk_model* m, int device, dpk_trainer** out)
     }
     if (t->theta.ensure(np) != hipSuccess || t->grad.ensure(np) != hipSuccess || t->mom1.ensure(np) != hipSuccess ||
         t->mom2.ensure(np) != hipSuccess || t->coef.ensure(sizeof(TrCoef) / sizeof(double)) != hipSuccess ||
+        t->rep.ensure((size_t)tre_copies(t->nets) * t->nets * TRE_NET) != hipSuccess ||
         hipHostMalloc((void**)&t->pin, sizeof(TrCoef) + sizeof(int)) != hipSuccess) {
         hipGetLastError();
         delete t;
@@ -243,6 +247,7 @@ int dpk_trainer_create(const dpk_model* m, int device, dpk_trainer** out)
     }
     if (hipMemcpy(t->theta.p, p.data(), sizeof(double) * np, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemset(t->grad.p, 0, sizeof(double) * np) != hipSuccess ||
+        hipMemset(t->rep.p, 0, sizeof(double) * t->rep.n) != hipSuccess ||
         hipMemset(t->mom1.p, 0, sizeof(double) * np) != hipSuccess ||
         hipMemset(t->mom2.p, 0, sizeof(double) * np) != hipSuccess) {
         delete t;
