@@ -112,7 +112,8 @@ def stage_rooflines(stage_ms: dict, precision: str, natoms: int, npairs: int, nc
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_water12288.txt")
 KERNEL_SOURCES = ("paper_2304_09409_amd/csrc/kernels_nn.hip", "paper_2304_09409_amd/csrc/kernels_geom.hip",
                   "paper_2304_09409_amd/csrc/dpk_internal.h", "paper_2304_09409_amd/csrc/kernels_fit.hip",
-                  "paper_2304_09409_amd/csrc/kernels_tab.hip", "paper_2304_09409_amd/csrc/dpk_device.h")
+                  "paper_2304_09409_amd/csrc/kernels_tab.hip", "paper_2304_09409_amd/csrc/dpk_device.h",
+                  "paper_2304_09409_amd/csrc/kernels_fitd.hip", "paper_2304_09409_amd/csrc/emb_device.h")
 
 
 def kernel_source_digest() -> str:

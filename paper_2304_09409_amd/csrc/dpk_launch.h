@@ -61,7 +61,6 @@ int embed_bwd_blocks(int precision, bool table, int64_t natoms, int ncu, bool e3
 // E and the virial of a single frame from the backward pass's nb partials [E, virial[9]], and the
 // frame's dropped-neighbour count into st
 void launch_finalize(int nb, const double* part, double* energy, double* virial, DevStats* st, hipStream_t s);
-int fit_atoms_per_block(int precision);
 void launch_embed_fwd(int precision, bool table, const EmbArgs& a, hipStream_t s, bool e3 = false);
 void launch_embed_bwd(int precision, bool table, const EmbArgs& a, hipStream_t s, bool e3 = false);
 void launch_e3_env(int precision, const EmbArgs& a, hipStream_t s);

@@ -1,4 +1,4 @@
-// kernels_nn.hip -- embedding net with the descriptor contraction, fitting net, and the
+// kernels_nn.hip -- embedding net with the descriptor contraction, dense FP32 fitting net, and the
 // hand-written adjoint (prod_force / prod_virial) of the se_e2_a Deep Potential.
 //
 // Paper: Sec. II.A.1 (environment rows, switching function eq. switch, embedding eq. G2,
@@ -24,9 +24,9 @@
 //     LDS except the forward pass's layer 2 (the untransposed layer 3 reads it transposed).
 //   * The backward pass re-evaluates the net with its forward-mode derivative d/ds (the input is
 //     a scalar), rather than storing G: G would cost 400 B per neighbour in HBM.
-//   * Fitting: 16 atoms per wave, all 240 features per wave; every layer transposed (W^T as A)
-//     so each layer's output tiles are the next layer's B operand; the descriptor D = T T_<^T
-//     is formed on the fly in B-operand layout; the input gradient uses W as A.
+// The fitting net here (k_fit_dense) serves the FP32 path of the M x M_< descriptor: 16 atoms per wave, every
+// layer transposed, D = T T_<^T formed on the fly in B-operand layout, the input gradient with W as A. The
+// BF16 paths are in kernels_fit.hip, FP64 and the descriptors of M values in kernels_fitd.hip.
 #include <hip/hip_runtime.h>
 #include "dpk_device.h"
 #include "emb_device.h"
@@ -1197,7 +1197,6 @@ int embed_bwd_blocks(int precision, bool table, int64_t natoms, int ncu, bool e3
     if (precision == 3) return embed_bwd_blocks_p<PF32>(table, natoms, nmodels, ncu, e3);
     return embed_bwd_blocks_p<PBF16>(table, natoms, nmodels, ncu, e3);
 }
-int fit_atoms_per_block(int) { return FIT_AF; }
 
 // The three-body backward kernels are instantiated explicitly: the host pass emitted no launch stub
 // for the FP64 network variant from its implicit instantiation alone.
