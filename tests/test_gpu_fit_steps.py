@@ -3,7 +3,9 @@ tile). Against the oracle at the edges of a tile and on both sides of the rule t
 tiles with three species: 1,952 atoms), with the parity tests' bounds for mixed precision; and against the
 one-launch kernel: a cluster alone (in steps) and beside a second one 100 A away (one launch) has the same
 atomic energies bit for bit, every sum having the same order, and forces within 1e-12 eV/A (FP64 sums of
-some 200 terms below 10 eV/A in an order that varies: 200 * 10 * 2^-53 = 2e-13)."""
+some 200 terms below 10 eV/A in an order that varies: 200 * 10 * 2^-53 = 2e-13). The FP64 net's steps (16-atom
+tiles, up to 128 of them with one per species to spare) against the oracle on both sides of their rule, with the
+parity tests' FP64 bounds."""
 import numpy as np
 import pytest
 
@@ -49,3 +51,18 @@ def test_steps_equal_one_launch(precision):
     n = len(ta)
     np.testing.assert_array_equal(two["atom_energy"][:n], one["atom_energy"])
     np.testing.assert_allclose(two["force"][:n], one["force"], rtol=0, atol=1e-12)
+
+
+@pytest.mark.parametrize("counts", [(1, 0, 0), (15, 17, 32), (0, 1, 129), (670, 640, 650), (700, 720, 700)],
+                         ids=lambda c: "-".join(map(str, c)))
+def test_fp64_steps_match_oracle(counts):
+    from oracle import Oracle
+    from paper_2304_09409_amd import dpk
+    print(f"[case] fp64 {counts}", flush=True)
+    c, t, b = frame(counts, 4)
+    ref = Oracle(synth.SERVE_MODEL, synth.serve_params()).compute(c, t, b)
+    ctx = dpk.Context(dpk.Model(synth.SERVE_MODEL, synth.serve_params()), precision="fp64")
+    got = ctx.compute(c, t, b, atom_energy=True)
+    ctx.close()
+    np.testing.assert_allclose(got["force"], ref["force"], rtol=0, atol=1e-10)
+    np.testing.assert_allclose(got["atom_energy"], ref["atom_energy"], rtol=0, atol=1e-11)
