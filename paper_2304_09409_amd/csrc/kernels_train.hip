@@ -118,6 +118,11 @@ __global__ void __launch_bounds__(256) k_trf_desc_adj(TrfArgs A)
 //   TRF_BWD  layer l (1 or 2) to the pre-activation of layer l - 1: X = zbar_l, B = W^T;
 //   TRF_IN   layer 0 to D: X = zbar_0, B = W^T, stored.
 // TM = 64 with 32-deep K-chunks where that fills the device, else 32 with 64-deep ones.
+// Bound: the FP64 unit and the reads' latency, two blocks per CU. 12,288 atoms: forward layers 1,445 -> 738
+// us, layer 0 to D 608 -> 409, with the edge test moved from the reads to the LDS writes (the products
+// waited for the next chunk), two blocks per CU and the column tiles of a row tile on one XCD. 64-wide tiles
+// from one block per CU on: below that the 32-wide ones give four times the blocks (192 atoms, forward 28 us
+// per layer).
 // ---------------------------------------------------------------------------------------------
 enum { TRF_FWD, TRF_BWD, TRF_IN };
 
@@ -293,7 +298,9 @@ __global__ void __launch_bounds__(256) k_trf_out(TrfArgs A)
 }
 
 // Weight gradients of the three hidden layers, Wbar = X^T Zb + Xd^T Zdb over the rows: 64 x 64 tiles, the
-// rows split over blockIdx.y; FP64 atomics into the gradient.
+// rows in ranges; FP64 atomics into the gradient. Bound: the FP64 unit (350 us of products at 12,288 atoms)
+// and the latency of the rows' reads, two blocks per CU: 552 us, 1,031 with the tiles of a range on all XCDs
+// and the edge test on arrival (see k_trf_gemm).
 constexpr int WG_T1 = (DD / 64) * 4, WG_T2 = 16, WG_TILES = WG_T1 + 2 * WG_T2;
 __global__ void __launch_bounds__(256, 2) k_trf_wgrad(TrfArgs A, int splits, int grp)
 {
