@@ -205,21 +205,28 @@ inline int emb_pos(int precision, int l, int g, int u)
 // order: fragment (c, t) at frag0 + c * ntiles + t, lane 16g + i holding row 16t + i.
 // by_tile: fragment (c, t) at frag0 + t * nch + c instead (a product that walks the row tiles reads
 // consecutive memory: with the chunks 200 KB apart its fragments took about 2,500 cycles to arrive).
-template <class Fn>
+// The matrix is W [in][FW], its element (row, k) W[k][row] (forward, W^T) or W[row][k] (the reverse pass).
+// Fragments are written in memory order.
 void pack_frags(std::vector<uint16_t>& out, size_t frag0, int ntiles, int nch, int rows, int kdim, bool split,
-                bool by_tile, Fn&& w)
+                bool by_tile, const double* W, bool forward)
 {
-    for (int c = 0; c < nch; ++c)
-        for (int t = 0; t < ntiles; ++t)
+    const size_t rs = forward ? 1 : FW, ks = forward ? FW : 1;
+    uint16_t* o = &out[frag0 * XF_ELEMS];
+    for (int a = 0; a < (by_tile ? ntiles : nch); ++a)
+        for (int b = 0; b < (by_tile ? nch : ntiles); ++b, o += XF_ELEMS) {
+            const int c = by_tile ? b : a, t = by_tile ? a : b;
+            double x[512];   // the fragment's values in lane order, then their two parts
             for (int lane = 0; lane < 64; ++lane)
                 for (int j = 0; j < 8; ++j) {
                     const int row = 16 * t + (lane & 15), k = kidx32(c, lane >> 4, j);
-                    const double v = (row < rows && k < kdim) ? w(row, k) : 0.0;
-                    const uint16_t hb = bf16_bits((float)v);
-                    const size_t i = (frag0 + (by_tile ? (size_t)t * nch + c : (size_t)c * ntiles + t)) * XF_ELEMS + lane * 8 + j;
-                    out[i] = hb;
-                    out[i + 512] = split ? bf16_bits((float)(v - (double)bf16_float(hb))) : 0;
+                    x[8 * lane + j] = row < rows && k < kdim ? W[row * rs + k * ks] : 0.0;
                 }
+            for (int e = 0; e < 512; ++e) {
+                const uint16_t hb = bf16_bits((float)x[e]);
+                o[e] = hb;
+                o[512 + e] = split ? bf16_bits((float)(x[e] - (double)bf16_float(hb))) : 0;
+            }
+        }
 }
 
 // Dense matrix (row-major, `rows` x `cols`) in each plane's element type.
@@ -245,20 +252,25 @@ struct Planes {
 
 // One matrix of the fragment-major 16x16x4 weights (k_fitd): `rows` x `kdim`, zero-padded to whole
 // tiles and chunks, at `base` of P (FP64 or FP32).
-template <class Fn>
-void pack_frags4(Planes& P, size_t base0, int ntiles, int nch, int rows, int kdim, bool by_tile, Fn&& w)
+void pack_frags4(Planes& P, size_t base, int ntiles, int nch, int rows, int kdim, bool by_tile, const double* W,
+                 bool forward)
 {
     const bool f64 = P.precision == DPK_FP64;
+    const size_t rs = forward ? 1 : FW, ks = forward ? FW : 1;
     for (int a = 0; a < (by_tile ? ntiles : nch); ++a)
-        for (int b = 0; b < (by_tile ? nch : ntiles); ++b, base0 += 256) {
+        for (int b = 0; b < (by_tile ? nch : ntiles); ++b, base += 256) {
             const int c = by_tile ? b : a, t = by_tile ? a : b;
-            const size_t base = base0;
-            for (int lane = 0; lane < 64; ++lane)
+            for (int g = 0; g < 4; ++g)
                 for (int v = 0; v < 4; ++v) {
-                    const int g = lane >> 4, row = 16 * t + (lane & 15), k = 16 * c + (f64 ? g + 4 * v : 4 * g + v);
-                    const double x = row < rows && k < kdim ? w(row, k) : 0.0;
-                    if (f64) P.d[base + (v >> 1) * 128 + lane * 2 + (v & 1)] = x;
-                    else P.f[base + lane * 4 + v] = (float)x;
+                    const int k = 16 * c + (f64 ? g + 4 * v : 4 * g + v), n = k < kdim ? std::min(16, rows - 16 * t) : 0;
+                    const double* w = W + (size_t)k * ks + (size_t)16 * t * rs;
+                    if (f64) {
+                        double* o = &P.d[base + (v >> 1) * 128 + 32 * g + (v & 1)];
+                        for (int i = 0; i < 16; ++i) o[2 * i] = i < n ? w[i * rs] : 0.0;
+                    } else {
+                        float* o = &P.f[base + 64 * g + v];
+                        for (int i = 0; i < 16; ++i) o[4 * i] = i < n ? (float)w[i * rs] : 0.0f;
+                    }
                 }
         }
 }
@@ -635,24 +647,24 @@ int upload_model(dpk_ctx* c)
             const bool split = prec == DPK_MIXED;
             const size_t f0 = (size_t)t * XF_NFRAG;
             const double *W1 = L[0].W, *W2 = L[1].W, *W3 = L[2].W;
-            pack_frags(fx, f0 + XF_W1F, 15, XF_NCH1, FW, DD, split, false, [&](int o, int f) { return W1[(size_t)f * FW + o]; });
-            pack_frags(fx, f0 + XF_W2F, 15, XF_NCH2, FW, FW, split, false, [&](int o, int i) { return W2[(size_t)i * FW + o]; });
-            pack_frags(fx, f0 + XF_W3F, 15, XF_NCH2, FW, FW, split, false, [&](int o, int i) { return W3[(size_t)i * FW + o]; });
-            pack_frags(fx, f0 + XF_W3B, 15, XF_NCH2, FW, FW, split, false, [&](int i, int o) { return W3[(size_t)i * FW + o]; });
-            pack_frags(fx, f0 + XF_W2B, 15, XF_NCH2, FW, FW, split, false, [&](int i, int o) { return W2[(size_t)i * FW + o]; });
-            pack_frags(fx, f0 + XF_W1B, E2, XF_NCH2, DD, FW, split, true, [&](int f, int o) { return W1[(size_t)f * FW + o]; });
+            pack_frags(fx, f0 + XF_W1F, 15, XF_NCH1, FW, DD, split, false, W1, true);
+            pack_frags(fx, f0 + XF_W2F, 15, XF_NCH2, FW, FW, split, false, W2, true);
+            pack_frags(fx, f0 + XF_W3F, 15, XF_NCH2, FW, FW, split, false, W3, true);
+            pack_frags(fx, f0 + XF_W3B, 15, XF_NCH2, FW, FW, split, false, W3, false);
+            pack_frags(fx, f0 + XF_W2B, 15, XF_NCH2, FW, FW, split, false, W2, false);
+            pack_frags(fx, f0 + XF_W1B, E2, XF_NCH2, DD, FW, split, true, W1, false);
             continue;
         }
         const size_t base = (size_t)t * FM_SIZE;
         // layer 1: W1^T [240][K] and W1 [K][240], K = 1600 (M x M_<) or 112 (M, zero-padded)
         const int nin = radial ? E2 : DD, kw = radial ? N3P : DD;
         if (frag4) {
-            pack_frags4(fm, base + FM_W1T, 15, kw / 16, FW, nin, false, [&](int o, int f) { return L[0].W[(size_t)f * FW + o]; });
-            pack_frags4(fm, base + FM_W1, kw / 16, 15, nin, FW, true, [&](int f, int o) { return L[0].W[(size_t)f * FW + o]; });
+            pack_frags4(fm, base + FM_W1T, 15, kw / 16, FW, nin, false, L[0].W, true);
+            pack_frags4(fm, base + FM_W1, kw / 16, 15, nin, FW, true, L[0].W, false);
             for (int li = 1; li <= 2; ++li) {
                 const double* w = L[li].W;
-                pack_frags4(fm, base + (li == 1 ? FM_W2T : FM_W3T), 15, 15, FW, FW, false, [&](int o, int i) { return w[(size_t)i * FW + o]; });
-                pack_frags4(fm, base + (li == 1 ? FM_W2 : FM_W3), 15, 15, FW, FW, false, [&](int i, int o) { return w[(size_t)i * FW + o]; });
+                pack_frags4(fm, base + (li == 1 ? FM_W2T : FM_W3T), 15, 15, FW, FW, false, w, true);
+                pack_frags4(fm, base + (li == 1 ? FM_W2 : FM_W3), 15, 15, FW, FW, false, w, false);
             }
             continue;
         }
