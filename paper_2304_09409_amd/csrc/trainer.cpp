@@ -245,11 +245,7 @@ int dpk_trainer_create(const dpk_model* m, int device, dpk_trainer** out)
         delete t;
         return set_error(DPK_E_OOM, "hipMalloc of the trainer's parameter buffers failed");
     }
-    if (hipMemcpy(t->theta.p, p.data(), sizeof(double) * np, hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemset(t->grad.p, 0, sizeof(double) * np) != hipSuccess ||
-        hipMemset(t->rep.p, 0, sizeof(double) * t->rep.n) != hipSuccess ||
-        hipMemset(t->mom1.p, 0, sizeof(double) * np) != hipSuccess ||
-        hipMemset(t->mom2.p, 0, sizeof(double) * np) != hipSuccess) {
+    if (hipMemcpy(t->theta.p, p.data(), sizeof(double) * np, hipMemcpyHostToDevice) != hipSuccess) {
         delete t;
         return set_error(DPK_E_DEVICE, "copy of the parameters to the device failed");
     }
@@ -263,9 +259,11 @@ int dpk_trainer_create(const dpk_model* m, int device, dpk_trainer** out)
         }
         tr_map(w.p[k], w.n[k], t->map[k].p, w.stream);
     }
-    if (hipStreamSynchronize(w.stream) != hipSuccess) {
+    // (cleared on the stream that the frames run on, which the null stream does not wait for or hold up)
+    for (DBuf* b : {&t->grad, &t->rep, &t->mom1, &t->mom2}) launch_zero(b->p, sizeof(double) * b->n, w.stream);
+    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(w.stream) != hipSuccess) {
         delete t;
-        return set_error(DPK_E_DEVICE, "the packing maps' launch failed");
+        return set_error(DPK_E_DEVICE, "clearing the gradient or building the packing maps failed");
     }
     *out = t;
     return DPK_OK;
@@ -302,7 +300,10 @@ int dpk_trainer_zero_grad(dpk_trainer* t)
     if (!t) return set_error(DPK_E_INVALID_ARG, "NULL trainer");
     TRCHK(hipSetDevice(t->device));
     TRCHK(hipDeviceSynchronize());
-    TRCHK(hipMemset(t->grad.p, 0, sizeof(double) * t->np));
+    PackedWeights w;
+    packed_weights(t->geo, &w);
+    launch_zero(t->grad.p, sizeof(double) * t->np, w.stream);   // (ordered with the next frame or step)
+    TRCHK(hipGetLastError());
     return DPK_OK;
 }
 
@@ -315,7 +316,9 @@ int dpk_trainer_adam_step(dpk_trainer* t, double lr, double beta1, double beta2,
     t->step += 1;
     t->stale = true;
     const double c1 = 1.0 - std::pow(beta1, (double)t->step), c2 = 1.0 - std::pow(beta2, (double)t->step);
-    tr_adam(t->np, t->theta.p, t->grad.p, t->mom1.p, t->mom2.p, lr, beta1, beta2, eps, c1, c2, nullptr);
+    PackedWeights w;
+    packed_weights(t->geo, &w);
+    tr_adam(t->np, t->theta.p, t->grad.p, t->mom1.p, t->mom2.p, lr, beta1, beta2, eps, c1, c2, w.stream);
     TRCHK(hipGetLastError());
     TRCHK(hipDeviceSynchronize());
     return DPK_OK;
