@@ -73,8 +73,12 @@ int tr_loss_blocks(int n);
 void tr_loss(const TrLossArgs& a, hipStream_t s);
 
 // Embedding nets. Chunks of 16 kept neighbours of one atom and neighbour type; coff [nt][n + 1] their
-// offsets (by neighbour type, then atom). dump: TRE_CHUNK doubles per chunk.
+// offsets (by neighbour type, then atom). dump: TRE_CHUNK doubles per chunk, for a window of chunks at a
+// time: 66.5 KB per chunk would otherwise hold 16 kept neighbours or one alike, and a frame of many types
+// with few neighbours of each needs a chunk for almost every pair. TRE_WINDOW chunks take 8.7 GB (a frame of
+// 12,288 water atoms has 73,800); with less memory free the windows are shorter, TRE_WINDOW_MIN at least.
 constexpr int TRE_CHUNK = 130 * 64;
+constexpr int TRE_WINDOW = 1 << 17, TRE_WINDOW_MIN = 1 << 10;
 // Adjoints of T and Td of an atom, over N_c: [layer-3 row position][T 4, Td 4], padding rows zero
 constexpr int TRE_TB = N3P * 8;
 constexpr int TRE_NET = 3 * E0 + E0 * E1 + 2 * E1 + E1 * E2 + 2 * E2;   // parameters of one embedding net
@@ -90,10 +94,12 @@ struct TreArgs {
     const TrCoef* coef;
     double* Td;                   // [n][100][4] (tangent pass output)
     const double* Tb;             // [n][TRE_TB] adjoints of T and Td
-    double* dump;
+    double* dump;                 // [window][TRE_CHUNK]
     int nets, nrep;
     double* rep;                  // [nrep][nets][TRE_NET], zero between frames
     double* grad;                 // gradient in the parameter layout (embedding nets first)
+    int chunks, window;           // chunks of the frame, and at most as many of them at a time
+    int* woff;                    // as coff, of a window (window < chunks)
 };
 // Chunk offsets; coff[nt - 1][n] is the number of chunks.
 void tre_offsets(int n, int nt, const int* nnei, int* coff, hipStream_t s);

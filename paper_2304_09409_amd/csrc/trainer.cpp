@@ -76,7 +76,7 @@ struct dpk_trainer {
     IBuf map[4];
     DBuf theta, grad, mom1, mom2;
     // frame workspace
-    IBuf coff, cmap;
+    IBuf coff, cmap, woff;
     DBuf fl, q, vdir, part, coef, Td, Tb, dump, rep;
     DBuf D, Dd, Db, Ddb, a[3], y[3], zd[3], yd[3], zb[3], zdb[3], yb, ydb;
     TrCoef* pin = nullptr;        // pinned copy of coef, and behind it the number of chunks
@@ -88,6 +88,19 @@ struct dpk_trainer {
 };
 
 namespace {
+
+// The operand blocks of the frame's chunks, or of a window of them: an eighth more than needed, for the next
+// frame, if there is room; half as many while there is none.
+hipError_t dump_window(dpk_trainer* t, size_t chunks)
+{
+    const size_t need = std::min<size_t>(std::max<size_t>(chunks, 1), TRE_WINDOW);
+    if (need * TRE_CHUNK <= t->dump.n) return hipSuccess;
+    for (size_t w = std::min<size_t>(need + need / 8, TRE_WINDOW);; w = w > need ? need : std::max<size_t>(w / 2, TRE_WINDOW_MIN)) {
+        const hipError_t e = t->dump.ensure(w * TRE_CHUNK);
+        if (e != hipErrorOutOfMemory || w <= TRE_WINDOW_MIN) return e;
+        hipGetLastError();
+    }
+}
 
 int frame(dpk_trainer* t, int64_t natoms, const double* coord, const int32_t* atype, const double* box,
           const dpk_loss_spec* spec, double weight, double* loss, double* energy, double* force, double* virial)
@@ -107,13 +120,8 @@ int frame(dpk_trainer* t, int64_t natoms, const double* coord, const int32_t* at
     if (rc) return rc;
     hipStream_t s = f.stream;
     const int n = f.n, nt = t->nt;
-    // workspace (the chunks as found, not as many as sel would allow; an eighth more for the next frame)
-    const size_t nz = n, chunks = std::max(1, *pin_chunks);
+    const size_t nz = n, chunks = std::max(0, *pin_chunks);   // (the chunks as found, not as many as sel would allow)
     TRCHK(t->cmap.ensure(4 * chunks));
-    if (chunks * TRE_CHUNK > t->dump.n && t->dump.ensure((chunks + chunks / 8) * TRE_CHUNK) != hipSuccess) {
-        hipGetLastError();
-        TRCHK(t->dump.ensure(chunks * TRE_CHUNK));
-    }
     for (DBuf* b : {&t->fl, &t->vdir}) TRCHK(b->ensure(3 * nz));
     TRCHK(t->q.ensure(nz));
     TRCHK(t->part.ensure(tr_loss_blocks(n)));
@@ -123,6 +131,9 @@ int frame(dpk_trainer* t, int64_t natoms, const double* coord, const int32_t* at
     for (int l = 0; l < 3; ++l)
         for (DBuf* b : {&t->a[l], &t->y[l], &t->zd[l], &t->yd[l], &t->zb[l], &t->zdb[l]}) TRCHK(b->ensure((size_t)FW * nz));
     for (DBuf* b : {&t->yb, &t->ydb}) TRCHK(b->ensure((size_t)FW * nz));
+    TRCHK(dump_window(t, chunks));   // (last: what the frame cannot do without comes first)
+    const size_t window = std::min<size_t>(t->dump.n / TRE_CHUNK, TRE_WINDOW);
+    if (window < chunks) TRCHK(t->woff.ensure((nz + 1) * nt));
     // loss and direction
     TrLossArgs la;
     std::memset(&la, 0, sizeof(la));
@@ -159,6 +170,9 @@ int frame(dpk_trainer* t, int64_t natoms, const double* coord, const int32_t* at
     e.Td = t->Td.p;
     e.Tb = t->Tb.p;
     e.dump = t->dump.p;
+    e.chunks = (int)chunks;
+    e.window = (int)window;
+    e.woff = t->woff.p;
     e.nets = t->nets;
     e.nrep = tre_copies(t->nets);
     e.rep = t->rep.p;
