@@ -16,6 +16,7 @@
 #include "dpk_internal.h"
 
 struct dpk_ctx;
+struct dpk_model;
 
 namespace dpk {
 
@@ -44,6 +45,7 @@ struct PackedWeights {
     hipStream_t stream;    // the context's stream
 };
 void packed_weights(dpk_ctx* c, PackedWeights* w);
+const double* model_params(const dpk_model* m);   // host, in the blob's order
 
 // Loss, its coefficients and the energy and virial of the frame (device).
 struct TrCoef {

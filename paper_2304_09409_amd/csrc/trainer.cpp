@@ -73,11 +73,13 @@ struct dpk_trainer {
     int64_t np = 0;
     int64_t step = 0;
     bool stale = true;            // the packed weights are older than theta
-    IBuf map[4];
-    DBuf theta, grad, mom1, mom2;
+    IBuf map;                     // packing maps of the four packed buffers, one after the other
+    // the parameters, and what is cleared at the start: gradient, its copies, moments (one allocation)
+    DBuf state;
+    double *theta = nullptr, *grad = nullptr, *rep = nullptr, *mom1 = nullptr, *mom2 = nullptr;
     // frame workspace
     IBuf coff, cmap, woff;
-    DBuf fl, q, vdir, part, coef, Td, Tb, dump, rep;
+    DBuf fl, q, vdir, part, coef, Td, Tb, dump;
     DBuf D, Dd, Db, Ddb, a[3], y[3], zd[3], yd[3], zb[3], zdb[3], yb, ydb;
     TrCoef* pin = nullptr;        // pinned copy of coef, and behind it the number of chunks
     ~dpk_trainer() {
@@ -108,7 +110,8 @@ int frame(dpk_trainer* t, int64_t natoms, const double* coord, const int32_t* at
     PackedWeights w;
     packed_weights(t->geo, &w);
     if (t->stale) {
-        for (int k = 0; k < 4; ++k) tr_pack(t->theta.p, t->map[k].p, w.n[k], w.p[k], w.stream);
+        const int* map = t->map.p;
+        for (int k = 0; k < 4; map += w.n[k++]) tr_pack(t->theta, map, w.n[k], w.p[k], w.stream);
         TRCHK(hipGetLastError());
         t->stale = false;
     }
@@ -175,8 +178,8 @@ int frame(dpk_trainer* t, int64_t natoms, const double* coord, const int32_t* at
     e.woff = t->woff.p;
     e.nets = t->nets;
     e.nrep = tre_copies(t->nets);
-    e.rep = t->rep.p;
-    e.grad = t->grad.p;
+    e.rep = t->rep;
+    e.grad = t->grad;
     TrfArgs a;
     std::memset(&a, 0, sizeof(a));
     a.n = n;
@@ -186,8 +189,8 @@ int frame(dpk_trainer* t, int64_t natoms, const double* coord, const int32_t* at
         a.max_rows = std::max(a.max_rows, a.rows[ty + 1]);
         a.rows[ty + 1] += a.rows[ty];
     }
-    a.theta = t->theta.p;
-    a.grad = t->grad.p;
+    a.theta = t->theta;
+    a.grad = t->grad;
     a.fit0 = (int64_t)t->nets * TRE_NET;
     a.T = f.T;
     a.Td = t->Td.p;
@@ -234,8 +237,7 @@ int dpk_trainer_create(const dpk_model* m, int device, dpk_trainer** out)
     if (rc) return rc;
     if (d.descriptor != DPK_SE_E2_A) return set_error(DPK_E_UNIMPLEMENTED, "training covers se_e2_a models");
     const int64_t np = dpk_model_param_count(&d);
-    std::vector<double> p(np), number(np);
-    if ((rc = dpk_model_describe(m, nullptr, p.data(), nullptr, nullptr))) return rc;
+    std::vector<double> number(np);
     // the context is packed from the numbers of the parameters, which gives the packing maps
     for (int64_t i = 0; i < np; ++i) number[i] = (double)(i + 1);
     auto* t = new dpk_trainer;
@@ -251,30 +253,29 @@ int dpk_trainer_create(const dpk_model* m, int device, dpk_trainer** out)
         delete t;
         return rc;
     }
-    if (t->theta.ensure(np) != hipSuccess || t->grad.ensure(np) != hipSuccess || t->mom1.ensure(np) != hipSuccess ||
-        t->mom2.ensure(np) != hipSuccess || t->coef.ensure(sizeof(TrCoef) / sizeof(double)) != hipSuccess ||
-        t->rep.ensure((size_t)tre_copies(t->nets) * t->nets * TRE_NET) != hipSuccess ||
+    PackedWeights w;
+    packed_weights(t->geo, &w);
+    const size_t nrep = (size_t)tre_copies(t->nets) * t->nets * TRE_NET, clear = 3 * (size_t)np + nrep;
+    if (t->state.ensure(np + clear) != hipSuccess || t->map.ensure(w.n[0] + w.n[1] + w.n[2] + w.n[3]) != hipSuccess ||
+        t->coef.ensure(sizeof(TrCoef) / sizeof(double)) != hipSuccess ||
         hipHostMalloc((void**)&t->pin, sizeof(TrCoef) + sizeof(int)) != hipSuccess) {
         hipGetLastError();
         delete t;
         return set_error(DPK_E_OOM, "hipMalloc of the trainer's parameter buffers failed");
     }
-    if (hipMemcpy(t->theta.p, p.data(), sizeof(double) * np, hipMemcpyHostToDevice) != hipSuccess) {
+    t->theta = t->state.p;
+    t->grad = t->theta + np;
+    t->mom1 = t->grad + np;
+    t->mom2 = t->mom1 + np;
+    t->rep = t->mom2 + np;
+    if (hipMemcpy(t->theta, model_params(m), sizeof(double) * np, hipMemcpyHostToDevice) != hipSuccess) {
         delete t;
         return set_error(DPK_E_DEVICE, "copy of the parameters to the device failed");
     }
-    PackedWeights w;
-    packed_weights(t->geo, &w);
-    for (int k = 0; k < 4; ++k) {
-        if (t->map[k].ensure(w.n[k]) != hipSuccess) {
-            hipGetLastError();
-            delete t;
-            return set_error(DPK_E_OOM, "hipMalloc of the trainer's packing maps failed");
-        }
-        tr_map(w.p[k], w.n[k], t->map[k].p, w.stream);
-    }
+    int* map = t->map.p;
+    for (int k = 0; k < 4; map += w.n[k++]) tr_map(w.p[k], w.n[k], map, w.stream);
     // (cleared on the stream that the frames run on, which the null stream does not wait for or hold up)
-    for (DBuf* b : {&t->grad, &t->rep, &t->mom1, &t->mom2}) launch_zero(b->p, sizeof(double) * b->n, w.stream);
+    launch_zero(t->grad, sizeof(double) * clear, w.stream);
     if (hipGetLastError() != hipSuccess || hipStreamSynchronize(w.stream) != hipSuccess) {
         delete t;
         return set_error(DPK_E_DEVICE, "clearing the gradient or building the packing maps failed");
@@ -305,7 +306,7 @@ int dpk_trainer_gradient(dpk_trainer* t, double* grad)
     if (!t || !grad) return set_error(DPK_E_INVALID_ARG, "NULL argument");
     TRCHK(hipSetDevice(t->device));
     TRCHK(hipDeviceSynchronize());
-    TRCHK(hipMemcpy(grad, t->grad.p, sizeof(double) * t->np, hipMemcpyDeviceToHost));
+    TRCHK(hipMemcpy(grad, t->grad, sizeof(double) * t->np, hipMemcpyDeviceToHost));
     return DPK_OK;
 }
 
@@ -316,7 +317,7 @@ int dpk_trainer_zero_grad(dpk_trainer* t)
     TRCHK(hipDeviceSynchronize());
     PackedWeights w;
     packed_weights(t->geo, &w);
-    launch_zero(t->grad.p, sizeof(double) * t->np, w.stream);   // (ordered with the next frame or step)
+    launch_zero(t->grad, sizeof(double) * t->np, w.stream);   // (ordered with the next frame or step)
     TRCHK(hipGetLastError());
     return DPK_OK;
 }
@@ -332,7 +333,7 @@ int dpk_trainer_adam_step(dpk_trainer* t, double lr, double beta1, double beta2,
     const double c1 = 1.0 - std::pow(beta1, (double)t->step), c2 = 1.0 - std::pow(beta2, (double)t->step);
     PackedWeights w;
     packed_weights(t->geo, &w);
-    tr_adam(t->np, t->theta.p, t->grad.p, t->mom1.p, t->mom2.p, lr, beta1, beta2, eps, c1, c2, w.stream);
+    tr_adam(t->np, t->theta, t->grad, t->mom1, t->mom2, lr, beta1, beta2, eps, c1, c2, w.stream);
     TRCHK(hipGetLastError());
     TRCHK(hipDeviceSynchronize());
     return DPK_OK;
@@ -343,7 +344,7 @@ int dpk_trainer_params(dpk_trainer* t, double* params)
     if (!t || !params) return set_error(DPK_E_INVALID_ARG, "NULL argument");
     TRCHK(hipSetDevice(t->device));
     TRCHK(hipDeviceSynchronize());
-    TRCHK(hipMemcpy(params, t->theta.p, sizeof(double) * t->np, hipMemcpyDeviceToHost));
+    TRCHK(hipMemcpy(params, t->theta, sizeof(double) * t->np, hipMemcpyDeviceToHost));
     return DPK_OK;
 }
 
@@ -352,7 +353,7 @@ int dpk_trainer_set_params(dpk_trainer* t, const double* params)
     if (!t || !params) return set_error(DPK_E_INVALID_ARG, "NULL argument");
     TRCHK(hipSetDevice(t->device));
     TRCHK(hipDeviceSynchronize());
-    TRCHK(hipMemcpy(t->theta.p, params, sizeof(double) * t->np, hipMemcpyHostToDevice));
+    TRCHK(hipMemcpy(t->theta, params, sizeof(double) * t->np, hipMemcpyHostToDevice));
     t->stale = true;
     return DPK_OK;
 }
