@@ -55,3 +55,23 @@ def test_list_equals_oracle(case):
     np.testing.assert_array_equal(ctx.debug_nlist(len(t)), ref["nlist"])
     assert ctx.stats()["nbr_dropped"] == ref["ndrop"]
     ctx.close()
+
+
+@pytest.mark.parametrize("case", list(CASES))
+def test_displacements_give_the_oracle_forces(case):
+    """The list's r_ij are rebuilt from the run packed into each key, so a wrong run or image shift would leave
+    the indices as they are (most of all where an atom's neighbours are its own images): forces and virial of
+    the FP64 path, whose error is within 1e-10 plus 1e-11 of the largest (random pairs come close, and a force
+    is a sum of terms up to a few hundred times its size)."""
+    from oracle import Oracle
+    from paper_2304_09409_amd import dpk
+    print(f"[case] {case}", flush=True)
+    c, t, b = CASES[case]()
+    params = synth.water_params()
+    ref = Oracle(synth.WATER_MODEL, params).compute(c, t, b)
+    ctx = dpk.Context(dpk.Model(synth.WATER_MODEL, params), precision="fp64")
+    got = ctx.compute(c, t, b)
+    for key in ("force", "virial"):
+        r = np.asarray(ref[key]).reshape(-1)
+        assert np.abs(np.asarray(got[key]).reshape(-1) - r).max() <= 1e-10 + 1e-11 * np.abs(r).max(), key
+    ctx.close()
