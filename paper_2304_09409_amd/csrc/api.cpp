@@ -2623,3 +2623,15 @@ void dpk::packed_weights(dpk_ctx* c, PackedWeights* w)
 }
 
 const double* dpk::model_params(const dpk_model* m) { return m->params.data(); }
+
+dpk_model* dpk::numbered_model(const dpk_model* m)
+{
+    dpk_model* q = new dpk_model;
+    q->desc = m->desc;
+    q->nets = m->nets;
+    q->nc = m->nc;
+    q->params.reserve(m->params.size());
+    for (size_t i = 0; i < m->params.size(); ++i) q->params.push_back((double)(i + 1));
+    index_layers(q);
+    return q;
+}

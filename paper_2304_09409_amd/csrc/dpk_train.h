@@ -46,6 +46,7 @@ struct PackedWeights {
 };
 void packed_weights(dpk_ctx* c, PackedWeights* w);
 const double* model_params(const dpk_model* m);   // host, in the blob's order
+dpk_model* numbered_model(const dpk_model* m);    // of m's description, the parameters 1, 2, 3, ...
 
 // Loss, its coefficients and the energy and virial of the frame (device).
 struct TrCoef {

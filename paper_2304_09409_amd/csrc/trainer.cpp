@@ -17,7 +17,6 @@
 #include <cmath>
 #include <cstring>
 #include <string>
-#include <vector>
 
 #include "../../include/dpk.h"
 #include "dpk_launch.h"
@@ -237,9 +236,6 @@ int dpk_trainer_create(const dpk_model* m, int device, dpk_trainer** out)
     if (rc) return rc;
     if (d.descriptor != DPK_SE_E2_A) return set_error(DPK_E_UNIMPLEMENTED, "training covers se_e2_a models");
     const int64_t np = dpk_model_param_count(&d);
-    std::vector<double> number(np);
-    // the context is packed from the numbers of the parameters, which gives the packing maps
-    for (int64_t i = 0; i < np; ++i) number[i] = (double)(i + 1);
     auto* t = new dpk_trainer;
     t->desc = d;
     t->device = device;
@@ -248,8 +244,9 @@ int dpk_trainer_create(const dpk_model* m, int device, dpk_trainer** out)
     t->nc = 0;
     for (int ty = 0; ty < d.ntypes; ++ty) t->nc += d.sel[ty];
     t->np = np;
-    if ((rc = dpk_model_create(&d, number.data(), np, &t->model)) ||
-        (rc = dpk_ctx_create(t->model, device, DPK_FP64, 0, 0, &t->geo))) {
+    // the context is packed from the numbers of the parameters, which gives the packing maps
+    t->model = numbered_model(m);
+    if ((rc = dpk_ctx_create(t->model, device, DPK_FP64, 0, 0, &t->geo))) {
         delete t;
         return rc;
     }
