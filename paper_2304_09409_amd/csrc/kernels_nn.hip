@@ -388,7 +388,7 @@ __global__ void __launch_bounds__((EmbCfg<P, true, TAB>::NW * 64)) k_embed_fwd(E
 //   g_ij = dE/dr_ij = [(dR_0 + dE/ds) s' + q (s' - s/r)] r^ + (s/r) dR_{1:3},  q = dR_{1:3} . r^,
 //   F_i += g_ij, F_j -= g_ij (FP64 atomics into caller order), Xi_ab -= g_ij,a r_ij,b (FP64,
 //   per-block partials, with E over the block's atoms for a single frame).
-// E3 (three-body descriptor, one atom per wave): a pair row gives
+// E3 (three-body descriptor, up to E3_APW atoms per wave, one after the other): a pair row gives
 //   dE/dtheta_jk = N_c^-2 sum_m dD_m (G_m + theta dG_m/dtheta)   (dT[m][0] = dE/dD_m),
 // and theta_jk = R_j . R_k adds dE/dtheta R_k to dE/dR_j and dE/dtheta R_j to dE/dR_k (LDS
 // atomics into the wave's slot rows); after the last pass each slot's dE/dR_j goes through the

@@ -16,11 +16,12 @@
 // Layouts as in the embedding kernels: features in registers and lane groups, one pair per lane column,
 // in the skip-aligned order, so every skip and its transpose stay in a lane. One wave per SIMD (up to
 // 512 registers: the layers' values, the running adjoints and the w_hat sums).
-// Bound: the FP64 unit (k_tre_tan 252, k_tre_adj 532, k_tre_wgrad 288 products of 65 cycles per chunk,
-// plus the vector work, with one wave per SIMD to hide its latencies) and, for k_tre_wgrad, reading the 65
-// KiB per chunk that k_tre_adj wrote (4.2 TB/s). 12,288 atoms (73,800 chunks): k_tre_tan 1,110-1,130 us,
-// k_tre_adj 2,040, k_tre_wgrad 1,180; 192 atoms 43, 89 and 80. With whole atoms per wave, and one copy of the
-// gradient, 192 atoms took 106, 239 and 106.
+// Bound: the FP64 unit (k_tre_tan 252, k_tre_adj 532 products of 65 cycles per chunk, k_tre_wgrad 320, of
+// which 32 are waves 3 and 7 repeating their tile of W3, whose sum is dropped; plus the vector work, with one
+// wave per SIMD to hide its latencies) and, for k_tre_wgrad, reading the 65 KiB per chunk that k_tre_adj
+// wrote (4.2 TB/s). 12,288 atoms (73,800 chunks), the means of several runs: k_tre_tan 1,110-1,200 us,
+// k_tre_adj 1,990-2,060, k_tre_wgrad 1,130-1,180; 192 atoms 43, 90 and 80. With whole atoms per wave, and one
+// copy of the gradient, 192 atoms took 106, 239 and 106.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
