@@ -14,6 +14,7 @@
 #include <stdint.h>
 
 #include "dpk_internal.h"
+#include "train_window.h"
 
 struct dpk_ctx;
 struct dpk_model;
@@ -78,10 +79,8 @@ void tr_loss(const TrLossArgs& a, hipStream_t s);
 // Embedding nets. Chunks of 16 kept neighbours of one atom and neighbour type; coff [nt][n + 1] their
 // offsets (by neighbour type, then atom). dump: TRE_CHUNK doubles per chunk, for a window of chunks at a
 // time: 66.5 KB per chunk would otherwise hold 16 kept neighbours or one alike, and a frame of many types
-// with few neighbours of each needs a chunk for almost every pair. TRE_WINDOW chunks take 8.7 GB (a frame of
-// 12,288 water atoms has 73,800); with less memory free the windows are shorter, TRE_WINDOW_MIN at least.
+// with few neighbours of each needs a chunk for almost every pair (train_window.h).
 constexpr int TRE_CHUNK = 130 * 64;
-constexpr int TRE_WINDOW = 1 << 17, TRE_WINDOW_MIN = 1 << 10;
 // Adjoints of T and Td of an atom, over N_c: [layer-3 row position][T 4, Td 4], padding rows zero
 constexpr int TRE_TB = N3P * 8;
 constexpr int TRE_NET = 3 * E0 + E0 * E1 + 2 * E1 + E1 * E2 + 2 * E2;   // parameters of one embedding net

@@ -90,17 +90,14 @@ struct dpk_trainer {
 
 namespace {
 
-// The operand blocks of the frame's chunks, or of a window of them: an eighth more than needed, for the next
-// frame, if there is room; half as many while there is none.
+// The operand blocks of the frame's chunks, or of a window of them.
 hipError_t dump_window(dpk_trainer* t, size_t chunks)
 {
-    const size_t need = std::min<size_t>(std::max<size_t>(chunks, 1), TRE_WINDOW);
-    if (need * TRE_CHUNK <= t->dump.n) return hipSuccess;
-    for (size_t w = std::min<size_t>(need + need / 8, TRE_WINDOW);; w = w > need ? need : std::max<size_t>(w / 2, TRE_WINDOW_MIN)) {
-        const hipError_t e = t->dump.ensure(w * TRE_CHUNK);
-        if (e != hipErrorOutOfMemory || w <= TRE_WINDOW_MIN) return e;
-        hipGetLastError();
-    }
+    return window_alloc(t->dump.n / TRE_CHUNK, chunks, hipSuccess, hipErrorOutOfMemory, [&](size_t n) {
+        const hipError_t e = t->dump.ensure(n * TRE_CHUNK);
+        if (e == hipErrorOutOfMemory) hipGetLastError();
+        return e;
+    });
 }
 
 int frame(dpk_trainer* t, int64_t natoms, const double* coord, const int32_t* atype, const double* box,
